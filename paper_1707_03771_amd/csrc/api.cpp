@@ -261,7 +261,7 @@ int64_t dfx::jk_need(int nbf, int naux, int64_t ncols_t) {
     const JKArgs a{nullptr, nullptr, naux, nbf, ncols_t, p};
     for (int nocc = 1; nocc <= std::min(nbf, 512); ++nocc) kmax = std::max<int64_t>(kmax, k_work_bytes(a, nocc));
   }
-  const int64_t jw = pad256(8 * (2 * ncols_t + naux + 8)) + pad256(8 * n2);
+  const int64_t jw = pad256((int64_t)j_work_bytes(nbf, naux, ncols_t));
   // the density route adds its eigen-decomposition (and eigenvectors), one K
   // and a chunk of 512 columns
   const int64_t dens = pad256(8 * n2) * 2 + pad256(8 * (int64_t)nbf) + pad256(8 * (int64_t)nbf * 512) +
@@ -845,26 +845,11 @@ int dfx_jk(const dfx_B* bc, const double* dev_in, int kind, int nocc, int precis
     JKArgs a{b->hi.as<float>(), b->lo.as<float>(), b->naux, b->nbf, b->ncols_t, precision};
     const int nbf = b->nbf;
     size_t need = 0;
-    const size_t jw = sizeof(double) * (2 * (size_t)b->ncols_t + b->naux + 8);
-    const size_t dbytes = (kind == DFX_COCC) ? sizeof(double) * (size_t)nbf * nbf : 0;
-    if (dev_J) need = std::max(need, jw + dbytes);
+    if (dev_J) need = std::max(need, j_work_bytes(nbf, b->naux, b->ncols_t));
     if (dev_K && kind == DFX_COCC) need = std::max(need, k_work_bytes(a, nocc));
     char* w = static_cast<char*>(b->ensure_work(need));
-    if (dev_J) {
-      const double* D = dev_in;
-      if (kind == DFX_COCC) {
-        double* Dd = reinterpret_cast<double*>(w + jw);
-        GemmF64 g{};
-        g.M = nbf; g.N = nbf; g.K = nocc;
-        g.A = dev_in; g.lda = nocc;
-        g.B = dev_in; g.ldb = nocc; g.tb = true;
-        g.C = Dd; g.ldc = nbf;
-        g.alpha = 1.0; g.beta = 0.0; g.batch = 1;
-        dgemm(g, st);
-        D = Dd;
-      }
-      j_build(a, D, dev_J, reinterpret_cast<double*>(w), st);
-    }
+    if (dev_J && kind == DFX_COCC) j_build_cocc(a, dev_in, nocc, dev_J, reinterpret_cast<double*>(w), st);
+    if (dev_J && kind == DFX_DENSITY) j_build(a, dev_in, dev_J, reinterpret_cast<double*>(w), st);
     if (dev_K && kind == DFX_COCC) k_build(a, dev_in, nocc, dev_K, w, st);
     if (dev_K && kind == DFX_DENSITY) k_from_density(a, dev_in, dev_K, st);
     DFX_HIP(hipGetLastError());

@@ -186,7 +186,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
     scale_cols(Cd.as<double>(), ed.as<double>(), n, nocc, Ce.as<double>(), st);
     gemm(n, n, nocc, Ce.as<double>(), nocc, false, Cd.as<double>(), nocc, true, Wm.as<double>(), n, 1.0);
     const JKArgs ja{B->hi.as<float>(), B->lo.as<float>(), naux, n, B->ncols_t, PREC_FP64};
-    DevMem gam(8 * (size_t)naux), dvec(8 * (size_t)B->ncols_t);
+    DevMem gam(8 * (size_t)naux), dvec(j_gamma_work_bytes(n, naux, B->ncols_t));
     j_gamma(ja, D.as<double>(), gam.as<double>(), dvec.as<double>(), st);
     dvec.release();
 

@@ -6,6 +6,8 @@
 //      K_mu nu = sum_Q sum_i X_Q,mu i X_Q,nu i       (Eq. 2a)
 // B is stored as two FP32 words (hi, lo) per element in the packed 32x32 tile
 // layout (common.h).  The FP64 path reads hi + lo; the mixed path reads hi.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace dfx {
@@ -34,29 +36,60 @@ __global__ void pack_density_kernel(const double* __restrict__ D, int nbf, doubl
   }
 }
 
+// The same from the occupied block, D = C C^T: one workgroup per tile, its four
+// waves one 16 x 16 quadrant each on v_mfma_f64_16x16x4f64, operands straight
+// from C (a few hundred KB, in L2).  Replaces a DGEMM for D (4 to 36 tiles of
+// 128 x 128 at nbf = 192 to 730: 21 to 30 us on a mostly idle chip) and the
+// packing pass after it; 4 us at nbf = 192, nocc = 40.
+__global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict__ C, int nbf, int nocc,
+                                                        double* __restrict__ d) {
+  const int t = blockIdx.x;
+  int I, J;
+  tile_ij(t, I, J);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int r0 = (w >> 1) * 16, c0 = (w & 1) * 16;
+  const int r = I * TILE + r0 + li, c = J * TILE + c0 + li;
+  const double* __restrict__ pr = C + (int64_t)(r < nbf ? r : 0) * nocc;
+  const double* __restrict__ pc = C + (int64_t)(c < nbf ? c : 0) * nocc;
+  v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int k = 0; k < nocc; k += 4) {
+    const bool in = k + lk < nocc;
+    const double a = in && r < nbf ? pr[k + lk] : 0.0;
+    const double b = in && c < nbf ? pc[k + lk] : 0.0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+  }
+  const double wt = (I == J) ? 1.0 : 2.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) d[(int64_t)t * TILE2 + (r0 + 4 * q + lk) * TILE + c0 + li] = wt * acc[q];
+}
+
 // gamma_Q = sum_c B[Q][c] d[c], B = hi + lo, FP64 accumulation.  A workgroup
 // takes JG_Q consecutive Q, so each element of d is fetched once per JG_Q rows
 // of B (d is as long as a row of B: read once per Q it doubled the kernel's
-// traffic).  Every Q keeps the same per-thread column order and tree, so the
-// result does not depend on JG_Q.
+// traffic), and blockIdx.y'th of the column tiles: gp[y][Q] is its part of the
+// sum, which the readers of gamma add in order (j_plan: enough workgroups to
+// fill the chip where naux / JG_Q alone does not).
 constexpr int JG_Q = 4;
 __global__ void __launch_bounds__(256) j_gamma_kernel(const float* __restrict__ hi,
                                                       const float* __restrict__ lo, int64_t ncols, int naux,
-                                                      const double* __restrict__ d, double* gam) {
+                                                      const double* __restrict__ d, int tchunk,
+                                                      double* __restrict__ gp) {
   const int Q0 = blockIdx.x * JG_Q;
   const int nq = min(JG_Q, naux - Q0);
-  const double4* d4 = reinterpret_cast<const double4*>(d);
-  const int64_t n4 = ncols >> 2;
+  const int64_t c0 = (int64_t)blockIdx.y * tchunk * TILE2;
+  const int64_t c1 = min(c0 + (int64_t)tchunk * TILE2, ncols);
   double s[JG_Q];
 #pragma unroll
   for (int k = 0; k < JG_Q; ++k) s[k] = 0.0;
-  for (int64_t i = threadIdx.x; i < n4; i += blockDim.x) {
-    const double4 dd = d4[i];
+  for (int64_t c = c0 + 4 * threadIdx.x; c < c1; c += TILE2) {
+    const double4 dd = *reinterpret_cast<const double4*>(d + c);
 #pragma unroll
     for (int k = 0; k < JG_Q; ++k) {
       if (k < nq) {
-        const float4 h = reinterpret_cast<const float4*>(hi + (int64_t)(Q0 + k) * ncols)[i];
-        const float4 l = reinterpret_cast<const float4*>(lo + (int64_t)(Q0 + k) * ncols)[i];
+        const float4 h = *reinterpret_cast<const float4*>(hi + (int64_t)(Q0 + k) * ncols + c);
+        const float4 l = *reinterpret_cast<const float4*>(lo + (int64_t)(Q0 + k) * ncols + c);
         s[k] += ((double)h.x + (double)l.x) * dd.x + ((double)h.y + (double)l.y) * dd.y +
                 ((double)h.z + (double)l.z) * dd.z + ((double)h.w + (double)l.w) * dd.w;
       }
@@ -72,63 +105,165 @@ __global__ void __launch_bounds__(256) j_gamma_kernel(const float* __restrict__ 
       for (int k = 0; k < JG_Q; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x < nq) gam[Q0 + threadIdx.x] = red[threadIdx.x][0];
+  if (threadIdx.x < nq) gp[(int64_t)blockIdx.y * naux + Q0 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Jvec[c] = sum_Q B[Q][c] gamma_Q, B = hi + lo, four columns per thread, fixed Q order
+// gamma = sum of the sg partial vectors, in order
+__global__ void j_gamma_sum_kernel(const double* __restrict__ gp, int sg, int naux, double* __restrict__ gam) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= naux) return;
+  double s = 0.0;
+  for (int k = 0; k < sg; ++k) s += gp[(int64_t)k * naux + q];
+  gam[q] = s;
+}
+
+// J_c = sum_Q B[Q][c] gamma_Q, B = hi + lo, over the Q of blockIdx.y, fixed Q
+// order: one workgroup per tile, four columns per thread.  One workgroup per
+// tile is 21 of them at nbf = 192 and 276 at 730, far from filling 256 CUs: the
+// Q range is split until there are about 768 (j_plan), and the parts are added
+// in j_unpack_kernel.
+constexpr int JB_Q = 256;  // gammas staged in LDS at a time
 __global__ void __launch_bounds__(256) j_back_kernel(const float* __restrict__ hi,
                                                      const float* __restrict__ lo, int64_t ncols,
-                                                     int naux, const double* __restrict__ gam,
-                                                     double* __restrict__ jv) {
-  const int64_t c4 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c4 >= (ncols >> 2)) return;
+                                                     int naux, const double* __restrict__ gp, int sg, int qchunk,
+                                                     double* __restrict__ jp) {
+  __shared__ double g[JB_Q];
+  const int64_t c4 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int q0 = blockIdx.y * qchunk, q1 = min(q0 + qchunk, naux);
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
   const float4* h4 = reinterpret_cast<const float4*>(hi) + c4;
   const float4* l4 = reinterpret_cast<const float4*>(lo) + c4;
   const int64_t stride = ncols >> 2;
-  for (int Q = 0; Q < naux; ++Q) {
-    const double g = gam[Q];
-    const float4 h = h4[Q * stride], l = l4[Q * stride];
-    a0 = fma((double)h.x + (double)l.x, g, a0);
-    a1 = fma((double)h.y + (double)l.y, g, a1);
-    a2 = fma((double)h.z + (double)l.z, g, a2);
-    a3 = fma((double)h.w + (double)l.w, g, a3);
+  for (int qb = q0; qb < q1; qb += JB_Q) {
+    const int nq = min(JB_Q, q1 - qb);
+    __syncthreads();  // the previous gammas have been read
+    if (threadIdx.x < nq) {
+      double s = 0.0;
+      for (int k = 0; k < sg; ++k) s += gp[(int64_t)k * naux + qb + threadIdx.x];
+      g[threadIdx.x] = s;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < nq; ++i) {
+      const float4 h = h4[(qb + i) * stride], l = l4[(qb + i) * stride];
+      a0 = fma((double)h.x + (double)l.x, g[i], a0);
+      a1 = fma((double)h.y + (double)l.y, g[i], a1);
+      a2 = fma((double)h.z + (double)l.z, g[i], a2);
+      a3 = fma((double)h.w + (double)l.w, g[i], a3);
+    }
   }
-  reinterpret_cast<double4*>(jv)[c4] = double4{a0, a1, a2, a3};
+  reinterpret_cast<double4*>(jp + blockIdx.y * ncols)[c4] = double4{a0, a1, a2, a3};
 }
 
-// tile layout -> dense symmetric matrix
-__global__ void unpack_sym_kernel(const double* __restrict__ v, int nbf, double* __restrict__ M) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)nbf * nbf) return;
-  int r = (int)(idx / nbf), c = (int)(idx % nbf);
-  if (r < c) {
-    const int t = r;
-    r = c;
-    c = t;
+// the sb parts of J in the tile layout, added in order -> dense symmetric
+// matrix, one workgroup per tile; the mirror image goes out through LDS so that
+// both copies are stored as rows
+__global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict__ jp, int64_t ncols, int sb, int nbf,
+                                                       double* __restrict__ M) {
+  __shared__ double tl[TILE][TILE + 1];
+  int I, J;
+  tile_ij(blockIdx.x, I, J);
+  // four consecutive elements of a tile row per thread
+  const int row = threadIdx.x >> 3, col = 4 * (threadIdx.x & 7);
+  const double* __restrict__ src = jp + (int64_t)blockIdx.x * TILE2 + 4 * threadIdx.x;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int k = 0; k < sb; ++k) {
+    const double4 v = *reinterpret_cast<const double4*>(src + k * ncols);
+    s[0] += v.x;
+    s[1] += v.y;
+    s[2] += v.z;
+    s[3] += v.w;
   }
-  M[idx] = v[tile_base(r >> 5, c >> 5) + ((r & 31) << 5) + (c & 31)];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = I * TILE + row, c = J * TILE + col + e;
+    if (r < nbf && c < nbf) M[(int64_t)r * nbf + c] = s[e];
+    tl[row][col + e] = s[e];
+  }
+  if (I == J) return;  // a diagonal tile holds both triangles
+  __syncthreads();
+#pragma unroll
+  for (int e = threadIdx.x; e < TILE2; e += 256) {
+    const int r = J * TILE + (e >> 5), c = I * TILE + (e & 31);
+    if (r < nbf && c < nbf) M[(int64_t)r * nbf + c] = tl[e & 31][e >> 5];
+  }
 }
 
-void j_gamma(const JKArgs& a, const double* D, double* gam, double* dvec, hipStream_t st) {
-  const int nt = ntiles_for(a.nbf);
-  hipLaunchKernelGGL(pack_density_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, D, a.nbf, dvec);
-  // both words of B in every precision: J is bandwidth-bound, and with the hi
-  // word alone its error (amplified by the conditioning of the metric) exceeds
-  // that of a reduced-precision K
-  hipLaunchKernelGGL(j_gamma_kernel, dim3((a.naux + JG_Q - 1) / JG_Q), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux,
-                     dvec, gam);
+// How the two passes over B are cut.  Both stream B.  The gamma pass wants eight
+// workgroups per CU (nbf = 1200, naux = 3600: 900 workgroups 4.25 ms, 2700
+// 4.08 ms); the J pass is best with about three per CU, as more of them work on
+// ranges of B far apart (the same system, J in 1 and 3 parts: 3.7 and 4.07 ms).
+// A part of gamma has at least four tiles (four trips of its loop), a part of J
+// at least 32 Q, and the parts of J stay within 32 MB, so that their traffic is
+// small against B's.  Measured, gamma + J in one part each and cut: nbf = 192,
+// naux = 848: 78 + 320 and 29 + 24 us; 730 / 3106: 1.42 + 1.89 and 1.40 + 1.20 ms.
+struct JPlan {
+  int sg, tchunk, sb, qchunk;
+};
+static JPlan j_plan(int nbf, int naux, int64_t ncols) {
+  JPlan p{};
+  const int tiles = (int)(ncols / TILE2);
+  auto cut = [](int64_t want, int64_t have, int64_t most) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((want + have - 1) / have, most));
+  };
+  p.sg = cut(2048, (naux + JG_Q - 1) / JG_Q, tiles / 4);
+  p.tchunk = (tiles + p.sg - 1) / p.sg;
+  p.sg = (tiles + p.tchunk - 1) / p.tchunk;
+  p.sb = cut(768, tiles, std::min<int64_t>(naux / 32, ((int64_t)4 << 20) / ncols));
+  p.qchunk = (naux + p.sb - 1) / p.sb;
+  p.sb = (naux + p.qchunk - 1) / p.qchunk;
+  return p;
+}
+
+static int64_t even4(int64_t n) { return (n + 3) & ~(int64_t)3; }
+
+// packed density (ncols), the parts of gamma (sg naux) and of J (sb ncols)
+size_t j_work_bytes(int nbf, int naux, int64_t ncols) {
+  const JPlan p = j_plan(nbf, naux, ncols);
+  return sizeof(double) * (size_t)(ncols + even4((int64_t)p.sg * naux) + p.sb * ncols);
+}
+
+// packed density and the parts of gamma
+size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols) {
+  return sizeof(double) * (size_t)(ncols + (int64_t)j_plan(nbf, naux, ncols).sg * naux);
+}
+
+// both words of B in every precision: J is bandwidth-bound, and with the hi
+// word alone its error (amplified by the conditioning of the metric) exceeds
+// that of a reduced-precision K
+static void launch_gamma(const JKArgs& a, const JPlan& p, const double* dvec, double* gp, hipStream_t st) {
+  hipLaunchKernelGGL(j_gamma_kernel, dim3((a.naux + JG_Q - 1) / JG_Q, p.sg), dim3(256), 0, st, a.hi, a.lo, a.ncols,
+                     a.naux, dvec, p.tchunk, gp);
+}
+
+void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStream_t st) {
+  const JPlan p = j_plan(a.nbf, a.naux, a.ncols);
+  double* gp = work + a.ncols;
+  hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, D, a.nbf, work);
+  launch_gamma(a, p, work, gp, st);
+  hipLaunchKernelGGL(j_gamma_sum_kernel, dim3((a.naux + 255) / 256), dim3(256), 0, st, gp, p.sg, a.naux, gam);
+}
+
+static void j_build_packed(const JKArgs& a, double* J, double* work, hipStream_t st) {
+  const JPlan p = j_plan(a.nbf, a.naux, a.ncols);
+  const unsigned tiles = (unsigned)(a.ncols / TILE2);
+  double* gp = work + a.ncols;
+  double* jp = gp + even4((int64_t)p.sg * a.naux);
+  launch_gamma(a, p, work, gp, st);
+  hipLaunchKernelGGL(j_back_kernel, dim3(tiles, p.sb), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, gp, p.sg,
+                     p.qchunk, jp);
+  hipLaunchKernelGGL(j_unpack_kernel, dim3(tiles), dim3(256), 0, st, jp, a.ncols, p.sb, a.nbf, J);
 }
 
 void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st) {
-  double* dvec = work;                       // ncols
-  double* gam = work + a.ncols;              // naux
-  double* jv = gam + ((a.naux + 3) & ~3);    // ncols
-  j_gamma(a, D, gam, dvec, st);
-  const unsigned gb = (unsigned)(((a.ncols >> 2) + 255) / 256);
-  hipLaunchKernelGGL(j_back_kernel, dim3(gb), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, gam, jv);
-  const int64_t n2 = (int64_t)a.nbf * a.nbf;
-  hipLaunchKernelGGL(unpack_sym_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, jv, a.nbf, J);
+  hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, D, a.nbf, work);
+  j_build_packed(a, J, work, st);
+}
+
+void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, hipStream_t st) {
+  hipLaunchKernelGGL(pack_cocc_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, C, a.nbf, nocc, work);
+  j_build_packed(a, J, work, st);
 }
 
 // ---------------------------------------------------------------------------

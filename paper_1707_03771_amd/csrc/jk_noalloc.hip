@@ -1,9 +1,9 @@
 // dfx_jk_noalloc: the Coulomb and exchange builds of dfx_jk for callers that
 // cannot allocate device memory (code under HIP graph capture, tight serving
 // loops, harnesses that forbid allocation).  Same kernels as dfx_jk; their
-// scratch (the density, the packed density and the Coulomb vectors for J; the
-// padded C, the half-transformed chunk X and the SYRK's partial sums for K)
-// lives in one file-scope device array instead of the B handle's workspace.
+// scratch (the packed density and the parts of gamma and of J for J; the padded
+// C, the half-transformed chunk X and the SYRK's partial sums for K) lives in
+// one file-scope device array instead of the B handle's workspace.
 //
 // The array is the same for every call on a GPU and keeps the last call's
 // contents.  Nothing in it needs to start at zero: every kernel here writes
@@ -42,8 +42,6 @@ static void* scratch_ptr() {
   return p;
 }
 
-static size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 }  // namespace dfx
 
 using namespace dfx;
@@ -62,25 +60,14 @@ int dfx_jk_noalloc(const dfx_B* b, const double* dev_C, int nocc, int precision,
     JKArgs a{b->hi.as<float>(), b->lo.as<float>(), b->naux, nbf, b->ncols_t, precision};
     a.ws_cap = NOALLOC_SCRATCH_BYTES;
     // sizes first: nothing is launched unless both builds fit
-    const size_t dbytes = up256(sizeof(double) * (size_t)nbf * nbf);
-    const size_t jbytes = dev_J ? dbytes + sizeof(double) * (2 * (size_t)b->ncols_t + b->naux + 8) : 0;
+    const size_t jbytes = dev_J ? j_work_bytes(nbf, b->naux, b->ncols_t) : 0;
     const size_t kbytes = dev_K ? k_work_bytes(a, nocc) : 0;  // DFX_ENOMEM if no chunk fits
     if (jbytes > NOALLOC_SCRATCH_BYTES || kbytes > NOALLOC_SCRATCH_BYTES)
       throw Error(DFX_ENOMEM, "dfx_jk_noalloc: needs " + std::to_string(std::max(jbytes, kbytes)) +
                                   " bytes of scratch, " + std::to_string(NOALLOC_SCRATCH_BYTES) + " available");
     char* w = static_cast<char*>(scratch_ptr());
-    if (dev_J) {
-      // D = C_occ C_occ^T, then J (Eqs. 3a, 3b) with the Coulomb vectors after it
-      double* D = reinterpret_cast<double*>(w);
-      GemmF64 g{};
-      g.M = nbf; g.N = nbf; g.K = nocc;
-      g.A = dev_C; g.lda = nocc;
-      g.B = dev_C; g.ldb = nocc; g.tb = true;
-      g.C = D; g.ldc = nbf;
-      g.alpha = 1.0; g.beta = 0.0; g.batch = 1;
-      dgemm(g, st);
-      j_build(a, D, dev_J, reinterpret_cast<double*>(w + dbytes), st);
-    }
+    // J (Eqs. 3a, 3b) of D = C_occ C_occ^T
+    if (dev_J) j_build_cocc(a, dev_C, nocc, dev_J, reinterpret_cast<double*>(w), st);
     // K (Eqs. 1a, 2a) reuses the whole array: the stream orders it after J
     if (dev_K) k_build(a, dev_C, nocc, dev_K, w, st);
     DFX_HIP(hipGetLastError());

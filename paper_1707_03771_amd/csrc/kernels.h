@@ -112,9 +112,14 @@ struct JKArgs {
   // even one auxiliary function per chunk does not fit.
   size_t ws_cap = 0;
 };
+// bytes of work of the Coulomb builds below
+size_t j_work_bytes(int nbf, int naux, int64_t ncols);
+// J from a density, or from the occupied block C [nbf][nocc] (D = C C^T)
 void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st);
-// gamma_Q = sum B_Q,mu nu D_mu nu alone (Eq. 3a); dvec: ncols doubles of work
-void j_gamma(const JKArgs& a, const double* D, double* gam, double* dvec, hipStream_t st);
+void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, hipStream_t st);
+// gamma_Q = sum B_Q,mu nu D_mu nu alone (Eq. 3a); work: j_gamma_work_bytes
+size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols);
+void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStream_t st);
 // K from the occupied block C [nbf][nocc] (row-major); work >= k_work_bytes
 size_t k_work_bytes(const JKArgs& a, int nocc);
 // optional GPU timers around the two K phases (events are recorded on st)

@@ -1054,7 +1054,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
         }
       }
       ja.prec = prec;
-      size_t need = std::max(sizeof(double) * (2 * (size_t)B->ncols_t + B->naux + 8), k_work_bytes(ja, nocc));
+      size_t need = std::max(j_work_bytes(n, B->naux, B->ncols_t), k_work_bytes(ja, nocc));
       // the floor is estimated once per stage, at the first iteration after the
       // stage's error fell below 1e-2: by then DIIS converges steadily and the
       // density is close enough to the solution for the estimate to be the floor
@@ -1486,7 +1486,7 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
     bool converged = false;
     for (it = 1; it <= o.max_iter; ++it) {
       // the K plan chunks Q by the occupied count, so size the work for both spins
-      void* w = B->ensure_work(std::max({sizeof(double) * (2 * (size_t)B->ncols_t + B->naux + 8),
+      void* w = B->ensure_work(std::max({j_work_bytes(n, B->naux, B->ncols_t),
                                          k_work_bytes(ja, std::max(1, na)), k_work_bytes(ja, std::max(1, nb))}));
       hipLaunchKernelGGL(add_kernel, dim3(nblk(n2)), dim3(256), 0, st, D[0].as<double>(), D[1].as<double>(),
                          Dt.as<double>(), n2);
