@@ -158,35 +158,40 @@ __global__ void __launch_bounds__(KX_T) kx64_kernel(const float* __restrict__ hi
       }
 }
 
-// ---- phase 2: P_s = X_s X_s^T (lower 128x128 tiles) for k-slices s of X.
+// ---- phase 2: P_s = X_s X_s^T (lower TM x TM tiles) for k-slices s of X.
 // Workgroups are dealt round-robin to the 8 XCDs; every tile of a slice goes to
-// one XCD so that the slice of X is fetched from HBM once per XCD L2.  Eight
-// waves in a 2 x 4 grid of 64 x 32 sub-tiles; on a diagonal tile the two waves
-// whose sub-tiles lie wholly above the diagonal load and synchronise but skip
-// their MFMAs.  Two LDS buffers alternate, so each stage needs one barrier:
-// stage t's buffer was last read in stage t - 2, which every wave finished
-// before the barrier of stage t - 1.
-constexpr int SY_T = 512;
-__global__ void __launch_bounds__(SY_T) syrk64_kernel(const double* __restrict__ X, int64_t ldx, int nbf,
-                                                      int64_t kslice, int64_t kdim, int nslices, int ntl,
-                                                      double* __restrict__ P) {
-  __shared__ double As[2][128][S64 + PA];
-  __shared__ double Bs[2][128][S64 + PA];
+// one XCD so that the slice of X is fetched from HBM once per XCD L2.  Tiles of
+// 128 take eight waves in a 2 x 4 grid of 64 x 32 sub-tiles, tiles of 64 (for
+// the sizes of which 128 leaves much of the border tiles empty, syrk_plan) four
+// waves in a 2 x 2 grid of 32 x 32.  On a diagonal tile the waves whose
+// sub-tiles lie wholly above the diagonal load and synchronise but skip their
+// MFMAs.  Two LDS buffers alternate, so each stage needs one barrier: stage t's
+// buffer was last read in stage t - 2, which every wave finished before the
+// barrier of stage t - 1.  A single slice goes straight to both triangles of K.
+constexpr int sy_threads(int tm) { return 4 * tm; }
+template <int TM>
+__global__ void __launch_bounds__(sy_threads(TM)) syrk64_kernel(const double* __restrict__ X, int64_t ldx, int nbf,
+                                                                int64_t kslice, int64_t kdim, int nslices, int ntl,
+                                                                double* __restrict__ P, int accumulate) {
+  constexpr int WM = TM / 2, WN = 32;  // sub-tile of a wave
+  constexpr int FA = WM / 16, FB = WN / 16;
+  __shared__ double As[2][TM][S64 + PA];
+  __shared__ double Bs[2][TM][S64 + PA];
   const int bid = blockIdx.x;
   const int xcd = bid & 7, local = bid >> 3;
-  const int s = xcd + 8 * (local / ntl);
-  const int tl = local % ntl;
+  const int s = nslices > 1 ? xcd + 8 * (local / ntl) : 0;
+  const int tl = nslices > 1 ? local % ntl : bid;
   if (s >= nslices) return;
   int ti = (int)((sqrt(8.0 * tl + 1.0) - 1.0) * 0.5);
   while ((ti + 1) * (ti + 2) / 2 <= tl) ++ti;
   while (ti * (ti + 1) / 2 > tl) --ti;
   const int tj = tl - ti * (ti + 1) / 2;
-  const int m0 = ti * 128, n0 = tj * 128;
+  const int m0 = ti * TM, n0 = tj * TM;
   const int64_t k0s = (int64_t)s * kslice;
   const int64_t k1s = k0s + kslice < kdim ? k0s + kslice : kdim;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = (w & 1) * 64, wn = (w >> 1) * 32;
-  const bool active = !(ti == tj && wn >= wm + 64);
+  const int wm = (w & 1) * WM, wn = (w >> 1) * WN;
+  const bool active = !(ti == tj && wn >= wm + WM);
   const int li = lane & 15, lk = lane >> 4;
   // loader: row r = tid / 4 of both operands, 4 consecutive k from kq
   const int r = tid >> 2, kq = (tid & 3) * 4;
@@ -219,25 +224,25 @@ __global__ void __launch_bounds__(SY_T) syrk64_kernel(const double* __restrict__
     }
   };
 
-  v4d acc[4][2];
+  v4d acc[FA][FB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < FA; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int b = 0; b < FB; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
 
   auto stage = [&](auto bufc) {
     constexpr int BUF = decltype(bufc)::value;
 #pragma unroll
     for (int kk = 0; kk < S64; kk += 4) {
-      double fa[4], fb[2];
+      double fa[FA], fb[FB];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) fa[a] = As[BUF][wm + a * 16 + li][kk + lk];
+      for (int a = 0; a < FA; ++a) fa[a] = As[BUF][wm + a * 16 + li][kk + lk];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) fb[b] = Bs[BUF][wn + b * 16 + li][kk + lk];
+      for (int b = 0; b < FB; ++b) fb[b] = Bs[BUF][wn + b * 16 + li][kk + lk];
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < FA; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < FB; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
     }
   };
@@ -265,41 +270,121 @@ __global__ void __launch_bounds__(SY_T) syrk64_kernel(const double* __restrict__
   if (!active) return;
   double* __restrict__ Ps = P + (int64_t)s * nbf * nbf;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < FA; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < FB; ++b)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int m = m0 + wm + a * 16 + 4 * q + lk;
         const int n = n0 + wn + b * 16 + li;
-        if (m < nbf && n <= m) Ps[(int64_t)m * nbf + n] = acc[a][b][q];
+        if (m >= nbf || n > m) continue;
+        double v = acc[a][b][q];
+        if (nslices == 1) {
+          if (accumulate) v += Ps[(int64_t)m * nbf + n];
+          Ps[(int64_t)n * nbf + m] = v;
+        }
+        Ps[(int64_t)m * nbf + n] = v;
       }
 }
 
-// K (lower) = sum_s P_s, fixed order
-__global__ void k_reduce64_kernel(const double* __restrict__ P, int ns, int nbf, double* __restrict__ K,
-                                  int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n2 = (int64_t)nbf * nbf;
-  if (idx >= n2) return;
-  const int r = (int)(idx / nbf), c = (int)(idx % nbf);
-  if (c > r) return;
-  double s = accumulate ? K[idx] : 0.0;
-  for (int k = 0; k < ns; ++k) s += P[k * n2 + idx];
-  K[idx] = s;
+// K = sum_s P_s from the lower triangles, both triangles of K written: one
+// workgroup per 16 x 16 tile, its four groups of 256 threads every fourth slice
+// each, the groups added in order.  (One thread per element adding all slices
+// in turn took 255 us at nbf = 192 with 688 slices, a chain of dependent loads.)
+__global__ void __launch_bounds__(1024) k_reduce_kernel(const double* __restrict__ P, int ns, int nbf,
+                                                        double* __restrict__ K, int accumulate) {
+  __shared__ double red[4][16][17];
+  int I = (int)((sqrt(8.0 * blockIdx.x + 1.0) - 1.0) * 0.5);
+  while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
+  while (I * (I + 1) / 2 > (int)blockIdx.x) --I;
+  const int J = blockIdx.x - I * (I + 1) / 2;
+  const int e = threadIdx.x & 255, g = threadIdx.x >> 8;
+  const int row = e >> 4, col = e & 15;
+  const int r = I * 16 + row, c = J * 16 + col;
+  const bool own = r < nbf && c <= r;
+  const int64_t n2 = (int64_t)nbf * nbf, idx = (int64_t)r * nbf + c;
+  double s = 0.0;
+  if (own) {
+#pragma unroll 8
+    for (int k = g; k < ns; k += 4) s += P[k * n2 + idx];
+  }
+  red[g][row][col] = s;
+  __syncthreads();
+  if (g == 0 && own) {
+    s = (accumulate ? K[idx] : 0.0) + ((red[0][row][col] + red[1][row][col]) + (red[2][row][col] + red[3][row][col]));
+    K[idx] = s;
+    red[0][row][col] = s;
+  }
+  __syncthreads();
+  const int mr = J * 16 + row, mc = I * 16 + col;  // the mirror image, stored as rows
+  if (g == 0 && mc < nbf && mr < mc) K[(int64_t)mr * nbf + mc] = red[0][col][row];
+}
+
+void k_reduce(const double* P, int ns, int nbf, double* K, bool accumulate, hipStream_t st) {
+  const int t = (nbf + 15) / 16;
+  hipLaunchKernelGGL(k_reduce_kernel, dim3((unsigned)(t * (t + 1) / 2)), dim3(1024), 0, st, P, ns, nbf, K,
+                     accumulate ? 1 : 0);
+}
+
+// Tile size and number of k-slices of an n x kdim SYRK.  In units of the
+// cycles of one CU: a stage (16 k) of a 128-tile keeps its matrix cores 4096
+// cycles and of a 64-tile 1024, at the efficiencies measured with one, two and
+// more workgroups on the CU; the workgroups are dealt to 32 CUs on each of 8
+// XCDs, so the CU with the most of them sets the time; every slice is written
+// and read again once, and more than one slice takes another launch (5 us).
+// Before, 128-tiles and about 2048 workgroups at any size: nbf = 192, kdim =
+// 33920 (3 tiles, 688 slices): 72 us + 255 us for the sum.
+struct SyrkPlan {
+  int tm, ntl, ns;
+};
+static SyrkPlan syrk_plan(int n, int64_t kdim, int64_t most_slices) {
+  SyrkPlan best{};
+  double tbest = 0.0;
+  for (int tm = 64; tm <= 128; tm += 64) {
+    const int mt = (n + tm - 1) / tm, ntl = mt * (mt + 1) / 2;
+    for (int ns = 1; ns <= 256; ns = ns == 1 ? 8 : ns + 8) {
+      if (ns > 1 && (ns > most_slices || ns > (kdim + S64 - 1) / S64 + 7)) break;
+      const int64_t per_xcd = ns > 1 ? (int64_t)ntl * ns / 8 : (ntl + 7) / 8;
+      const int64_t per_cu = (per_xcd + 31) / 32;
+      const double stages = (double)((kdim + (int64_t)ns * S64 - 1) / ((int64_t)ns * S64));
+      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.75) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.6 : 0.7);
+      double t = (double)per_cu * (stages * (tm == 128 ? 4096.0 : 1024.0) / eff + 3000.0);
+      if (ns > 1) t += 12000.0 + (double)ns * n * n * 8.0 / 5.0e12 * 2.4e9;
+      if (!best.tm || t < tbest) {
+        best = SyrkPlan{tm, ntl, ns};
+        tbest = t;
+      }
+    }
+  }
+  return best;
+}
+
+// K (+)= X X^T over k < kdim; P: ns n^2 doubles (none for one slice)
+static void syrk_run(const SyrkPlan& p, const double* X, int64_t ldx, int n, int64_t kdim, double* P, double* K,
+                     bool accumulate, hipStream_t st) {
+  const int64_t kslice = ((kdim + p.ns - 1) / p.ns + S64 - 1) / S64 * S64;
+  double* out = p.ns > 1 ? P : K;
+  const unsigned grid = (unsigned)(p.ns * p.ntl);
+  if (p.tm == 128)
+    hipLaunchKernelGGL(syrk64_kernel<128>, dim3(grid), dim3(sy_threads(128)), 0, st, X, ldx, n, kslice, kdim, p.ns,
+                       p.ntl, out, accumulate ? 1 : 0);
+  else
+    hipLaunchKernelGGL(syrk64_kernel<64>, dim3(grid), dim3(sy_threads(64)), 0, st, X, ldx, n, kslice, kdim, p.ns,
+                       p.ntl, out, accumulate ? 1 : 0);
+  if (p.ns > 1) k_reduce(P, p.ns, n, K, accumulate, st);
 }
 
 struct F64Plan {
-  int qc, ns, ntl, np, nbfp;
+  int qc, np, nbfp;
+  SyrkPlan sy;
   int64_t ldx;
   size_t x_bytes, p_bytes, c_bytes;
 };
 
 static size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// X chunks of at most 8 GiB, balanced over the chunks; enough SYRK slices (a
-// multiple of 8) to give the chip ~2048 workgroups, partial sums within 2 GiB.
-// Under a work cap: eight slices and X in what the cap leaves.
+// X chunks of at most 8 GiB, balanced over the chunks; SYRK partial sums within
+// 2 GiB.  Under a work cap: at most eight slices and X in what the cap leaves.
 static F64Plan f64_plan(const JKArgs& a, int nocc) {
   F64Plan p{};
   const size_t per_q = (size_t)a.nbf * nocc * sizeof(double);
@@ -323,14 +408,9 @@ static F64Plan f64_plan(const JKArgs& a, int nocc) {
   p.qc = (a.naux + nchunks - 1) / nchunks;
   const int64_t kdim = (int64_t)p.qc * nocc;
   p.ldx = (kdim + 7) / 8 * 8;
-  const int mt = (a.nbf + 127) / 128;
-  p.ntl = mt * (mt + 1) / 2;
-  int64_t ns = (2048 + p.ntl - 1) / p.ntl;
-  const int64_t by_len = (kdim + S64 - 1) / S64;  // at least one stage per slice
-  ns = std::min(ns, std::max<int64_t>(1, std::min(by_mem, by_len)));
-  p.ns = (int)(((ns + 7) / 8) * 8);
+  p.sy = syrk_plan(a.nbf, kdim, std::max<int64_t>(by_mem, 8));
   p.x_bytes = (size_t)a.nbf * p.ldx * sizeof(double);
-  p.p_bytes = (size_t)p.ns * a.nbf * a.nbf * sizeof(double);
+  p.p_bytes = (size_t)p.sy.ns * a.nbf * a.nbf * sizeof(double);
   return p;
 }
 
@@ -376,7 +456,6 @@ void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* wo
   double* X = reinterpret_cast<double*>(w);
   double* P = reinterpret_cast<double*>(w + a256(p.x_bytes));
   double* Cp = reinterpret_cast<double*>(w + a256(p.x_bytes) + a256(p.p_bytes));
-  const int64_t n2 = (int64_t)a.nbf * a.nbf;
   const int64_t ncp = (int64_t)p.nbfp * p.np;
   hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
                      p.np, Cp);
@@ -397,36 +476,22 @@ void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* wo
     }
     if (timer) timer->end_x();
     if (timer) timer->begin_syrk();
-    const int64_t kslice = ((kdim + p.ns - 1) / p.ns + S64 - 1) / S64 * S64;
-    hipLaunchKernelGGL(syrk64_kernel, dim3((unsigned)(p.ns * p.ntl)), dim3(SY_T), 0, st, X, p.ldx, a.nbf, kslice,
-                       kdim, p.ns, p.ntl, P);
-    hipLaunchKernelGGL(k_reduce64_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, P, p.ns, a.nbf, K,
-                       q0 > 0 ? 1 : 0);
+    syrk_run(p.sy, X, p.ldx, a.nbf, kdim, P, K, q0 > 0, st);
     if (timer) timer->end_syrk();
   }
-  sym_from_lower(K, a.nbf, st);
 }
 
 // C = A A^T (n x n, both triangles) for a row-major n x k matrix A with an even
-// row stride lda, on the exchange build's SYRK: lower 128 x 128 tiles, eight
-// k-slices (one per XCD), summed in FP64 in a fixed order, then mirrored.
-// For a symmetric A this is A^2 at half the FLOPs of a general product.
-// work: syrk_f64_work_elems(n) doubles.
+// row stride lda, on the exchange build's SYRK: at most eight k-slices, summed
+// in FP64 in a fixed order.  For a symmetric A this is A^2 at half the FLOPs of
+// a general product.  work: syrk_f64_work_elems(n) doubles.
 size_t syrk_f64_work_elems(int n) { return (size_t)8 * n * n; }
 
 void syrk_f64(const double* A, int64_t lda, int n, int64_t k, double* C, double* work, hipStream_t st) {
   if (n <= 0) return;
   if ((lda & 1) || lda < k || (reinterpret_cast<uintptr_t>(A) & 15))
     throw Error(-1, "syrk_f64: A needs an even row stride >= k and 16-byte alignment");
-  const int mt = (n + 127) / 128;
-  const int ntl = mt * (mt + 1) / 2;
-  const int ns = 8;
-  const int64_t kslice = ((k + ns - 1) / ns + S64 - 1) / S64 * S64;
-  const int64_t n2 = (int64_t)n * n;
-  hipLaunchKernelGGL(syrk64_kernel, dim3((unsigned)(ns * ntl)), dim3(SY_T), 0, st, A, lda, n, kslice, k, ns, ntl,
-                     work);
-  hipLaunchKernelGGL(k_reduce64_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, work, ns, n, C, 0);
-  sym_from_lower(C, n, st);
+  syrk_run(syrk_plan(n, k, 8), A, lda, n, k, work, C, false, st);
 }
 
 }  // namespace dfx

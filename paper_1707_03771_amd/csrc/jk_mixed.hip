@@ -315,24 +315,33 @@ __global__ void __launch_bounds__(SYM_T) syrk_mixed_kernel(const typename Tr::E*
       }
 }
 
-// K (lower) = sum_s P_s in FP64, fixed order; then mirrored by the caller
-__global__ void k_reduce_mixed_kernel(const double* __restrict__ P, int ns, int nbf, double* __restrict__ K,
-                                      int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n2 = (int64_t)nbf * nbf;
-  if (idx >= n2) return;
-  const int r = (int)(idx / nbf), c = (int)(idx % nbf);
-  if (c > r) return;
-  double s = accumulate ? K[idx] : 0.0;
-  for (int k = 0; k < ns; ++k) s += P[k * n2 + idx];
-  K[idx] = s;
-}
-
 struct MixedPlan {
   int ncb, npad, nbfp, qc, ns, ntl;
   int64_t kslice, kdim;
   size_t ct_bytes, x_bytes, p_bytes;
 };
+
+// Number of k-slices of the SYRK (a multiple of 8, one XCD each).  In cycles of
+// one CU: a stage (KT products) of a 128-tile at the rate measured with one and
+// with more workgroups on the CU, times the workgroups of the busiest CU, plus
+// the partial sums written and read once.  Before, about 2048 workgroups at any
+// size: three tiles and 688 slices at nbf = 192, whose sum cost more than the
+// product.
+static int syrk_slices(int n, int64_t kdim, int ntl, size_t esize) {
+  int best = 8;
+  double tbest = 0.0;
+  for (int ns = 8; ns <= 256 && (ns == 8 || (int64_t)(ns - 8) * KT < kdim); ns += 8) {
+    const int64_t per_cu = ((int64_t)ntl * ns / 8 + 31) / 32;
+    const double stages = (double)((kdim + (int64_t)ns * KT - 1) / ((int64_t)ns * KT));
+    const double cyc = esize == 4 ? (per_cu == 1 ? 8000.0 : 6500.0) : (per_cu == 1 ? 2500.0 : 1600.0);
+    const double t = (double)per_cu * (stages * cyc + 3000.0) + (double)ns * n * n * 8.0 / 5.0e12 * 2.4e9;
+    if (ns == 8 || t < tbest) {
+      best = ns;
+      tbest = t;
+    }
+  }
+  return best;
+}
 
 static MixedPlan mixed_plan(const JKArgs& a, int nocc, size_t esize) {
   MixedPlan p{};
@@ -356,13 +365,7 @@ static MixedPlan mixed_plan(const JKArgs& a, int nocc, size_t esize) {
   p.kdim = (int64_t)p.qc * nocc;
   const int mt = (a.nbf + 127) / 128;
   p.ntl = mt * (mt + 1) / 2;
-  // enough slices to fill the chip several times over, a multiple of 8 (the FP32
-  // sums are already flushed to FP64 every KT products inside the kernel)
-  int ns = (2048 + p.ntl - 1) / p.ntl;
-  ns = ((ns + 7) / 8) * 8;
-  const int64_t maxs = (p.kdim + KT - 1) / KT;
-  if (ns > maxs) ns = (int)(((maxs + 7) / 8) * 8);
-  if (ns < 8 || a.ws_cap) ns = 8;
+  const int ns = a.ws_cap ? 8 : syrk_slices(a.nbf, p.kdim, p.ntl, esize);
   p.ns = ns;
   p.kslice = ((p.kdim + ns - 1) / ns + KT - 1) / KT * KT;
   p.ct_bytes = (size_t)p.npad * p.nbfp * esize;
@@ -390,7 +393,6 @@ static void k_build_tr(const JKArgs& a, const double* C, int nocc, double* K, vo
   const int64_t ctn = (int64_t)p.npad * p.nbfp;
   hipLaunchKernelGGL(ct_kernel<E>, dim3((unsigned)((ctn + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.npad,
                      p.nbfp, Ct);
-  const int64_t n2 = (int64_t)a.nbf * a.nbf;
   for (int q0 = 0; q0 < a.naux; q0 += p.qc) {
     const int nq = std::min(p.qc, a.naux - q0);
     const int64_t kdim = (int64_t)nq * nocc;
@@ -413,11 +415,9 @@ static void k_build_tr(const JKArgs& a, const double* C, int nocc, double* K, vo
     const int nblocks = ((ns + 7) / 8) * 8 * p.ntl;
     hipLaunchKernelGGL(syrk_mixed_kernel<Tr>, dim3(nblocks), dim3(SYM_T), 0, st, X, ldx, a.nbf, kslice, kdim, ns,
                        p.ntl, P);
-    hipLaunchKernelGGL(k_reduce_mixed_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, P, ns, a.nbf,
-                       K, q0 > 0 ? 1 : 0);
+    k_reduce(P, ns, a.nbf, K, q0 > 0, st);
     if (timer) timer->end_syrk();
   }
-  sym_from_lower(K, a.nbf, st);
 }
 
 void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,

@@ -144,6 +144,8 @@ double mp2_energy(const JKArgs& a, const double* C, int nmo, const double* eps, 
                   hipStream_t st);
 void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
                  KTimer* timer);
+// K (+)= sum of the ns slices P (their lower triangles), both triangles written (jk_f64.hip)
+void k_reduce(const double* P, int ns, int nbf, double* K, bool accumulate, hipStream_t st);
 // C = A A^T (both triangles) for a row-major n x k A, even row stride lda,
 // 16-byte aligned (jk_f64.hip); work: syrk_f64_work_elems(n) doubles
 size_t syrk_f64_work_elems(int n);
@@ -162,6 +164,5 @@ void export_rows(const float* hi, const float* lo, const double* raw, int64_t nc
 
 // ---- small dense helpers (linalg.hip) ----------------------------------------
 void fill_f64(double* p, size_t n, double v, hipStream_t st);
-void sym_from_lower(double* A, int n, hipStream_t st);
 
 }  // namespace dfx

@@ -651,17 +651,6 @@ void fill_f64(double* p, size_t n, double v, hipStream_t st) {
   hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n, v);
 }
 
-__global__ void sym_lower_kernel(double* A, int n) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)n * n) return;
-  const int r = (int)(idx / n), c = (int)(idx % n);
-  if (c > r) A[idx] = A[(int64_t)c * n + r];
-}
-void sym_from_lower(double* A, int n, hipStream_t st) {
-  const int64_t t = (int64_t)n * n;
-  hipLaunchKernelGGL(sym_lower_kernel, dim3((unsigned)((t + 255) / 256)), dim3(256), 0, st, A, n);
-}
-
 __global__ void zero_upper_kernel(double* A, int n) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)n * n) return;
