@@ -276,10 +276,12 @@ dfx::Eri3Need dfx::eri3_need(const HostShells& b, const HostShells& a, int flags
   const int64_t m2 = pad256(8 * naux * naux), raw = pad256(8 * naux * ncb);
   const int64_t npall = nsh * (nsh + 1) / 2;
   z.bytes_B = 2 * pad256(4 * naux * nct);
+  const int64_t nt = ntiles_for((int)nbf);
+  const int64_t tile_lists = pad256(8 * nt * ((nt + 63) / 64)) + 2 * pad256(4 * nct / TILE2);
   z.bytes_raw = raw;
   z.bytes_metric = 2 * m2;
   z.bottom = shells_bytes(b) + shells_bytes(a) + z.bytes_B + m2 + ((flags & DFX_KEEP_METRIC) ? m2 : 0) +
-             ((flags & DFX_KEEP_RAW) ? raw : 0);
+             ((flags & DFX_KEEP_RAW) ? raw : 0) + tile_lists;
   const int64_t lists = 16 * npall + 25 * npall + 20 * nauxsh + 256 * 256;
   // raw itself, or its working copy when raw is kept; L when not kept; the
   // Cholesky work (also the solve's packed diagonal blocks) and the tile map
@@ -287,7 +289,9 @@ dfx::Eri3Need dfx::eri3_need(const HostShells& b, const HostShells& a, int flags
             pad256(8 * (int64_t)cholesky_work_elems((int)naux)) + 256 + std::max(2 * pad256(8 * ncb), pad256(8 * nct));
   z.jk = jk_need((int)nbf, (int)naux, nct);
   const int64_t top = std::max(z.setup, z.jk + pad256(8 * ncb));
-  z.total = z.bottom + top + top / 64 + ((int64_t)16 << 20);
+  // 16 MB for fragmentation, which the tile lists come out of
+  z.total = z.bottom + top + top / 64 + ((int64_t)16 << 20) - tile_lists;
+  z.tile_lists = tile_lists;
   return z;
 }
 
@@ -302,7 +306,7 @@ int64_t dfx::scf_need(const HostShells& b, const HostShells& a, int natom, int d
   const int64_t guess = (int64_t)natom * natom * 4 * 9842 + ((int64_t)1 << 20);
   const int64_t pre = 4 * n2 + 3 * 256;  // split-K partials and small buffers made before B
   const int64_t top = std::max(e.setup + pre, mats + guess + e.jk);
-  return e.bottom + top + top / 64 + ((int64_t)16 << 20);
+  return e.bottom + top + top / 64 + ((int64_t)16 << 20) - e.tile_lists;
 }
 
 void* dfx_B::ensure_work(size_t bytes) {
@@ -340,6 +344,12 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     B->lo.alloc(sizeof(float) * (size_t)naux * B->ncols_t);
     B->J2.alloc(sizeof(double) * naux * (size_t)naux);
     if (flags & DFX_KEEP_METRIC) B->L.alloc(sizeof(double) * naux * (size_t)naux);
+    {
+      const size_t nt = ntiles_for(nbf);
+      B->tmask.alloc(sizeof(unsigned long long) * nt * ((nt + 63) / 64));
+      B->tiles.alloc(sizeof(int) * (size_t)(B->ncols_t / TILE2));
+      B->tpos.alloc(sizeof(int) * (size_t)(B->ncols_t / TILE2));
+    }
     GpuTimer tm(st);
 
     // -- metric J_PQ = (P|Q)
@@ -614,6 +624,28 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
           }
       }
     }
+    // the tiles that hold a kept pair, for the passes over B (JKArgs)
+    {
+      const int nt = ntiles_for(nbf);
+      B->mw = (nt + 63) / 64;
+      std::vector<unsigned long long> mask((size_t)nt * B->mw, 0);
+      std::vector<int> tiles, tpos((size_t)(B->ncols_t / TILE2), -1);
+      for (int I = 0; I < nt; ++I)
+        for (int J = 0; J <= I; ++J) {
+          const int64_t t0 = tile_base(I, J);
+          if (std::all_of(src.begin() + t0, src.begin() + t0 + TILE2, [](int64_t c) { return c < 0; })) continue;
+          tpos[t0 / TILE2] = (int)tiles.size();
+          tiles.push_back((int)(t0 / TILE2));
+          mask[(size_t)I * B->mw + J / 64] |= 1ull << (J % 64);
+          mask[(size_t)J * B->mw + I / 64] |= 1ull << (I % 64);
+        }
+      B->nt_kept = (int)tiles.size();
+      DFX_HIP(hipMemcpyAsync(B->tmask.p, mask.data(), sizeof(mask[0]) * mask.size(), hipMemcpyHostToDevice, st));
+      DFX_HIP(hipMemcpyAsync(B->tpos.p, tpos.data(), sizeof(int) * tpos.size(), hipMemcpyHostToDevice, st));
+      if (!tiles.empty())
+        DFX_HIP(hipMemcpyAsync(B->tiles.p, tiles.data(), sizeof(int) * tiles.size(), hipMemcpyHostToDevice, st));
+      DFX_HIP(hipStreamSynchronize(st));  // the host lists go out of scope
+    }
     DevMem src_d = upload(src, st);
     // B = L^-1 raw by blocked forward substitution, in place (on a copy when the
     // raw integrals are kept), then split into the two FP32 words.  The timed
@@ -842,7 +874,7 @@ int dfx_jk(const dfx_B* bc, const double* dev_in, int kind, int nocc, int precis
     if (kind == DFX_COCC && (nocc <= 0 || nocc > b->nbf)) throw Error(DFX_EINVAL, "dfx_jk: bad nocc");
     hipStream_t st = (hipStream_t)stream;
     ArenaScope scope(b->arena.get());
-    JKArgs a{b->hi.as<float>(), b->lo.as<float>(), b->naux, b->nbf, b->ncols_t, precision};
+    const JKArgs a = b->jk_args(precision);
     const int nbf = b->nbf;
     size_t need = 0;
     if (dev_J) need = std::max(need, j_work_bytes(nbf, b->naux, b->ncols_t));
@@ -863,7 +895,7 @@ int dfx_mp2(const dfx_B* bc, const double* dev_C, int nmo, const double* eps, in
     dfx_B* b = const_cast<dfx_B*>(bc);
     if (nmo <= 0 || nmo > b->nbf || nocc <= 0 || nocc >= nmo || nfrozen < 0 || nfrozen >= nocc)
       throw Error(DFX_EINVAL, "dfx_mp2: bad orbital counts");
-    JKArgs a{b->hi.as<float>(), b->lo.as<float>(), b->naux, b->nbf, b->ncols_t, DFX_FP64};
+    const JKArgs a = b->jk_args(DFX_FP64);
     *E2 = mp2_energy(a, dev_C, nmo, eps, nocc, nfrozen, (hipStream_t)stream);
   });
 }

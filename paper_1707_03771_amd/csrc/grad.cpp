@@ -106,7 +106,7 @@ int64_t grad_need(const HostShells& b, const HostShells& a, int natom, int nocc)
   // one-electron: Cartesian weights (two arrays) and partial sums
   w += 2 * p(8 * npall * 100) + p(8 * 6 * npall) + p(8 * (npall / 64 + 16) * natom * 3) + 64 * 256;
   const int64_t top = std::max(e.setup, w);
-  return e.bottom + top + top / 64 + ((int64_t)32 << 20);
+  return e.bottom + top + top / 64 + ((int64_t)32 << 20) - e.tile_lists;
 }
 
 }  // namespace dfx
@@ -185,7 +185,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
     gemm(n, n, nocc, Cd.as<double>(), nocc, false, Cd.as<double>(), nocc, true, D.as<double>(), n, 1.0);
     scale_cols(Cd.as<double>(), ed.as<double>(), n, nocc, Ce.as<double>(), st);
     gemm(n, n, nocc, Ce.as<double>(), nocc, false, Cd.as<double>(), nocc, true, Wm.as<double>(), n, 1.0);
-    const JKArgs ja{B->hi.as<float>(), B->lo.as<float>(), naux, n, B->ncols_t, PREC_FP64};
+    const JKArgs ja = B->jk_args(PREC_FP64);
     DevMem gam(8 * (size_t)naux), dvec(j_gamma_work_bytes(n, naux, B->ncols_t));
     j_gamma(ja, D.as<double>(), gam.as<double>(), dvec.as<double>(), st);
     dvec.release();

@@ -178,6 +178,9 @@ struct dfx_B {
   std::vector<double> Qab, QC;      // host copies
   dfx::DevMem hi, lo, raw, J2, L;   // device tensors
   dfx::DevMem work;                 // grow-only scratch for dfx_jk
+  // the tiles of B that hold a kept pair (JKArgs)
+  dfx::DevMem tmask, tiles, tpos;
+  int mw = 0, nt_kept = 0;
   dfx::DevMem toff;                 // packed column -> tile offset (built on demand)
   // raw's column layout: class cls = 4 max(la, lb) + min(la, lb) holds its pairs
   // (first shell cls_f, the larger l; second cls_s) from column cls_base[cls],
@@ -188,6 +191,10 @@ struct dfx_B {
   dfx::DevMem rawcol_d;             // (built on demand, for the raw export)
   dfx_B_info info{};
   void* ensure_work(size_t bytes);
+  dfx::JKArgs jk_args(int prec) const {
+    return dfx::JKArgs{hi.as<float>(), lo.as<float>(), naux, nbf, ncols_t, prec,
+                       tmask.as<unsigned long long>(), mw, tiles.as<int>(), tpos.as<int>(), nt_kept};
+  }
 };
 
 namespace dfx {
@@ -197,6 +204,7 @@ struct Eri3Need {
   int64_t bottom;  // outlives the call: shells, B (hi, lo), J_PQ slot, kept metric / raw
   int64_t setup;   // released before the call returns
   int64_t jk;      // largest dfx_jk work on the result
+  int64_t tile_lists;  // of bottom: the lists of kept tiles
   int64_t total;   // bottom + max(setup, jk + export map) + fragmentation slack
 };
 Eri3Need eri3_need(const HostShells& b, const HostShells& a, int flags);

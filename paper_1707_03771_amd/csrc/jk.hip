@@ -24,9 +24,10 @@ __device__ __forceinline__ void tile_ij(int t, int& I, int& J) {
   J = t - i * (i + 1) / 2;
 }
 
-// weighted density in the tile layout: off-diagonal tiles count twice
-__global__ void pack_density_kernel(const double* __restrict__ D, int nbf, double* __restrict__ d) {
-  const int t = blockIdx.x;
+// weighted density in the tile layout (the kept tiles): off-diagonal tiles count twice
+__global__ void pack_density_kernel(const double* __restrict__ D, int nbf, const int* __restrict__ tiles,
+                                    double* __restrict__ d) {
+  const int t = tiles[blockIdx.x];
   int I, J;
   tile_ij(t, I, J);
   const double w = (I == J) ? 1.0 : 2.0;
@@ -42,8 +43,8 @@ __global__ void pack_density_kernel(const double* __restrict__ D, int nbf, doubl
 // 128 x 128 at nbf = 192 to 730: 21 to 30 us on a mostly idle chip) and the
 // packing pass after it; 4 us at nbf = 192, nocc = 40.
 __global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict__ C, int nbf, int nocc,
-                                                        double* __restrict__ d) {
-  const int t = blockIdx.x;
+                                                        const int* __restrict__ tiles, double* __restrict__ d) {
+  const int t = tiles[blockIdx.x];
   int I, J;
   tile_ij(t, I, J);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -68,22 +69,23 @@ __global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict
 // gamma_Q = sum_c B[Q][c] d[c], B = hi + lo, FP64 accumulation.  A workgroup
 // takes JG_Q consecutive Q, so each element of d is fetched once per JG_Q rows
 // of B (d is as long as a row of B: read once per Q it doubled the kernel's
-// traffic), and blockIdx.y'th of the column tiles: gp[y][Q] is its part of the
+// traffic), and the blockIdx.y'th part of the kept tiles: gp[y][Q] is its part of the
 // sum, which the readers of gamma add in order (j_plan: enough workgroups to
 // fill the chip where naux / JG_Q alone does not).
 constexpr int JG_Q = 4;
 __global__ void __launch_bounds__(256) j_gamma_kernel(const float* __restrict__ hi,
                                                       const float* __restrict__ lo, int64_t ncols, int naux,
-                                                      const double* __restrict__ d, int tchunk,
+                                                      const double* __restrict__ d,
+                                                      const int* __restrict__ tiles, int nt_kept, int tchunk,
                                                       double* __restrict__ gp) {
   const int Q0 = blockIdx.x * JG_Q;
   const int nq = min(JG_Q, naux - Q0);
-  const int64_t c0 = (int64_t)blockIdx.y * tchunk * TILE2;
-  const int64_t c1 = min(c0 + (int64_t)tchunk * TILE2, ncols);
+  const int t0 = blockIdx.y * tchunk, t1 = min(t0 + tchunk, nt_kept);
   double s[JG_Q];
 #pragma unroll
   for (int k = 0; k < JG_Q; ++k) s[k] = 0.0;
-  for (int64_t c = c0 + 4 * threadIdx.x; c < c1; c += TILE2) {
+  for (int t = t0; t < t1; ++t) {
+    const int64_t c = (int64_t)tiles[t] * TILE2 + 4 * threadIdx.x;
     const double4 dd = *reinterpret_cast<const double4*>(d + c);
 #pragma unroll
     for (int k = 0; k < JG_Q; ++k) {
@@ -118,17 +120,18 @@ __global__ void j_gamma_sum_kernel(const double* __restrict__ gp, int sg, int na
 }
 
 // J_c = sum_Q B[Q][c] gamma_Q, B = hi + lo, over the Q of blockIdx.y, fixed Q
-// order: one workgroup per tile, four columns per thread.  One workgroup per
+// order: one workgroup per kept tile, four columns per thread.  One workgroup per
 // tile is 21 of them at nbf = 192 and 276 at 730, far from filling 256 CUs: the
 // Q range is split until there are about 768 (j_plan), and the parts are added
 // in j_unpack_kernel.
 constexpr int JB_Q = 256;  // gammas staged in LDS at a time
 __global__ void __launch_bounds__(256) j_back_kernel(const float* __restrict__ hi,
                                                      const float* __restrict__ lo, int64_t ncols,
-                                                     int naux, const double* __restrict__ gp, int sg, int qchunk,
+                                                     int naux, const int* __restrict__ tiles,
+                                                     const double* __restrict__ gp, int sg, int qchunk,
                                                      double* __restrict__ jp) {
   __shared__ double g[JB_Q];
-  const int64_t c4 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t c4 = (int64_t)tiles[blockIdx.x] * 256 + threadIdx.x;
   const int q0 = blockIdx.y * qchunk, q1 = min(q0 + qchunk, naux);
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
   const float4* h4 = reinterpret_cast<const float4*>(hi) + c4;
@@ -152,24 +155,28 @@ __global__ void __launch_bounds__(256) j_back_kernel(const float* __restrict__ h
       a3 = fma((double)h.w + (double)l.w, g[i], a3);
     }
   }
-  reinterpret_cast<double4*>(jp + blockIdx.y * ncols)[c4] = double4{a0, a1, a2, a3};
+  reinterpret_cast<double4*>(jp)[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x] =
+      double4{a0, a1, a2, a3};
 }
 
-// the sb parts of J in the tile layout, added in order -> dense symmetric
-// matrix, one workgroup per tile; the mirror image goes out through LDS so that
+// the sb parts of the kept tiles of J, added in order -> dense symmetric matrix
+// (zero where no tile was kept), one workgroup per tile; the mirror image goes out through LDS so that
 // both copies are stored as rows
-__global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict__ jp, int64_t ncols, int sb, int nbf,
+__global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict__ jp, const int* __restrict__ tpos,
+                                                       int nt_kept, int sb, int nbf,
                                                        double* __restrict__ M) {
   __shared__ double tl[TILE][TILE + 1];
   int I, J;
   tile_ij(blockIdx.x, I, J);
   // four consecutive elements of a tile row per thread
   const int row = threadIdx.x >> 3, col = 4 * (threadIdx.x & 7);
-  const double* __restrict__ src = jp + (int64_t)blockIdx.x * TILE2 + 4 * threadIdx.x;
+  const int pos = tpos[blockIdx.x];
+  const double* __restrict__ src = jp + (int64_t)(pos < 0 ? 0 : pos) * TILE2 + 4 * threadIdx.x;
+  const int parts = pos < 0 ? 0 : sb;
   double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 8
-  for (int k = 0; k < sb; ++k) {
-    const double4 v = *reinterpret_cast<const double4*>(src + k * ncols);
+  for (int k = 0; k < parts; ++k) {
+    const double4 v = *reinterpret_cast<const double4*>(src + (int64_t)k * nt_kept * TILE2);
     s[0] += v.x;
     s[1] += v.y;
     s[2] += v.z;
@@ -201,16 +208,18 @@ __global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict_
 struct JPlan {
   int sg, tchunk, sb, qchunk;
 };
-static JPlan j_plan(int nbf, int naux, int64_t ncols) {
+static JPlan j_plan(int naux, int64_t ncols, int kept) {
   JPlan p{};
-  const int tiles = (int)(ncols / TILE2);
+  const int all = (int)(ncols / TILE2), tiles = std::max(1, kept);
   auto cut = [](int64_t want, int64_t have, int64_t most) {
     return (int)std::max<int64_t>(1, std::min<int64_t>((want + have - 1) / have, most));
   };
   p.sg = cut(2048, (naux + JG_Q - 1) / JG_Q, tiles / 4);
   p.tchunk = (tiles + p.sg - 1) / p.sg;
   p.sg = (tiles + p.tchunk - 1) / p.tchunk;
-  p.sb = cut(768, tiles, std::min<int64_t>(naux / 32, ((int64_t)4 << 20) / ncols));
+  // no more memory than with every tile kept
+  const int64_t most = std::min<int64_t>(naux / 32, ((int64_t)4 << 20) / ncols);
+  p.sb = std::min<int>(cut(768, tiles, most), (int)((int64_t)cut(768, all, most) * all / tiles));
   p.qchunk = (naux + p.sb - 1) / p.sb;
   p.sb = (naux + p.qchunk - 1) / p.qchunk;
   return p;
@@ -220,13 +229,13 @@ static int64_t even4(int64_t n) { return (n + 3) & ~(int64_t)3; }
 
 // packed density (ncols), the parts of gamma (sg naux) and of J (sb ncols)
 size_t j_work_bytes(int nbf, int naux, int64_t ncols) {
-  const JPlan p = j_plan(nbf, naux, ncols);
+  const JPlan p = j_plan(naux, ncols, (int)(ncols / TILE2));
   return sizeof(double) * (size_t)(ncols + even4((int64_t)p.sg * naux) + p.sb * ncols);
 }
 
 // packed density and the parts of gamma
 size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols) {
-  return sizeof(double) * (size_t)(ncols + (int64_t)j_plan(nbf, naux, ncols).sg * naux);
+  return sizeof(double) * (size_t)(ncols + (int64_t)j_plan(naux, ncols, (int)(ncols / TILE2)).sg * naux);
 }
 
 // both words of B in every precision: J is bandwidth-bound, and with the hi
@@ -234,35 +243,39 @@ size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols) {
 // that of a reduced-precision K
 static void launch_gamma(const JKArgs& a, const JPlan& p, const double* dvec, double* gp, hipStream_t st) {
   hipLaunchKernelGGL(j_gamma_kernel, dim3((a.naux + JG_Q - 1) / JG_Q, p.sg), dim3(256), 0, st, a.hi, a.lo, a.ncols,
-                     a.naux, dvec, p.tchunk, gp);
+                     a.naux, dvec, a.tiles, a.nt_kept, p.tchunk, gp);
 }
 
 void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStream_t st) {
-  const JPlan p = j_plan(a.nbf, a.naux, a.ncols);
+  const JPlan p = j_plan(a.naux, a.ncols, a.nt_kept);
   double* gp = work + a.ncols;
-  hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, D, a.nbf, work);
+  if (a.nt_kept)
+    hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
   launch_gamma(a, p, work, gp, st);
   hipLaunchKernelGGL(j_gamma_sum_kernel, dim3((a.naux + 255) / 256), dim3(256), 0, st, gp, p.sg, a.naux, gam);
 }
 
 static void j_build_packed(const JKArgs& a, double* J, double* work, hipStream_t st) {
-  const JPlan p = j_plan(a.nbf, a.naux, a.ncols);
+  const JPlan p = j_plan(a.naux, a.ncols, a.nt_kept);
   const unsigned tiles = (unsigned)(a.ncols / TILE2);
   double* gp = work + a.ncols;
   double* jp = gp + even4((int64_t)p.sg * a.naux);
   launch_gamma(a, p, work, gp, st);
-  hipLaunchKernelGGL(j_back_kernel, dim3(tiles, p.sb), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, gp, p.sg,
-                     p.qchunk, jp);
-  hipLaunchKernelGGL(j_unpack_kernel, dim3(tiles), dim3(256), 0, st, jp, a.ncols, p.sb, a.nbf, J);
+  if (a.nt_kept)
+    hipLaunchKernelGGL(j_back_kernel, dim3(a.nt_kept, p.sb), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, a.tiles,
+                       gp, p.sg, p.qchunk, jp);
+  hipLaunchKernelGGL(j_unpack_kernel, dim3(tiles), dim3(256), 0, st, jp, a.tpos, a.nt_kept, p.sb, a.nbf, J);
 }
 
 void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st) {
-  hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, D, a.nbf, work);
+  if (a.nt_kept)
+    hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
   j_build_packed(a, J, work, st);
 }
 
 void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, hipStream_t st) {
-  hipLaunchKernelGGL(pack_cocc_kernel, dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, C, a.nbf, nocc, work);
+  if (a.nt_kept)
+    hipLaunchKernelGGL(pack_cocc_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, C, a.nbf, nocc, a.tiles, work);
   j_build_packed(a, J, work, st);
 }
 

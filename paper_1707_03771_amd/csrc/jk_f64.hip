@@ -158,6 +158,194 @@ __global__ void __launch_bounds__(KX_T) kx64_kernel(const float* __restrict__ hi
       }
 }
 
+// ---- phase 1 with up to 160 occupied columns: NB blocks of 16 columns, so that
+// no more than 15 columns are padding (a multiple of 64 wasted 49% at nocc = 65
+// and 38% at 40).  Four waves own RW x 16 rows each and all NB column blocks;
+// C is read in place.  Only the tiles of B that hold a kept pair are visited: a
+// workgroup walks the union of its tile rows' masks, and a tile row without the
+// tile reads nothing.  In long molecules half of the tiles hold none (zigzag
+// C30H62: 56% of the columns screened).
+constexpr int KS_T = 256;
+template <int NB, int RW>
+__global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ hi, const float* __restrict__ lo,
+                                                     int64_t ncols, int nbf, int q0,
+                                                     const unsigned long long* __restrict__ mask, int mw,
+                                                     const double* __restrict__ C, int nocc,
+                                                     double* __restrict__ X, int64_t ldx) {
+  constexpr int NP = 16 * NB;
+  constexpr int MR = 64 * RW;                 // rows of the workgroup
+  constexpr int TR = MR / 32;                 // its tile rows
+  constexpr int TPR = KS_T / TR;              // threads per tile row
+  constexpr int EP = 32 * S64 / TPR;          // consecutive A elements per thread per stage: 4 or 8
+  constexpr int DK = S64 / EP;                // threads per row of a direct stage
+  constexpr int TM = 32 / EP;                 // threads per row of a mirrored stage
+  typedef float v4fl __attribute__((ext_vector_type(4)));
+  __shared__ double As[2][MR][S64 + PA];
+  __shared__ double Bs[2][S64][NP + PB];
+  const int Q = q0 + blockIdx.y;
+  const int m0 = blockIdx.x * MR;
+  const int I0 = m0 >> 5;
+  const int nt = ntiles_for(nbf);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int wr = w * 16 * RW;
+  const float* __restrict__ rh = hi + (int64_t)Q * ncols;
+  const float* __restrict__ rl = lo + (int64_t)Q * ncols;
+  const int grp = __builtin_amdgcn_readfirstlane(tid / TPR), t = tid % TPR;  // a wave is in one tile row
+  const int I = I0 + grp;
+  const unsigned long long* __restrict__ mrow = mask + (int64_t)(I < nt ? I : 0) * mw;
+
+  // the next tile column J of the union of the workgroup's tile rows (uniform),
+  // or nt
+  int word = -1, J = nt;
+  unsigned long long bits = 0;
+  auto advance = [&]() {
+    while (bits == 0) {
+      if (++word >= mw) {
+        J = nt;
+        return;
+      }
+#pragma unroll
+      for (int r = 0; r < TR; ++r)
+        if (I0 + r < nt) bits |= mask[(int64_t)(I0 + r) * mw + word];
+    }
+    J = word * 64 + __builtin_ctzll(bits);
+    bits &= bits - 1;
+  };
+
+  constexpr int CK = KS_T / S64;              // threads per k row of the C stage: 16
+  const int ck = tid / CK, ci = tid % CK;     // k row, first column
+  // loads without branches, so that all of a stage are in flight at once: an
+  // operand that is zero reads a valid place (tile 0, the last row or column of
+  // C) and is set to zero on its way into LDS
+  v4fl ah[EP / 4], al[EP / 4];
+  double cr[NB];
+  bool direct = false, kept = false, inrow = false;
+  auto load = [&](int Jt, int h) {
+    direct = I >= Jt;
+    kept = I < nt && (mrow[Jt >> 6] >> (Jt & 63) & 1);
+    // direct tile (I, J): row mu = t / DK, nu = 16 h + EP (t % DK) ..; else tile
+    // (J, I): row nu = 16 h + t / TM, mu = EP (t % TM) ..
+    const int64_t base = kept ? (direct ? tile_base(I, Jt) : tile_base(Jt, I)) : 0;
+    const int off = direct ? (t / DK) * 32 + 16 * h + (t % DK) * EP : (16 * h + t / TM) * 32 + (t % TM) * EP;
+#pragma unroll
+    for (int v = 0; v < EP / 4; ++v) {
+      ah[v] = reinterpret_cast<const v4fl*>(rh + base + off)[v];
+      al[v] = reinterpret_cast<const v4fl*>(rl + base + off)[v];
+    }
+    const int nu = 32 * Jt + 16 * h + ck;
+    inrow = nu < nbf;
+    const double* __restrict__ cp = C + (int64_t)min(nu, nbf - 1) * nocc;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) cr[b] = cp[min(16 * b + ci, nocc - 1)];
+  };
+  auto store = [&](int b) {
+    double v[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) v[e] = kept ? (double)ah[e >> 2][e & 3] + (double)al[e >> 2][e & 3] : 0.0;
+    if (direct) {
+      const int r = grp * 32 + t / DK, k0 = (t % DK) * EP;
+#pragma unroll
+      for (int e = 0; e < EP; ++e) As[b][r][k0 + e] = v[e];
+    } else {
+      const int k = t / TM, r0 = grp * 32 + (t % TM) * EP;
+#pragma unroll
+      for (int e = 0; e < EP; ++e) As[b][r0 + e][k] = v[e];
+    }
+#pragma unroll
+    for (int c = 0; c < NB; ++c) Bs[b][ck][16 * c + ci] = inrow && 16 * c + ci < nocc ? cr[c] : 0.0;
+  };
+
+  v4d acc[RW][NB];
+#pragma unroll
+  for (int a = 0; a < RW; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+  auto mma = [&](auto bufc) {
+    constexpr int BUF = decltype(bufc)::value;
+#pragma unroll
+    for (int kk = 0; kk < S64; kk += 4) {
+      double fa[RW];
+#pragma unroll
+      for (int a = 0; a < RW; ++a) fa[a] = As[BUF][wr + a * 16 + li][kk + lk];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const double fb = Bs[BUF][kk + lk][b * 16 + li];
+#pragma unroll
+        for (int a = 0; a < RW; ++a) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb, acc[a][b], 0, 0, 0);
+      }
+    }
+  };
+  // the two halves of a tile column alternate over the two LDS buffers, one
+  // barrier per half: a buffer was last read two stages ago, which every wave
+  // finished before the barrier of the stage between
+  advance();
+  if (J < nt) load(J, 0);
+  while (J < nt) {
+    store(0);
+    __syncthreads();
+    load(J, 1);  // in flight during the MFMAs below
+    mma(std::integral_constant<int, 0>{});
+    store(1);
+    __syncthreads();
+    advance();
+    if (J < nt) load(J, 0);
+    mma(std::integral_constant<int, 1>{});
+  }
+#pragma unroll
+  for (int a = 0; a < RW; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int mu = m0 + wr + a * 16 + 4 * r + lk;
+        const int i = b * 16 + li;
+        if (mu < nbf && i < nocc) X[(int64_t)mu * ldx + (int64_t)blockIdx.y * nocc + i] = acc[a][b][r];
+      }
+}
+
+// X rows m of the workgroups, or 0 where the kernel above does not serve: up to
+// 160 columns; 128 rows halve the reads of C per flop and are taken unless the
+// last workgroup of 128 would be half empty in a small matrix
+static int kxs_rows(int nbf, int nocc) {
+  if (nocc > 160) return 0;
+  const int m128 = (nbf + 127) / 128 * 128, m64 = (nbf + 63) / 64 * 64;
+  return m128 <= m64 + m64 / 8 ? 128 : 64;
+}
+
+static void kx64_launch(const JKArgs& a, const double* C, int nocc, int q0, int nq, const double* Cp, double* X,
+                        int64_t ldx, hipStream_t st) {
+  if (const int mr = kxs_rows(a.nbf, nocc)) {
+    const dim3 g((a.nbf + mr - 1) / mr, nq);
+    switch ((nocc + 15) / 16) {
+#define KXS(N)                                                                                                    \
+  case N:                                                                                                         \
+    if (mr == 128)                                                                                                \
+      hipLaunchKernelGGL((kx64s_kernel<N, 2>), g, dim3(KS_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
+                         C, nocc, X, ldx);                                                                        \
+    else                                                                                                          \
+      hipLaunchKernelGGL((kx64s_kernel<N, 1>), g, dim3(KS_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
+                         C, nocc, X, ldx);                                                                        \
+    break;
+      KXS(1) KXS(2) KXS(3) KXS(4) KXS(5) KXS(6) KXS(7) KXS(8) KXS(9) KXS(10)
+#undef KXS
+    }
+    return;
+  }
+  const int ncb = (nocc + 63) / 64;
+  const int mr = 64 * kx_rb(ncb);
+  const dim3 g((a.nbf + mr - 1) / mr, nq);
+  switch (ncb) {
+#define KX64(N)                                                                                                  \
+  case N:                                                                                                        \
+    hipLaunchKernelGGL((kx64_kernel<N, kx_rb(N)>), g, dim3(KX_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, Cp, nocc, \
+                       X, ldx);                                                                                  \
+    break;
+    KX64(3) KX64(4) KX64(5) KX64(6) KX64(7) KX64(8)
+#undef KX64
+  }
+}
+
 // ---- phase 2: P_s = X_s X_s^T (lower TM x TM tiles) for k-slices s of X.
 // Workgroups are dealt round-robin to the 8 XCDs; every tile of a slice goes to
 // one XCD so that the slice of X is fetched from HBM once per XCD L2.  Tiles of
@@ -388,7 +576,7 @@ static size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 static F64Plan f64_plan(const JKArgs& a, int nocc) {
   F64Plan p{};
   const size_t per_q = (size_t)a.nbf * nocc * sizeof(double);
-  p.np = 64 * ((nocc + 63) / 64);
+  p.np = kxs_rows(a.nbf, nocc) ? 0 : 64 * ((nocc + 63) / 64);  // columns of the padded copy of C, if one is made
   p.nbfp = ntiles_for(a.nbf) * TILE;
   p.c_bytes = (size_t)p.nbfp * p.np * sizeof(double);
   size_t xbytes = (size_t)8 << 30;
@@ -408,7 +596,9 @@ static F64Plan f64_plan(const JKArgs& a, int nocc) {
   p.qc = (a.naux + nchunks - 1) / nchunks;
   const int64_t kdim = (int64_t)p.qc * nocc;
   p.ldx = (kdim + 7) / 8 * 8;
-  p.sy = syrk_plan(a.nbf, kdim, std::max<int64_t>(by_mem, 8));
+  // no more partial sums than 2048 tiles of 128 x 128 would have
+  const int64_t mt = (a.nbf + 127) / 128, most = (2048 / (mt * (mt + 1) / 2) + 8) / 8 * 8;
+  p.sy = syrk_plan(a.nbf, kdim, std::max<int64_t>(std::min(by_mem, most), 8));
   p.x_bytes = (size_t)a.nbf * p.ldx * sizeof(double);
   p.p_bytes = (size_t)p.sy.ns * a.nbf * a.nbf * sizeof(double);
   return p;
@@ -427,19 +617,10 @@ void half_transform_f64(const JKArgs& a, const double* C, int nocc, int q0, int 
   if (q0 < 0 || nq <= 0 || q0 + nq > a.naux || ldx < (int64_t)nq * nocc) throw Error(-1, "half transform: bad range");
   double* Cp = reinterpret_cast<double*>(work);
   const int64_t ncp = (int64_t)p.nbfp * p.np;
-  hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
-                     p.np, Cp);
-  const int mr = 64 * kx_rb(ncb);
-  const dim3 g1((a.nbf + mr - 1) / mr, nq);
-  switch (ncb) {
-#define KX64(N)                                                                                                   \
-  case N:                                                                                                         \
-    hipLaunchKernelGGL((kx64_kernel<N, kx_rb(N)>), g1, dim3(KX_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, Cp, nocc, \
-                       X, ldx);                                                                                   \
-    break;
-    KX64(1) KX64(2) KX64(3) KX64(4) KX64(5) KX64(6) KX64(7) KX64(8)
-#undef KX64
-  }
+  if (ncp)
+    hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
+                       p.np, Cp);
+  kx64_launch(a, C, nocc, q0, nq, Cp, X, ldx, st);
 }
 
 size_t k_work_bytes_f64(const JKArgs& a, int nocc) {
@@ -457,23 +638,14 @@ void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* wo
   double* P = reinterpret_cast<double*>(w + a256(p.x_bytes));
   double* Cp = reinterpret_cast<double*>(w + a256(p.x_bytes) + a256(p.p_bytes));
   const int64_t ncp = (int64_t)p.nbfp * p.np;
-  hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
-                     p.np, Cp);
+  if (ncp)
+    hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
+                       p.np, Cp);
   for (int q0 = 0; q0 < a.naux; q0 += p.qc) {
     const int nq = std::min(p.qc, a.naux - q0);
     const int64_t kdim = (int64_t)nq * nocc;
-    const int mr = 64 * kx_rb(ncb);
-    const dim3 g1((a.nbf + mr - 1) / mr, nq);
     if (timer) timer->begin_x();
-    switch (ncb) {
-#define KX64(N)                                                                                                   \
-  case N:                                                                                                         \
-    hipLaunchKernelGGL((kx64_kernel<N, kx_rb(N)>), g1, dim3(KX_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, Cp, nocc, \
-                       X, p.ldx);                                                                                 \
-    break;
-      KX64(1) KX64(2) KX64(3) KX64(4) KX64(5) KX64(6) KX64(7) KX64(8)
-#undef KX64
-    }
+    kx64_launch(a, C, nocc, q0, nq, Cp, X, p.ldx, st);
     if (timer) timer->end_x();
     if (timer) timer->begin_syrk();
     syrk_run(p.sy, X, p.ldx, a.nbf, kdim, P, K, q0 > 0, st);

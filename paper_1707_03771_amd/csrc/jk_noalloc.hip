@@ -57,7 +57,7 @@ int dfx_jk_noalloc(const dfx_B* b, const double* dev_C, int nocc, int precision,
     if (nocc > 512) throw Error(DFX_EUNSUPPORTED, "dfx_jk_noalloc: more than 512 occupied orbitals");
     hipStream_t st = (hipStream_t)stream;
     const int nbf = b->nbf;
-    JKArgs a{b->hi.as<float>(), b->lo.as<float>(), b->naux, nbf, b->ncols_t, precision};
+    JKArgs a = b->jk_args(precision);
     a.ws_cap = NOALLOC_SCRATCH_BYTES;
     // sizes first: nothing is launched unless both builds fit
     const size_t jbytes = dev_J ? j_work_bytes(nbf, b->naux, b->ncols_t) : 0;

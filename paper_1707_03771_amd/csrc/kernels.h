@@ -106,13 +106,21 @@ struct JKArgs {
   int naux, nbf;
   int64_t ncols;   // tiled columns
   int prec;
+  // the tiles of B that hold a kept pair (the rest of B is zero): a bit per tile
+  // column in mw 64-bit words per tile row (both triangles), the nt_kept lower
+  // tiles in order, and of every lower tile its place among them or -1
+  const unsigned long long* mask;
+  int mw;
+  const int* tiles;
+  const int* tpos;
+  int nt_kept;
   // K work cap in bytes (0: the default chunk sizes).  With a cap the
   // auxiliary index is cut into as many chunks as it takes for k_work_bytes to
   // stay within it, and the SYRK keeps eight partial-sum slices; DFX_ENOMEM if
   // even one auxiliary function per chunk does not fit.
   size_t ws_cap = 0;
 };
-// bytes of work of the Coulomb builds below
+// bytes of work of the Coulomb builds below, for any set of kept tiles
 size_t j_work_bytes(int nbf, int naux, int64_t ncols);
 // J from a density, or from the occupied block C [nbf][nocc] (D = C C^T)
 void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st);

@@ -979,7 +979,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       void end_syrk() override { s->end(); }
     } ktimer;
     int n_jk_p[3] = {0, 0, 0};
-    JKArgs ja{B->hi.as<float>(), B->lo.as<float>(), B->naux, n, B->ncols_t, PREC_FP64};
+    JKArgs ja = B->jk_args(PREC_FP64);
     const bool mixed = (o.schedule == DFX_SCHED_MIXED);
     int nfp64 = 0, it = 0, n_mixed = 0, it_done = 0;
     double floor_est[3] = {0.0, 0.0, 0.0};
@@ -1478,7 +1478,7 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
     DFX_HIP(hipStreamSynchronize(st));
     const auto t1c = clk::now();
 
-    JKArgs ja{B->hi.as<float>(), B->lo.as<float>(), B->naux, n, B->ncols_t, PREC_FP64};
+    JKArgs ja = B->jk_args(PREC_FP64);
     dfx_scf_info inf{};
     std::vector<double> Bdiis((size_t)dsz * dsz, 0.0);
     int hcount = 0, hpos = 0, it = 0;
