@@ -446,6 +446,7 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
         }
       }
     B->ncols_p = B->col_off.back();
+    B->ldr = (B->ncols_p + 15) / 16 * 16;
     // raw's columns class by class, pair by pair, each pair's block row-major in
     // (first shell, second shell) (the ERI stores of a wave fill one contiguous
     // block); canonical column -> raw column for export
@@ -467,7 +468,7 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
 
     // -- raw (mu nu|P), aux-major, packed pair columns; every element is written
     // by the class launches below (screened triplets as zeros), so no clearing
-    B->raw.alloc(sizeof(double) * (size_t)naux * B->ncols_p);
+    B->raw.alloc(sizeof(double) * (size_t)naux * B->ldr);
     std::vector<DevMem> qcl_d(5);
     for (int l = 0; l <= 4; ++l) {
       std::vector<double> q;
@@ -561,7 +562,7 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
         a.nk = (int)auxby[lc].size();
         a.tau = tau;
         a.out = B->raw.as<double>();
-        a.ld = B->ncols_p;
+        a.ld = B->ldr;
         a.rys = rys;
         eri3_dispatch(cls / 4, cls % 4, lc, false, STORE_CLASS, a, fork.s[k]);
       }
@@ -668,8 +669,8 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     tt.start();
     // the Cholesky work (at least 65 naux doubles) holds the packed diagonal blocks
     if (cw.n < sizeof(double) * trsm_work_elems(naux)) throw Error(-1, "eri3: Cholesky work too small for the solve");
-    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, cw.as<double>(), st, &ut);
-    tile_split(Bw, naux, B->ncols_p, src_d.as<int64_t>(), B->hi.as<float>(), B->lo.as<float>(), B->ncols_t, st);
+    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, B->ldr, cw.as<double>(), st, &ut);
+    tile_split(Bw, naux, B->ldr, src_d.as<int64_t>(), B->hi.as<float>(), B->lo.as<float>(), B->ncols_t, st);
     DFX_HIP(hipGetLastError());
     tt.stop();
     B->info.trsm_seconds = tt.seconds();
@@ -844,7 +845,8 @@ int dfx_B_export(const dfx_B* bc, int what, int q0, int q1, double* dev_out, voi
     if (what == DFX_EXPORT_RAW && !b->rawcol_d.p) b->rawcol_d = upload(b->rawcol, st);
     export_rows(what == DFX_EXPORT_RAW ? nullptr : b->hi.as<float>(),
                 what == DFX_EXPORT_B ? b->lo.as<float>() : nullptr,
-                what == DFX_EXPORT_RAW ? b->raw.as<double>() : nullptr, b->ncols_t, q0, q1,
+                what == DFX_EXPORT_RAW ? b->raw.as<double>() : nullptr,
+                what == DFX_EXPORT_RAW ? b->ldr : b->ncols_t, q0, q1,
                 what == DFX_EXPORT_RAW ? b->rawcol_d.as<int64_t>() : b->toff.as<int64_t>(), b->ncols_p, dev_out, st);
     DFX_HIP(hipGetLastError());
   });

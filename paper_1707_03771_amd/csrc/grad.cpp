@@ -162,7 +162,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
     std::unique_ptr<dfx_B> B = build_B(std::move(hb), std::move(ha), o.tau, DFX_KEEP_METRIC, st);
     const HostShells& bas = B->bas;
     const HostShells& axs = B->aux;
-    const int64_t ncols = B->ncols_p;
+    const int64_t ncols = B->ncols_p, ldg = B->ldr;  // Gam has raw's columns and row stride
     const double* L = B->L.as<double>();
     inf.t_setup = B->info.eri_seconds + B->info.metric_seconds + B->info.trsm_seconds;
 
@@ -205,7 +205,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
           }
     }
     DevMem cmu_d = upload(cmu, st), cnu_d = upload(cnu, st);
-    DevMem Gam(8 * (size_t)naux * std::max<int64_t>(ncols, 1));
+    DevMem Gam(8 * (size_t)naux * std::max<int64_t>(ldg, 1));
     const int64_t nsq = (int64_t)nocc * nocc;
     DevMem bmat(8 * (size_t)naux * nsq);
     {
@@ -222,7 +222,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
         gemm(n, n, nocc, U.as<double>(), ldx, false, Cd.as<double>(), nocc, true, T.as<double>(), n, -2.0, nq, nocc, 0,
              n2);
         gam_pack(T.as<double>(), D.as<double>(), n, gam.as<double>() + q0, cmu_d.as<int>(), cnu_d.as<int>(), ncols, nq,
-                 Gam.as<double>() + (int64_t)q0 * ncols, st);
+                 Gam.as<double>() + (int64_t)q0 * ldg, ldg, st);
         // b_Q = C^T X_Q
         gemm(nocc, nocc, n, Cd.as<double>(), nocc, true, X.as<double>(), ldx, false,
              bmat.as<double>() + (int64_t)q0 * nsq, nocc, 1.0, nq, 0, nocc, nsq);
@@ -233,10 +233,10 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
     gemm(naux, naux, (int)nsq, bmat.as<double>(), nsq, false, bmat.as<double>(), nsq, true, M.as<double>(), naux, 1.0);
     bmat.release();
     rank1_sub2(M.as<double>(), gam.as<double>(), naux, st);
-    trsm_solve_t(L, naux, M.as<double>(), naux, st);                // L^-T M
+    trsm_solve_t(L, naux, M.as<double>(), naux, naux, st);                // L^-T M
     transpose_sq(M.as<double>(), Y.as<double>(), naux, st);         // (L^-T M)^T = M L^-1
-    trsm_solve_t(L, naux, Y.as<double>(), naux, st);                // L^-T M L^-1
-    trsm_solve_t(L, naux, Gam.as<double>(), ncols, st);
+    trsm_solve_t(L, naux, Y.as<double>(), naux, naux, st);                // L^-T M L^-1
+    trsm_solve_t(L, naux, Gam.as<double>(), ncols, ldg, st);
     sp_w.end();
 
     std::vector<double> g((size_t)natom * 3, 0.0);
@@ -283,7 +283,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
           e.rys = rys;
           const dim3 grid = eri3_grid(e);
           ga.gam = Gam.as<double>();
-          ga.ldg = ncols;
+          ga.ldg = ldg;
           ga.scale_off = 2.0;
           const int ng = grad_groups_of(LA, LB, lc);
           const int64_t ps = (int64_t)grid.y * e.npairs, ks = (int64_t)e.nk * grid.x;

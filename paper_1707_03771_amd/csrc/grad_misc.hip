@@ -255,12 +255,12 @@ void onee_grad_dispatch(int LA, int LB, OneEGradArgs g, const double* Dw, const 
 // + T[q][mu][nu], (mu, nu) = cols[c] (T = -2 D X_q C^T, dense per row of the chunk)
 __global__ void gam_pack_kernel(const double* __restrict__ T, const double* __restrict__ D, int nbf,
                                 const double* __restrict__ gam, const int* __restrict__ cmu,
-                                const int* __restrict__ cnu, int64_t ncols, double* __restrict__ out) {
+                                const int* __restrict__ cnu, int64_t ncols, double* __restrict__ out, int64_t ld) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncols) return;
   const int q = blockIdx.y;
   const int64_t e = (int64_t)cmu[c] * nbf + cnu[c];
-  out[(int64_t)q * ncols + c] = fma(4.0 * gam[q], D[e], T[(int64_t)q * nbf * nbf + e]);
+  out[(int64_t)q * ld + c] = fma(4.0 * gam[q], D[e], T[(int64_t)q * nbf * nbf + e]);
 }
 
 // M -= 2 gam gam^T (n x n)
@@ -294,10 +294,10 @@ __global__ void scale_cols_kernel(const double* __restrict__ C, const double* __
 }
 
 void gam_pack(const double* T, const double* D, int nbf, const double* gam, const int* cmu, const int* cnu,
-              int64_t ncols, int nq, double* out, hipStream_t st) {
+              int64_t ncols, int nq, double* out, int64_t ld, hipStream_t st) {
   if (nq <= 0 || ncols <= 0) return;
   hipLaunchKernelGGL(gam_pack_kernel, dim3((unsigned)((ncols + 255) / 256), nq), dim3(256), 0, st, T, D, nbf, gam,
-                     cmu, cnu, ncols, out);
+                     cmu, cnu, ncols, out, ld);
 }
 void rank1_sub2(double* M, const double* gam, int n, hipStream_t st) {
   const int64_t t = (int64_t)n * n;

@@ -172,6 +172,7 @@ struct dfx_B {
   dfx::DevShellSet dbas, daux;
   int nbf = 0, naux = 0;
   int64_t ncols_t = 0, ncols_p = 0;
+  int64_t ldr = 0;                  // row stride of raw: ncols_p up to whole 128-byte lines
   double tau = 1e-12;
   std::vector<int> pa, pb;          // kept pairs (canonical)
   std::vector<int64_t> col_off;     // [npairs + 1]

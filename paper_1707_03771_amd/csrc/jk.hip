@@ -296,7 +296,7 @@ void k_build(const JKArgs& a, const double* C, int nocc, double* K, void* work, 
 // ---------------------------------------------------------------------------
 // canonical packed export: out[q - q0][c] = B[q][toff[c]] (hi + lo), or raw[q][toff[c]]
 __global__ void export_kernel(const float* __restrict__ hi, const float* __restrict__ lo,
-                              const double* __restrict__ raw, int64_t ncols_t,
+                              const double* __restrict__ raw, int64_t ld,
                               const int64_t* __restrict__ toff, int64_t ncols_p, int q0,
                               double* __restrict__ out) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -304,8 +304,8 @@ __global__ void export_kernel(const float* __restrict__ hi, const float* __restr
   const int q = q0 + blockIdx.y;
   // toff[c]: the tile offset of canonical column c in B's rows, or its raw column
   out[(int64_t)blockIdx.y * ncols_p + c] =
-      raw ? raw[(int64_t)q * ncols_p + toff[c]]
-          : (double)hi[(int64_t)q * ncols_t + toff[c]] + (lo ? (double)lo[(int64_t)q * ncols_t + toff[c]] : 0.0);
+      raw ? raw[(int64_t)q * ld + toff[c]]
+          : (double)hi[(int64_t)q * ld + toff[c]] + (lo ? (double)lo[(int64_t)q * ld + toff[c]] : 0.0);
 }
 
 // out[q - q0][mu][nu] = B_q (mu, nu) = hi + lo at the packed tile position
@@ -328,11 +328,11 @@ void unpack_rows(const float* hi, const float* lo, int64_t ncols_t, int nbf, int
   hipLaunchKernelGGL(unpack_rows_kernel, g, dim3(256), 0, st, hi, lo, ncols_t, nbf, q0, out);
 }
 
-void export_rows(const float* hi, const float* lo, const double* raw, int64_t ncols_t, int q0, int q1,
+void export_rows(const float* hi, const float* lo, const double* raw, int64_t ld, int q0, int q1,
                  const int64_t* toff, int64_t ncols_p, double* out, hipStream_t st) {
   if (q1 <= q0 || ncols_p <= 0) return;
   const dim3 g((unsigned)((ncols_p + 255) / 256), q1 - q0);
-  hipLaunchKernelGGL(export_kernel, g, dim3(256), 0, st, hi, lo, raw, ncols_t, toff, ncols_p, q0, out);
+  hipLaunchKernelGGL(export_kernel, g, dim3(256), 0, st, hi, lo, raw, ld, toff, ncols_p, q0, out);
 }
 
 }  // namespace dfx

@@ -11,16 +11,24 @@
 #include <string>
 #include <type_traits>
 
+#include "gemm_dma.h"
 #include "kernels.h"
 
 namespace dfx {
-
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int S64 = 16;   // k-width of one LDS stage (half a tile column of B_Q)
 constexpr int PA = 1;     // row padding (doubles) of [row][k] tiles: odd row strides keep the
                           // fragment reads of 16 consecutive rows on distinct banks
 constexpr int PB = 16;    // row padding (doubles) of the [k][i] C stage
+
+// Place of X[mu][k], k = (Q, i): rows of stride ldx, or with ldx = 0 in blocks of
+// 16 k, [k / 16][mu][k % 16]: a stage of the contraction below then reads
+// consecutive kilobytes.  With rows of 10 to 20 MB it took 128 bytes from each of
+// 256 pages per stage: the
+// contraction at nbf = 1200, nocc = 120, naux = 3600 in 12.4 ms, in blocks 11.0.
+__device__ __forceinline__ int64_t x_place(int64_t ldx, int nbf, int mu, int64_t k) {
+  return ldx ? (int64_t)mu * ldx + k : ((k >> 4) * nbf + mu) * 16 + (k & 15);
+}
 
 // C_occ zero-padded to Cp[nbfp][np] (np = 64 NCB, nbfp = 32 ntiles), so that a
 // k-stage of C is one contiguous, aligned block
@@ -154,24 +162,39 @@ __global__ void __launch_bounds__(KX_T) kx64_kernel(const float* __restrict__ hi
       for (int r = 0; r < 4; ++r) {
         const int mu = m0 + wr + a * 16 + 4 * r + lk;
         const int i = wc + b * 16 + li;
-        if (mu < nbf && i < nocc) X[(int64_t)mu * ldx + (int64_t)blockIdx.y * nocc + i] = acc[a][b][r];
+        if (mu < nbf && i < nocc) X[x_place(ldx, nbf, mu, (int64_t)blockIdx.y * nocc + i)] = acc[a][b][r];
       }
 }
 
 // ---- phase 1 with up to 160 occupied columns: NB blocks of 16 columns, so that
 // no more than 15 columns are padding (a multiple of 64 wasted 49% at nocc = 65
-// and 38% at 40).  Four waves own RW x 16 rows each and all NB column blocks;
-// C is read in place.  Only the tiles of B that hold a kept pair are visited: a
-// workgroup walks the union of its tile rows' masks, and a tile row without the
-// tile reads nothing.  In long molecules half of the tiles hold none (zigzag
-// C30H62: 56% of the columns screened).
+// and 38% at 40).  Four waves own RW x 16 rows each and all NB column blocks.
+// Only the tiles of B that hold a kept pair are visited: a workgroup walks the
+// union of its tile rows' masks, and a tile row without the tile reads nothing
+// (a buffer of length zero gives zeros).  In long molecules half of the tiles
+// hold none (zigzag C30H62: 56% of the columns screened).
+// As for the products of gemm_dma.h, vector instructions stop the matrix cores:
+// C goes to LDS by DMA from a padded copy (whose rows of odd nu have their
+// 16-column blocks swapped in pairs when NB is even, so that fragment reads
+// spread over the banks), B's words come by buffer loads at scalar bases, and
+// what is left is their conversion, in one place per stage.
 constexpr int KS_T = 256;
+__global__ void cpad16_kernel(const double* __restrict__ C, int nbf, int nocc, int nbfp, int np,
+                              double* __restrict__ Cp) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (int64_t)nbfp * np) return;
+  const int nu = (int)(idx / np), c = (int)(idx % np);
+  const int i = (nu & 1) && np % 32 == 0 ? c ^ 16 : c;
+  Cp[idx] = (nu < nbf && i < nocc) ? C[(int64_t)nu * nocc + i] : 0.0;
+}
+
+extern __shared__ __attribute__((aligned(1024))) double kxs_lds[];
 template <int NB, int RW>
-__global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ hi, const float* __restrict__ lo,
-                                                     int64_t ncols, int nbf, int q0,
-                                                     const unsigned long long* __restrict__ mask, int mw,
-                                                     const double* __restrict__ C, int nocc,
-                                                     double* __restrict__ X, int64_t ldx) {
+__global__ void __launch_bounds__(KS_T, 2) kx64s_kernel(const float* __restrict__ hi, const float* __restrict__ lo,
+                                                        int64_t ncols, int nbf, int q0,
+                                                        const unsigned long long* __restrict__ mask, int mw,
+                                                        const double* __restrict__ Cp, int nocc,
+                                                        double* __restrict__ X, int64_t ldx) {
   constexpr int NP = 16 * NB;
   constexpr int MR = 64 * RW;                 // rows of the workgroup
   constexpr int TR = MR / 32;                 // its tile rows
@@ -179,14 +202,17 @@ __global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ h
   constexpr int EP = 32 * S64 / TPR;          // consecutive A elements per thread per stage: 4 or 8
   constexpr int DK = S64 / EP;                // threads per row of a direct stage
   constexpr int TM = 32 / EP;                 // threads per row of a mirrored stage
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
   typedef float v4fl __attribute__((ext_vector_type(4)));
   __shared__ double As[2][MR][S64 + PA];
-  __shared__ double Bs[2][S64][NP + PB];
+  // dynamic: the compiler does not see the DMA loads write it, and must not take
+  // it for memory that nothing writes
+  double* const Bs[2] = {kxs_lds, kxs_lds + S64 * NP};
   const int Q = q0 + blockIdx.y;
   const int m0 = blockIdx.x * MR;
   const int I0 = m0 >> 5;
   const int nt = ntiles_for(nbf);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const int wr = w * 16 * RW;
   const float* __restrict__ rh = hi + (int64_t)Q * ncols;
@@ -213,36 +239,40 @@ __global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ h
     bits &= bits - 1;
   };
 
-  constexpr int CK = KS_T / S64;              // threads per k row of the C stage: 16
-  const int ck = tid / CK, ci = tid % CK;     // k row, first column
-  // loads without branches, so that all of a stage are in flight at once: an
-  // operand that is zero reads a valid place (tile 0, the last row or column of
-  // C) and is set to zero on its way into LDS
-  v4fl ah[EP / 4], al[EP / 4];
-  double cr[NB];
-  bool direct = false, kept = false, inrow = false;
-  auto load = [&](int Jt, int h) {
+  // byte offsets of the lane in a tile: direct tile (I, J): row mu = t / DK, nu =
+  // EP (t % DK) ..; tile (J, I), mirrored: row nu = t / TM, mu = EP (t % TM) ..
+  const int vod = ((t / DK) * 32 + (t % DK) * EP) * 4, vom = ((t / TM) * 32 + (t % TM) * EP) * 4;
+  v4u ah[EP / 4], al[EP / 4];
+  bool direct = false;
+  auto load = [&](int Jt, int h, int buf) {
     direct = I >= Jt;
-    kept = I < nt && (mrow[Jt >> 6] >> (Jt & 63) & 1);
-    // direct tile (I, J): row mu = t / DK, nu = 16 h + EP (t % DK) ..; else tile
-    // (J, I): row nu = 16 h + t / TM, mu = EP (t % TM) ..
+    const bool kept = I < nt && (mrow[Jt >> 6] >> (Jt & 63) & 1);
     const int64_t base = kept ? (direct ? tile_base(I, Jt) : tile_base(Jt, I)) : 0;
-    const int off = direct ? (t / DK) * 32 + 16 * h + (t % DK) * EP : (16 * h + t / TM) * 32 + (t % TM) * EP;
+    const int n = kept ? TILE2 * 4 : 0;
+    const __amdgpu_buffer_rsrc_t dh =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(rh + base), 0, n, 0x00027000);
+    const __amdgpu_buffer_rsrc_t dl =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(rl + base), 0, n, 0x00027000);
+    const int vo = direct ? vod : vom, so = direct ? 64 * h : 2048 * h;
 #pragma unroll
     for (int v = 0; v < EP / 4; ++v) {
-      ah[v] = reinterpret_cast<const v4fl*>(rh + base + off)[v];
-      al[v] = reinterpret_cast<const v4fl*>(rl + base + off)[v];
+      ah[v] = __builtin_amdgcn_raw_buffer_load_b128(dh, vo, so + 16 * v, 0);
+      al[v] = __builtin_amdgcn_raw_buffer_load_b128(dl, vo, so + 16 * v, 0);
     }
-    const int nu = 32 * Jt + 16 * h + ck;
-    inrow = nu < nbf;
-    const double* __restrict__ cp = C + (int64_t)min(nu, nbf - 1) * nocc;
+    // the C stage: 2 NB loads of 1 KB, dealt to the waves
+    const double* cs = Cp + (int64_t)(2 * Jt + h) * S64 * NP;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) cr[b] = cp[min(16 * b + ci, nocc - 1)];
+    for (int c = 0; c < (2 * NB + 3) / 4; ++c)
+      if (4 * c + w < 2 * NB)
+        DmaOp<true, 32>::dma(cs + (4 * c + w) * 128, 1024, &Bs[buf][(4 * c + w) * 128], lane * 16);
   };
   auto store = [&](int b) {
     double v[EP];
 #pragma unroll
-    for (int e = 0; e < EP; ++e) v[e] = kept ? (double)ah[e >> 2][e & 3] + (double)al[e >> 2][e & 3] : 0.0;
+    for (int e = 0; e < EP; ++e) {
+      const v4fl h = __builtin_bit_cast(v4fl, ah[e >> 2]), l = __builtin_bit_cast(v4fl, al[e >> 2]);
+      v[e] = (double)h[e & 3] + (double)l[e & 3];
+    }
     if (direct) {
       const int r = grp * 32 + t / DK, k0 = (t % DK) * EP;
 #pragma unroll
@@ -252,8 +282,6 @@ __global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ h
 #pragma unroll
       for (int e = 0; e < EP; ++e) As[b][r0 + e][k] = v[e];
     }
-#pragma unroll
-    for (int c = 0; c < NB; ++c) Bs[b][ck][16 * c + ci] = inrow && 16 * c + ci < nocc ? cr[c] : 0.0;
   };
 
   v4d acc[RW][NB];
@@ -261,36 +289,62 @@ __global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ h
   for (int a = 0; a < RW; ++a)
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-  auto mma = [&](auto bufc) {
-    constexpr int BUF = decltype(bufc)::value;
+  double fa[2][RW], fb[2][NB];  // the fragments of the current and the next k-step
+  const int sw = NB % 2 == 0 ? (lk & 1) << 4 : 0;
+  auto frag = [&](int buf, int kk, int f) {
 #pragma unroll
-    for (int kk = 0; kk < S64; kk += 4) {
-      double fa[RW];
+    for (int a = 0; a < RW; ++a) fa[f][a] = As[buf][wr + a * 16 + li][kk + lk];
 #pragma unroll
-      for (int a = 0; a < RW; ++a) fa[a] = As[BUF][wr + a * 16 + li][kk + lk];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const double fb = Bs[BUF][kk + lk][b * 16 + li];
-#pragma unroll
-        for (int a = 0; a < RW; ++a) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb, acc[a][b], 0, 0, 0);
-      }
-    }
+    for (int b = 0; b < NB; ++b)
+      fb[f][b] = NB % 2 == 0 ? Bs[buf][lk * NP + li + (((b & 1) << 4) ^ sw) + (b >> 1) * 32 + kk * NP]
+                             : Bs[buf][lk * NP + li + b * 16 + kk * NP];
   };
-  // the two halves of a tile column alternate over the two LDS buffers, one
-  // barrier per half: a buffer was last read two stages ago, which every wave
-  // finished before the barrier of the stage between
+  auto mma = [&](int f) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int a = 0; a < RW; ++a)
+        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[f][a], fb[f][b], acc[a][b], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // The two halves of a tile column alternate over the two LDS buffers.  In a
+  // stage, the fragments of a k-step are read during the MFMAs of the step
+  // before it, across stages too.  After the barrier, where every fragment of
+  // the stage is in registers, the next stage but one is requested: C straight
+  // into the buffer just read, B's words into registers, from which they reach
+  // that buffer in the middle of the next stage.
+  auto stage = [&](auto bufc, bool next, bool next2, int Jt, int h) {
+    constexpr int BUF = decltype(bufc)::value;
+    frag(BUF, 4, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(0);
+    frag(BUF, 8, 0);
+    if (next) store(BUF ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(1);
+    frag(BUF, 12, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(0);
+    stage_sync();
+    if (next) frag(BUF ^ 1, 0, 0);
+    if (next2) load(Jt, h, BUF);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(1);
+  };
   advance();
-  if (J < nt) load(J, 0);
-  while (J < nt) {
+  if (J < nt) {
+    load(J, 0, 0);
     store(0);
-    __syncthreads();
-    load(J, 1);  // in flight during the MFMAs below
-    mma(std::integral_constant<int, 0>{});
-    store(1);
-    __syncthreads();
+    load(J, 1, 1);
+    stage_sync();
+    frag(0, 0, 0);
+  }
+  while (J < nt) {
     advance();
-    if (J < nt) load(J, 0);
-    mma(std::integral_constant<int, 1>{});
+    const bool more = J < nt;
+    stage(std::integral_constant<int, 0>{}, true, more, J, 0);
+    stage(std::integral_constant<int, 1>{}, more, more, J, 1);
   }
 #pragma unroll
   for (int a = 0; a < RW; ++a)
@@ -300,32 +354,35 @@ __global__ void __launch_bounds__(KS_T) kx64s_kernel(const float* __restrict__ h
       for (int r = 0; r < 4; ++r) {
         const int mu = m0 + wr + a * 16 + 4 * r + lk;
         const int i = b * 16 + li;
-        if (mu < nbf && i < nocc) X[(int64_t)mu * ldx + (int64_t)blockIdx.y * nocc + i] = acc[a][b][r];
+        if (mu < nbf && i < nocc) X[x_place(ldx, nbf, mu, (int64_t)blockIdx.y * nocc + i)] = acc[a][b][r];
       }
 }
 
-// X rows m of the workgroups, or 0 where the kernel above does not serve: up to
-// 160 columns; 128 rows halve the reads of C per flop and are taken unless the
-// last workgroup of 128 would be half empty in a small matrix
+// Rows per workgroup, or 0 where the kernel above does not serve: up to 160
+// columns; 128 rows halve the reads of C per flop and are taken unless the last
+// workgroup of 128 would be half empty in a small matrix, or the accumulators
+// and fragments of 128 rows would no longer fit in 256 registers.
 static int kxs_rows(int nbf, int nocc) {
   if (nocc > 160) return 0;
+  if (nocc > 128) return 64;
   const int m128 = (nbf + 127) / 128 * 128, m64 = (nbf + 63) / 64 * 64;
   return m128 <= m64 + m64 / 8 ? 128 : 64;
 }
 
-static void kx64_launch(const JKArgs& a, const double* C, int nocc, int q0, int nq, const double* Cp, double* X,
-                        int64_t ldx, hipStream_t st) {
+static void kx64_launch(const JKArgs& a, int nocc, int q0, int nq, const double* Cp, double* X, int64_t ldx,
+                        hipStream_t st) {
   if (const int mr = kxs_rows(a.nbf, nocc)) {
     const dim3 g((a.nbf + mr - 1) / mr, nq);
+    const unsigned lds = 2 * S64 * 16 * ((nocc + 15) / 16) * sizeof(double);
     switch ((nocc + 15) / 16) {
 #define KXS(N)                                                                                                    \
   case N:                                                                                                         \
     if (mr == 128)                                                                                                \
-      hipLaunchKernelGGL((kx64s_kernel<N, 2>), g, dim3(KS_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
-                         C, nocc, X, ldx);                                                                        \
+      hipLaunchKernelGGL((kx64s_kernel<N, N <= 8 ? 2 : 1>), g, dim3(KS_T), lds, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
+                         Cp, nocc, X, ldx);                                                                       \
     else                                                                                                          \
-      hipLaunchKernelGGL((kx64s_kernel<N, 1>), g, dim3(KS_T), 0, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
-                         C, nocc, X, ldx);                                                                        \
+      hipLaunchKernelGGL((kx64s_kernel<N, 1>), g, dim3(KS_T), lds, st, a.hi, a.lo, a.ncols, a.nbf, q0, a.mask, a.mw, \
+                         Cp, nocc, X, ldx);                                                                       \
     break;
       KXS(1) KXS(2) KXS(3) KXS(4) KXS(5) KXS(6) KXS(7) KXS(8) KXS(9) KXS(10)
 #undef KXS
@@ -346,25 +403,19 @@ static void kx64_launch(const JKArgs& a, const double* C, int nocc, int q0, int 
   }
 }
 
-// ---- phase 2: P_s = X_s X_s^T (lower TM x TM tiles) for k-slices s of X.
-// Workgroups are dealt round-robin to the 8 XCDs; every tile of a slice goes to
-// one XCD so that the slice of X is fetched from HBM once per XCD L2.  Tiles of
-// 128 take eight waves in a 2 x 4 grid of 64 x 32 sub-tiles, tiles of 64 (for
-// the sizes of which 128 leaves much of the border tiles empty, syrk_plan) four
-// waves in a 2 x 2 grid of 32 x 32.  On a diagonal tile the waves whose
-// sub-tiles lie wholly above the diagonal load and synchronise but skip their
-// MFMAs.  Two LDS buffers alternate, so each stage needs one barrier: stage t's
-// buffer was last read in stage t - 2, which every wave finished before the
-// barrier of stage t - 1.  A single slice goes straight to both triangles of K.
-constexpr int sy_threads(int tm) { return 4 * tm; }
+// ---- phase 2: P_s = X_s X_s^T (lower TM x TM tiles) for k-slices s of X, on the
+// main loop of gemm_dma.h.  Workgroups are dealt round-robin to the 8 XCDs;
+// every tile of a slice goes to one XCD so that the slice of X is fetched from
+// HBM once per XCD L2.  Tiles of 64 serve the sizes of which 128 leaves much of
+// the border tiles empty (syrk_plan).  On a diagonal tile the wave whose
+// sub-tile lies above the diagonal skips its MFMAs.  A single slice goes
+// straight to both triangles of K.
+extern __shared__ __attribute__((aligned(1024))) double syrk_lds[];
 template <int TM>
-__global__ void __launch_bounds__(sy_threads(TM)) syrk64_kernel(const double* __restrict__ X, int64_t ldx, int nbf,
-                                                                int64_t kslice, int64_t kdim, int nslices, int ntl,
-                                                                double* __restrict__ P, int accumulate) {
-  constexpr int WM = TM / 2, WN = 32;  // sub-tile of a wave
-  constexpr int FA = WM / 16, FB = WN / 16;
-  __shared__ double As[2][TM][S64 + PA];
-  __shared__ double Bs[2][TM][S64 + PA];
+__global__ void __launch_bounds__(GT, 2) syrk64_kernel(const double* __restrict__ X, int64_t ldx, int64_t kst,
+                                                       int nbf, int64_t kslice, int64_t kdim, int nslices, int ntl,
+                                                       double* __restrict__ P, int accumulate) {
+  constexpr int FA = TM / 32;
   const int bid = blockIdx.x;
   const int xcd = bid & 7, local = bid >> 3;
   const int s = nslices > 1 ? xcd + 8 * (local / ntl) : 0;
@@ -375,98 +426,29 @@ __global__ void __launch_bounds__(sy_threads(TM)) syrk64_kernel(const double* __
   while (ti * (ti + 1) / 2 > tl) --ti;
   const int tj = tl - ti * (ti + 1) / 2;
   const int m0 = ti * TM, n0 = tj * TM;
-  const int64_t k0s = (int64_t)s * kslice;
-  const int64_t k1s = k0s + kslice < kdim ? k0s + kslice : kdim;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = (w & 1) * WM, wn = (w >> 1) * WN;
-  const bool active = !(ti == tj && wn >= wm + WM);
+  const int64_t k0s = min((int64_t)s * kslice, kdim);
+  const int klen = (int)(min(k0s + kslice, kdim) - k0s);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (w & 1) * (TM / 2), wn = (w >> 1) * (TM / 2);
+  const bool active = ti != tj || wn <= wm;
   const int li = lane & 15, lk = lane >> 4;
-  // loader: row r = tid / 4 of both operands, 4 consecutive k from kq
-  const int r = tid >> 2, kq = (tid & 3) * 4;
-  const int ma = m0 + r, nb = n0 + r;
-
-  double va[4], vb[4];
-  auto load = [&](int64_t k0) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) va[e] = vb[e] = 0.0;
-    if (k0 + S64 <= k1s) {
-      if (ma < nbf) {
-        const double2* p = reinterpret_cast<const double2*>(X + (int64_t)ma * ldx + k0 + kq);
-        const double2 v0 = p[0], v1 = p[1];
-        va[0] = v0.x, va[1] = v0.y, va[2] = v1.x, va[3] = v1.y;
-      }
-      if (nb < nbf) {
-        const double2* p = reinterpret_cast<const double2*>(X + (int64_t)nb * ldx + k0 + kq);
-        const double2 v0 = p[0], v1 = p[1];
-        vb[0] = v0.x, vb[1] = v0.y, vb[2] = v1.x, vb[3] = v1.y;
-      }
-    } else {  // ragged end of the slice
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t k = k0 + kq + e;
-        if (k < k1s) {
-          if (ma < nbf) va[e] = X[(int64_t)ma * ldx + k];
-          if (nb < nbf) vb[e] = X[(int64_t)nb * ldx + k];
-        }
-      }
-    }
-  };
-
-  v4d acc[FA][FB];
-#pragma unroll
-  for (int a = 0; a < FA; ++a)
-#pragma unroll
-    for (int b = 0; b < FB; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-
-  auto stage = [&](auto bufc) {
-    constexpr int BUF = decltype(bufc)::value;
-#pragma unroll
-    for (int kk = 0; kk < S64; kk += 4) {
-      double fa[FA], fb[FB];
-#pragma unroll
-      for (int a = 0; a < FA; ++a) fa[a] = As[BUF][wm + a * 16 + li][kk + lk];
-#pragma unroll
-      for (int b = 0; b < FB; ++b) fb[b] = Bs[BUF][wn + b * 16 + li][kk + lk];
-#pragma unroll
-      for (int a = 0; a < FA; ++a)
-#pragma unroll
-        for (int b = 0; b < FB; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    }
-  };
-  auto put = [&](int buf) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      As[buf][r][kq + e] = va[e];
-      Bs[buf][r][kq + e] = vb[e];
-    }
-  };
-
-  if (k0s < k1s) load(k0s);
-  for (int64_t k0 = k0s; k0 < k1s; k0 += 2 * S64) {
-    put(0);
-    __syncthreads();
-    if (k0 + S64 < k1s) load(k0 + S64);
-    if (active) stage(std::integral_constant<int, 0>{});
-    if (k0 + S64 < k1s) {
-      put(1);
-      __syncthreads();
-      if (k0 + 2 * S64 < k1s) load(k0 + 2 * S64);
-      if (active) stage(std::integral_constant<int, 1>{});
-    }
-  }
+  DmaOp<true, TM> a, b;
+  a.init(X + k0s * kst, ldx, m0, nbf, klen, w, lane, kst);
+  b.init(X + k0s * kst, ldx, n0, nbf, klen, w, lane, kst);
+  v4d acc[FA][FA];
+  dma_gemm<true, true, TM, TM>(a, b, klen, syrk_lds, wm, wn, active, acc);
   if (!active) return;
   double* __restrict__ Ps = P + (int64_t)s * nbf * nbf;
 #pragma unroll
-  for (int a = 0; a < FA; ++a)
+  for (int i = 0; i < FA; ++i)
 #pragma unroll
-    for (int b = 0; b < FB; ++b)
+    for (int j = 0; j < FA; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int m = m0 + wm + a * 16 + 4 * q + lk;
-        const int n = n0 + wn + b * 16 + li;
+        const int m = m0 + wm + i * 16 + 4 * q + lk;
+        const int n = n0 + wn + j * 16 + li;
         if (m >= nbf || n > m) continue;
-        double v = acc[a][b][q];
+        double v = acc[i][j][q];
         if (nslices == 1) {
           if (accumulate) v += Ps[(int64_t)m * nbf + n];
           Ps[(int64_t)n * nbf + m] = v;
@@ -535,7 +517,7 @@ static SyrkPlan syrk_plan(int n, int64_t kdim, int64_t most_slices) {
       const int64_t per_xcd = ns > 1 ? (int64_t)ntl * ns / 8 : (ntl + 7) / 8;
       const int64_t per_cu = (per_xcd + 31) / 32;
       const double stages = (double)((kdim + (int64_t)ns * S64 - 1) / ((int64_t)ns * S64));
-      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.75) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.6 : 0.7);
+      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.75) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.62 : 0.78);
       double t = (double)per_cu * (stages * (tm == 128 ? 4096.0 : 1024.0) / eff + 3000.0);
       if (ns > 1) t += 12000.0 + (double)ns * n * n * 8.0 / 5.0e12 * 2.4e9;
       if (!best.tm || t < tbest) {
@@ -547,17 +529,19 @@ static SyrkPlan syrk_plan(int n, int64_t kdim, int64_t most_slices) {
   return best;
 }
 
-// K (+)= X X^T over k < kdim; P: ns n^2 doubles (none for one slice)
-static void syrk_run(const SyrkPlan& p, const double* X, int64_t ldx, int n, int64_t kdim, double* P, double* K,
+// K (+)= X X^T over k < kdim; X row-major (kst = 1), or in blocks of 16 k (ldx =
+// 16, kst = n); P: ns n^2 doubles (none for one slice)
+static void syrk_run(const SyrkPlan& p, const double* X, int64_t ldx, int64_t kst, int n, int64_t kdim, double* P, double* K,
                      bool accumulate, hipStream_t st) {
   const int64_t kslice = ((kdim + p.ns - 1) / p.ns + S64 - 1) / S64 * S64;
   double* out = p.ns > 1 ? P : K;
   const unsigned grid = (unsigned)(p.ns * p.ntl);
+  const unsigned lds = 4 * p.tm * GK * sizeof(double);
   if (p.tm == 128)
-    hipLaunchKernelGGL(syrk64_kernel<128>, dim3(grid), dim3(sy_threads(128)), 0, st, X, ldx, n, kslice, kdim, p.ns,
+    hipLaunchKernelGGL(syrk64_kernel<128>, dim3(grid), dim3(GT), lds, st, X, ldx, kst, n, kslice, kdim, p.ns,
                        p.ntl, out, accumulate ? 1 : 0);
   else
-    hipLaunchKernelGGL(syrk64_kernel<64>, dim3(grid), dim3(sy_threads(64)), 0, st, X, ldx, n, kslice, kdim, p.ns,
+    hipLaunchKernelGGL(syrk64_kernel<64>, dim3(grid), dim3(GT), lds, st, X, ldx, kst, n, kslice, kdim, p.ns,
                        p.ntl, out, accumulate ? 1 : 0);
   if (p.ns > 1) k_reduce(P, p.ns, n, K, accumulate, st);
 }
@@ -565,7 +549,6 @@ static void syrk_run(const SyrkPlan& p, const double* X, int64_t ldx, int n, int
 struct F64Plan {
   int qc, np, nbfp;
   SyrkPlan sy;
-  int64_t ldx;
   size_t x_bytes, p_bytes, c_bytes;
 };
 
@@ -576,14 +559,14 @@ static size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 static F64Plan f64_plan(const JKArgs& a, int nocc) {
   F64Plan p{};
   const size_t per_q = (size_t)a.nbf * nocc * sizeof(double);
-  p.np = kxs_rows(a.nbf, nocc) ? 0 : 64 * ((nocc + 63) / 64);  // columns of the padded copy of C, if one is made
+  p.np = kxs_rows(a.nbf, nocc) ? 16 * ((nocc + 15) / 16) : 64 * ((nocc + 63) / 64);  // columns of the copy of C
   p.nbfp = ntiles_for(a.nbf) * TILE;
   p.c_bytes = (size_t)p.nbfp * p.np * sizeof(double);
   size_t xbytes = (size_t)8 << 30;
   int64_t by_mem = ((int64_t)2 << 30) / ((int64_t)a.nbf * a.nbf * 8);
   if (a.ws_cap) {
-    // eight slices, C, the row padding of X (7 doubles per row) and alignment
-    const size_t fixed = a256((size_t)8 * a.nbf * a.nbf * 8) + p.c_bytes + (size_t)a.nbf * 56 + 1024;
+    // eight slices, C, the last block of X and alignment
+    const size_t fixed = a256((size_t)8 * a.nbf * a.nbf * 8) + p.c_bytes + (size_t)a.nbf * 8 * S64 + 1024;
     if (a.ws_cap < fixed + per_q)
       throw Error(DFX_ENOMEM, "K work: " + std::to_string(a.ws_cap) + " bytes hold no chunk (" +
                                   std::to_string(fixed + per_q) + " needed)");
@@ -595,13 +578,20 @@ static F64Plan f64_plan(const JKArgs& a, int nocc) {
   const int nchunks = (int)((a.naux + cap - 1) / cap);
   p.qc = (a.naux + nchunks - 1) / nchunks;
   const int64_t kdim = (int64_t)p.qc * nocc;
-  p.ldx = (kdim + 7) / 8 * 8;
   // no more partial sums than 2048 tiles of 128 x 128 would have
   const int64_t mt = (a.nbf + 127) / 128, most = (2048 / (mt * (mt + 1) / 2) + 8) / 8 * 8;
   p.sy = syrk_plan(a.nbf, kdim, std::max<int64_t>(std::min(by_mem, most), 8));
-  p.x_bytes = (size_t)a.nbf * p.ldx * sizeof(double);
+  p.x_bytes = (size_t)a.nbf * ((kdim + S64 - 1) / S64 * S64) * sizeof(double);
   p.p_bytes = (size_t)p.sy.ns * a.nbf * a.nbf * sizeof(double);
   return p;
+}
+
+static void pad_cocc(const JKArgs& a, const double* C, int nocc, const F64Plan& p, double* Cp, hipStream_t st) {
+  const dim3 g((unsigned)(((int64_t)p.nbfp * p.np + 255) / 256));
+  if (kxs_rows(a.nbf, nocc))
+    hipLaunchKernelGGL(cpad16_kernel, g, dim3(256), 0, st, C, a.nbf, nocc, p.nbfp, p.np, Cp);
+  else
+    hipLaunchKernelGGL(cpad_kernel, g, dim3(256), 0, st, C, a.nbf, nocc, p.nbfp, p.np, Cp);
 }
 
 size_t half_transform_f64_work(const JKArgs& a, int nocc) {
@@ -616,11 +606,8 @@ void half_transform_f64(const JKArgs& a, const double* C, int nocc, int q0, int 
   if (ncb > 8) throw Error(-6, "half transform: more than 512 columns");
   if (q0 < 0 || nq <= 0 || q0 + nq > a.naux || ldx < (int64_t)nq * nocc) throw Error(-1, "half transform: bad range");
   double* Cp = reinterpret_cast<double*>(work);
-  const int64_t ncp = (int64_t)p.nbfp * p.np;
-  if (ncp)
-    hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
-                       p.np, Cp);
-  kx64_launch(a, C, nocc, q0, nq, Cp, X, ldx, st);
+  pad_cocc(a, C, nocc, p, Cp, st);
+  kx64_launch(a, nocc, q0, nq, Cp, X, ldx, st);
 }
 
 size_t k_work_bytes_f64(const JKArgs& a, int nocc) {
@@ -637,18 +624,15 @@ void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* wo
   double* X = reinterpret_cast<double*>(w);
   double* P = reinterpret_cast<double*>(w + a256(p.x_bytes));
   double* Cp = reinterpret_cast<double*>(w + a256(p.x_bytes) + a256(p.p_bytes));
-  const int64_t ncp = (int64_t)p.nbfp * p.np;
-  if (ncp)
-    hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)((ncp + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp,
-                       p.np, Cp);
+  pad_cocc(a, C, nocc, p, Cp, st);
   for (int q0 = 0; q0 < a.naux; q0 += p.qc) {
     const int nq = std::min(p.qc, a.naux - q0);
     const int64_t kdim = (int64_t)nq * nocc;
     if (timer) timer->begin_x();
-    kx64_launch(a, C, nocc, q0, nq, Cp, X, p.ldx, st);
+    kx64_launch(a, nocc, q0, nq, Cp, X, 0, st);
     if (timer) timer->end_x();
     if (timer) timer->begin_syrk();
-    syrk_run(p.sy, X, p.ldx, a.nbf, kdim, P, K, q0 > 0, st);
+    syrk_run(p.sy, X, S64, a.nbf, a.nbf, kdim, P, K, q0 > 0, st);
     if (timer) timer->end_syrk();
   }
 }
@@ -663,7 +647,7 @@ void syrk_f64(const double* A, int64_t lda, int n, int64_t k, double* C, double*
   if (n <= 0) return;
   if ((lda & 1) || lda < k || (reinterpret_cast<uintptr_t>(A) & 15))
     throw Error(-1, "syrk_f64: A needs an even row stride >= k and 16-byte alignment");
-  syrk_run(syrk_plan(n, k, 8), A, lda, n, k, work, C, false, st);
+  syrk_run(syrk_plan(n, k, 8), A, lda, 1, n, k, work, C, false, st);
 }
 
 }  // namespace dfx

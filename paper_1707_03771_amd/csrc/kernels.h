@@ -54,7 +54,7 @@ void dgemm(const GemmF64& g, hipStream_t st);
 void dgemm_sk(const GemmF64& g, double* work, int64_t work_elems, hipStream_t st);
 
 
-// B = L^-1 raw in place over raw (n x ncols, FP64, row stride ncols), by
+// B = L^-1 raw in place over raw (n x ncols, FP64, row stride ld), by
 // blocked forward substitution with the lower-triangular L (n x n): backward
 // stable, unlike a product with an explicit inverse.  work: trsm_work_elems(n)
 // doubles (packed copies of L's 64 x 64 diagonal blocks), free once the last
@@ -70,14 +70,14 @@ struct TrsmTimer {
   virtual ~TrsmTimer() = default;
 };
 size_t trsm_work_elems(int n);
-TrsmStats trsm_solve(const double* L, int n, double* raw, int64_t ncols, double* work, hipStream_t st,
+TrsmStats trsm_solve(const double* L, int n, double* raw, int64_t ncols, int64_t ld, double* work, hipStream_t st,
                      TrsmTimer* timer = nullptr);
-// X = L^-T X in place (n x ncols, row stride ncols) by blocked back
+// X = L^-T X in place (n x ncols, row stride ld) by blocked back
 // substitution with the lower-triangular L: the transpose of trsm_solve.
-void trsm_solve_t(const double* L, int n, double* X, int64_t ncols, hipStream_t st);
-// hi = fl32(B), lo = fl32(B - hi) of B (n x ncols) into rows of length ld_out (whole
+void trsm_solve_t(const double* L, int n, double* X, int64_t ncols, int64_t ld, hipStream_t st);
+// hi = fl32(B), lo = fl32(B - hi) of B (n rows, row stride ld) into rows of length ld_out (whole
 // 32 x 32 tiles): element t of each row from column src[t] of B, zero where src[t] < 0
-void tile_split(const double* B, int n, int64_t ncols, const int64_t* src, float* hi, float* lo, int64_t ld_out,
+void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* hi, float* lo, int64_t ld_out,
                 hipStream_t st);
 
 // Blocked Cholesky J = L L^T in place (lower), then Linv = L^-1.  Returns via
@@ -167,7 +167,8 @@ void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* 
 // dense rows out[q1 - q0][nbf][nbf] (FP64 = hi + lo) from the tiled storage
 void unpack_rows(const float* hi, const float* lo, int64_t ncols_t, int nbf, int q0, int q1, double* out,
                  hipStream_t st);
-void export_rows(const float* hi, const float* lo, const double* raw, int64_t ncols_t, int q0, int q1,
+// ld: the row stride of the source, tiled or raw
+void export_rows(const float* hi, const float* lo, const double* raw, int64_t ld, int q0, int q1,
                  const int64_t* toff, int64_t ncols_p, double* out, hipStream_t st);
 
 // ---- small dense helpers (linalg.hip) ----------------------------------------

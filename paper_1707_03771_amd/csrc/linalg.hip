@@ -4,15 +4,15 @@
 // M' = L^-1 by blocked forward substitution, then split into two FP32 words.
 #include <algorithm>
 
+#include "gemm_dma.h"
 #include "kernels.h"
 
 namespace dfx {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-
-constexpr int GM = 128, GN = 128, GK = 16, GT = 256;
-// k-major LDS rows of GM + 16 doubles: the four k rows a fragment read touches
-// fall on alternate halves of the 64 banks (2 passes per read, the minimum)
+// the register-staged kernel: 128 x 128 tiles, k-major LDS rows of 128 + 16
+// doubles: the four k rows a fragment read touches fall on alternate halves of
+// the 64 banks (2 passes per read, the minimum)
+constexpr int GM = 128, GN = 128;
 constexpr int LDS_PAD = 16;
 enum { EPI_F64 = 0, EPI_SUB = 1 };  // EPI_SUB: C -= A B (the B transform's updates)
 
@@ -36,10 +36,12 @@ __device__ __forceinline__ void ld8d(const double* __restrict__ p, double* v) {
   }
 }
 
-// C = alpha op(A) op(B) + beta C (EPI_F64), or C -= op(A) op(B) (EPI_SUB).
-// Each k-stage is loaded into registers while the MFMAs of the previous stage run.
+// C = alpha op(A) op(B) + beta C (EPI_F64), or C -= op(A) op(B) (EPI_SUB), for
+// operands of any stride and alignment: each k-stage is loaded into registers
+// while the MFMAs of the previous stage run.  Aligned operands take
+// dgemm_kernel below.
 template <bool TA, bool TB, int EPI>
-__global__ void __launch_bounds__(GT, 2) dgemm_kernel(GemmF64 g) {
+__global__ void __launch_bounds__(GT, 2) dgemm_any_kernel(GemmF64 g) {
   __shared__ double As[GK][GM + LDS_PAD];
   __shared__ double Bs[GK][GN + LDS_PAD];
   const int MB = (g.M + GM - 1) / GM, NB = (g.N + GN - 1) / GN;
@@ -169,22 +171,127 @@ __global__ void __launch_bounds__(GT, 2) dgemm_kernel(GemmF64 g) {
       }
 }
 
+// ---- the same for operands whose rows are 16-byte aligned (gemm_dma.h) ----------
+extern __shared__ __attribute__((aligned(1024))) double gemm_lds[];
+
+// Four waves in a 2 x 2 grid of (TM / 2) x (TN / 2) sub-tiles.
+template <bool TA, bool TB, int EPI, int TM, int TN>
+__global__ void __launch_bounds__(GT, 2) dgemm_kernel(GemmF64 g) {
+  constexpr int FA = TM / 32, FB = TN / 32;  // 16-row and 16-column fragments of a wave
+  const int MB = (g.M + TM - 1) / TM, NB = (g.N + TN - 1) / TN;
+  const int t = xcd_tile(blockIdx.x, MB * NB);
+  const int m0 = (t % MB) * TM, n0 = (t / MB) * TN;
+  if (g.lowerC && n0 > m0 + TM - 1) return;
+  const int z = blockIdx.z;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (w & 1) * (TM / 2), wn = (w >> 1) * (TN / 2);
+  const int li = lane & 15, lk = lane >> 4;
+  int kmax = g.K;
+  if (g.lowerA && m0 + TM < kmax) kmax = m0 + TM;
+  DmaOp<!TA, TM> a;
+  DmaOp<TB, TN> b;
+  a.init(g.A + z * g.sA, g.lda, m0, g.M, kmax, w, lane);
+  b.init(g.B + z * g.sB, g.ldb, n0, g.N, kmax, w, lane);
+
+  v4d acc[FA][FB];
+  dma_gemm<!TA, TB, TM, TN>(a, b, kmax, gemm_lds, wm, wn, true, acc);
+
+  // acc[i][j][r] is C[wm + 16 i + 4 r + lk][wn + 16 j + li]; C is read a
+  // fragment row at a time, all loads before the stores that they might alias
+  double* __restrict__ C = g.C + z * g.sC;
+  const bool readc = EPI == EPI_SUB || g.beta != 0.0;
+#pragma unroll
+  for (int i = 0; i < FA; ++i) {
+    double c[FB][4];
+    const int mb = m0 + wm + i * 16 + lk, nb = n0 + wn + li;
+    double* __restrict__ cp = C + (int64_t)mb * g.ldc + nb;
+    if (readc) {
+#pragma unroll
+      for (int j = 0; j < FB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          c[j][r] = (mb + 4 * r < g.M && nb + 16 * j < g.N) ? cp[(int64_t)(4 * r) * g.ldc + 16 * j] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < FB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (mb + 4 * r >= g.M || nb + 16 * j >= g.N) continue;
+        double v;
+        if (EPI == EPI_SUB) {
+          v = c[j][r] - acc[i][j][r];
+        } else {
+          v = g.alpha * acc[i][j][r];
+          if (g.beta != 0.0) v = fma(g.beta, c[j][r], v);
+        }
+        cp[(int64_t)(4 * r) * g.ldc + 16 * j] = v;
+      }
+  }
+}
+
+// Tile of an M x N product over K: the one with the least time on the busiest
+// CU.  In cycles: a stage is (TM / 32)(TN / 32) 4 MFMAs of 64 cycles per wave,
+// slower when a CU has one workgroup only, and a workgroup costs some 6000 more
+// to fill its pipeline and to store its tile.
+struct GemmTile {
+  int tm, tn;
+};
+static GemmTile gemm_tile(int M, int N, int K, int batch) {
+  GemmTile best{128, 128};
+  double tbest = 0.0;
+  for (int tm = 128; tm >= 64; tm -= 64)
+    for (int tn = 128; tn >= 64; tn -= 64) {
+      const int64_t wgs = (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * std::max(1, batch);
+      const int64_t per_cu = (wgs + 255) / 256;
+      const double mf = (tm / 32) * (tn / 32) * 4 * 64.0;
+      const double stage = per_cu == 1 ? mf / 0.85 + 700.0 : mf / 0.85 + 100.0;
+      const double t = (double)per_cu * (((K + GK - 1) / GK) * stage + 3000.0 + (per_cu == 1 ? 3000.0 : 0.0) + mf);
+      if (tbest == 0.0 || t < tbest) {
+        best = GemmTile{tm, tn};
+        tbest = t;
+      }
+    }
+  return best;
+}
+
 static int gemm_tiles(int M, int N) { return ((M + GM - 1) / GM) * ((N + GN - 1) / GN); }
+
+// rows of both operands 16-byte aligned (the lanes' offsets fit 32 bits)
+static bool gemm_aligned(const GemmF64& g) {
+  auto ok = [](const double* p, int64_t ld, int64_t s) {
+    return !(reinterpret_cast<uintptr_t>(p) & 15) && ld % 2 == 0 && s % 2 == 0 && ld < (1 << 25);
+  };
+  return ok(g.A, g.lda, g.batch > 1 ? g.sA : 0) && ok(g.B, g.ldb, g.batch > 1 ? g.sB : 0);
+}
+
+template <bool TA, bool TB, int EPI>
+static void gemm_launch(const GemmF64& g, hipStream_t st) {
+  const int nz = g.batch > 0 ? g.batch : 1;
+  if (!gemm_aligned(g)) {
+    hipLaunchKernelGGL((dgemm_any_kernel<TA, TB, EPI>), dim3(gemm_tiles(g.M, g.N), 1, nz), dim3(GT), 0, st, g);
+    return;
+  }
+  const GemmTile t = gemm_tile(g.M, g.N, g.K, nz);
+  const dim3 grid(((g.M + t.tm - 1) / t.tm) * ((g.N + t.tn - 1) / t.tn), 1, nz);
+  const unsigned lds = 2 * (t.tm + t.tn) * GK * sizeof(double);
+  if (t.tm == 128 && t.tn == 128)
+    hipLaunchKernelGGL((dgemm_kernel<TA, TB, EPI, 128, 128>), grid, dim3(GT), lds, st, g);
+  else if (t.tm == 128)
+    hipLaunchKernelGGL((dgemm_kernel<TA, TB, EPI, 128, 64>), grid, dim3(GT), lds, st, g);
+  else if (t.tn == 128)
+    hipLaunchKernelGGL((dgemm_kernel<TA, TB, EPI, 64, 128>), grid, dim3(GT), lds, st, g);
+  else
+    hipLaunchKernelGGL((dgemm_kernel<TA, TB, EPI, 64, 64>), grid, dim3(GT), lds, st, g);
+}
 
 void dgemm(const GemmF64& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0) return;
-  const dim3 grid(gemm_tiles(g.M, g.N), 1, g.batch > 0 ? g.batch : 1);
   GemmF64 a = g;
-  if (g.K <= 0) {  // C = beta C
-    a.K = 0;
-  }
-#define L(TA_, TB_) \
-  hipLaunchKernelGGL((dgemm_kernel<TA_, TB_, EPI_F64>), grid, dim3(GT), 0, st, a)
-  if (!g.ta && !g.tb) L(false, false);
-  else if (!g.ta && g.tb) L(false, true);
-  else if (g.ta && !g.tb) L(true, false);
-  else L(true, true);
-#undef L
+  if (g.K <= 0) a.K = 0;  // C = beta C
+  if (!g.ta && !g.tb) gemm_launch<false, false, EPI_F64>(a, st);
+  else if (!g.ta && g.tb) gemm_launch<false, true, EPI_F64>(a, st);
+  else if (g.ta && !g.tb) gemm_launch<true, false, EPI_F64>(a, st);
+  else gemm_launch<true, true, EPI_F64>(a, st);
 }
 
 // C = alpha sum_s W_s + beta C, partials W_s [M][N] contiguous, summed in order
@@ -214,23 +321,14 @@ void dgemm_sk(const GemmF64& g, double* work, int64_t work_elems, hipStream_t st
   a.alpha = 1.0;
   a.beta = 0.0;
   a.batch = 1;
-  auto launch = [&](const GemmF64& x, int nz) {
-    const dim3 grid(tiles, 1, nz);
-#define L(TA_, TB_) \
-  hipLaunchKernelGGL((dgemm_kernel<TA_, TB_, EPI_F64>), grid, dim3(GT), 0, st, x)
-    if (!x.ta && !x.tb) L(false, false);
-    else if (!x.ta && x.tb) L(false, true);
-    else if (x.ta && !x.tb) L(true, false);
-    else L(true, true);
-#undef L
-  };
   if ((int64_t)klen * ns == g.K) {  // equal k-ranges: one batched launch
     a.K = klen;
     a.sA = g.ta ? (int64_t)klen * g.lda : klen;
     a.sB = g.tb ? klen : (int64_t)klen * g.ldb;
     a.sC = mn;
     a.C = work;
-    launch(a, ns);
+    a.batch = ns;
+    dgemm(a, st);
   } else {
     int z = 0;
     for (int k0 = 0; k0 < g.K; k0 += klen, ++z) {
@@ -239,7 +337,7 @@ void dgemm_sk(const GemmF64& g, double* work, int64_t work_elems, hipStream_t st
       a.B = g.tb ? g.B + k0 : g.B + (int64_t)k0 * g.ldb;
       a.C = work + z * mn;
       a.sA = a.sB = a.sC = 0;
-      launch(a, 1);
+      dgemm(a, st);
     }
     ns = z;
   }
@@ -249,7 +347,7 @@ void dgemm_sk(const GemmF64& g, double* work, int64_t work_elems, hipStream_t st
 
 // ---------------------------------------------------------------------------
 // B = L^-1 raw by blocked forward substitution, in place over raw (n x ncols,
-// row stride ncols).  Left-looking over blocks of TB = 128 rows: the block's
+// row stride ld).  Left-looking over blocks of TB = 128 rows: the block's
 // rows take R_i -= L_i,0:i B_0:i as one DGEMM (MFMA, the rows before it are
 // already B), then the 128 x 128 diagonal block is solved by substitution, in
 // two halves of 64 rows with the DGEMM R_2 -= L_21 B_1 between them.  Unlike a
@@ -420,7 +518,7 @@ __global__ void __launch_bounds__(TS_T) trsv64t_cols_kernel(const double* __rest
 // rows (coalesced), while the workgroup reads the few contiguous pair blocks of
 // B the tile draws on, with their reuse in one XCD's L2.
 constexpr int SPLIT_Q = 4;
-__global__ void __launch_bounds__(256) tile_split_kernel(const double* __restrict__ B, int64_t ncols, int nrows,
+__global__ void __launch_bounds__(256) tile_split_kernel(const double* __restrict__ B, int64_t ld, int nrows,
                                                          const int64_t* __restrict__ src, float* __restrict__ hi,
                                                          float* __restrict__ lo, int64_t ld_out) {
   const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
@@ -433,7 +531,7 @@ __global__ void __launch_bounds__(256) tile_split_kernel(const double* __restric
   for (int k = 0; k < SPLIT_Q; ++k)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      v[k][j] = (q0 + k < nrows && s[j] >= 0) ? B[(int64_t)(q0 + k) * ncols + s[j]] : 0.0;
+      v[k][j] = (q0 + k < nrows && s[j] >= 0) ? B[(int64_t)(q0 + k) * ld + s[j]] : 0.0;
 #pragma unroll
   for (int k = 0; k < SPLIT_Q; ++k) {
     if (q0 + k >= nrows) break;
@@ -481,57 +579,57 @@ static void trsv64t_cols(const double* L, int64_t ldl, int nr, double* X, int64_
 
 // C -= A^T X over all columns: A stored K x M (lda), the transposed blocks of L
 static void trsm_update_t(const double* A, int64_t lda, int M, int K, const double* Bsrc, double* C, int64_t ncols,
-                          hipStream_t st) {
+                          int64_t ld, hipStream_t st) {
   const int64_t slab = (int64_t)GN * 65536;
   for (int64_t c0 = 0; c0 < ncols; c0 += slab) {
     GemmF64 g{};
     g.M = M; g.N = (int)std::min<int64_t>(slab, ncols - c0); g.K = K;
     g.A = A; g.lda = lda; g.ta = true;
-    g.B = Bsrc + c0; g.ldb = ncols;
-    g.C = C + c0; g.ldc = ncols;
+    g.B = Bsrc + c0; g.ldb = ld;
+    g.C = C + c0; g.ldc = ld;
     g.alpha = -1.0; g.beta = 1.0; g.batch = 1;
-    hipLaunchKernelGGL((dgemm_kernel<true, false, EPI_SUB>), dim3(gemm_tiles(g.M, g.N)), dim3(GT), 0, st, g);
+    gemm_launch<true, false, EPI_SUB>(g, st);
   }
 }
 
-void trsm_solve_t(const double* L, int n, double* X, int64_t ncols, hipStream_t st) {
+void trsm_solve_t(const double* L, int n, double* X, int64_t ncols, int64_t ld, hipStream_t st) {
   if (ncols <= 0 || n <= 0) return;
   constexpr int TB = 2 * TS_R;
   const int nb = (n + TB - 1) / TB;
   for (int bi = nb - 1; bi >= 0; --bi) {
     const int r0 = bi * TB, rb = std::min(TB, n - r0), r1 = r0 + rb;
     // rows r0.. of the block: R -= (L_k,block)^T X_k over the solved rows k >= r1
-    if (r1 < n) trsm_update_t(L + (int64_t)r1 * n + r0, n, rb, n - r1, X + (int64_t)r1 * ncols,
-                              X + (int64_t)r0 * ncols, ncols, st);
+    if (r1 < n) trsm_update_t(L + (int64_t)r1 * n + r0, n, rb, n - r1, X + (int64_t)r1 * ld,
+                              X + (int64_t)r0 * ld, ncols, ld, st);
     const int h1 = std::min(TS_R, rb);
     if (rb > TS_R) {  // lower half of the block first, then the upper one
       const int rm = r0 + TS_R;
-      trsv64t_cols(L + (int64_t)rm * n + rm, n, rb - TS_R, X + (int64_t)rm * ncols, ncols, ncols, st);
-      trsm_update_t(L + (int64_t)rm * n + r0, n, TS_R, rb - TS_R, X + (int64_t)rm * ncols, X + (int64_t)r0 * ncols,
-                    ncols, st);
+      trsv64t_cols(L + (int64_t)rm * n + rm, n, rb - TS_R, X + (int64_t)rm * ld, ld, ncols, st);
+      trsm_update_t(L + (int64_t)rm * n + r0, n, TS_R, rb - TS_R, X + (int64_t)rm * ld, X + (int64_t)r0 * ld,
+                    ncols, ld, st);
     }
-    trsv64t_cols(L + (int64_t)r0 * n + r0, n, h1, X + (int64_t)r0 * ncols, ncols, ncols, st);
+    trsv64t_cols(L + (int64_t)r0 * n + r0, n, h1, X + (int64_t)r0 * ld, ld, ncols, st);
   }
 }
 
 static double trsm_update(const double* A, int64_t lda, int M, int K, const double* Bsrc, double* C, int64_t ncols,
-                          hipStream_t st) {
+                          int64_t ld, hipStream_t st) {
   const int64_t slab = (int64_t)GN * 65536;
   for (int64_t c0 = 0; c0 < ncols; c0 += slab) {
     GemmF64 g{};
     g.M = M; g.N = (int)std::min<int64_t>(slab, ncols - c0); g.K = K;
     g.A = A; g.lda = lda;
-    g.B = Bsrc + c0; g.ldb = ncols;
-    g.C = C + c0; g.ldc = ncols;
+    g.B = Bsrc + c0; g.ldb = ld;
+    g.C = C + c0; g.ldc = ld;
     g.alpha = -1.0; g.beta = 1.0; g.batch = 1;
-    hipLaunchKernelGGL((dgemm_kernel<false, false, EPI_SUB>), dim3(gemm_tiles(g.M, g.N)), dim3(GT), 0, st, g);
+    gemm_launch<false, false, EPI_SUB>(g, st);
   }
   return 2.0 * M * (double)K * (double)ncols;
 }
 
 size_t trsm_work_elems(int n) { return (size_t)(n / TS_R) * TS_R * TS_R; }
 
-TrsmStats trsm_solve(const double* L, int n, double* raw, int64_t ncols, double* work, hipStream_t st,
+TrsmStats trsm_solve(const double* L, int n, double* raw, int64_t ncols, int64_t ld, double* work, hipStream_t st,
                      TrsmTimer* timer) {
   TrsmStats z{};
   if (ncols <= 0) return z;
@@ -544,33 +642,33 @@ TrsmStats trsm_solve(const double* L, int n, double* raw, int64_t ncols, double*
     const int rb = std::min(TB, n - r0);
     if (r0 > 0) {
       if (timer) timer->begin();
-      z.update_flops += trsm_update(L + (int64_t)r0 * n, n, rb, r0, raw, raw + (int64_t)r0 * ncols, ncols, st);
+      z.update_flops += trsm_update(L + (int64_t)r0 * n, n, rb, r0, raw, raw + (int64_t)r0 * ld, ncols, ld, st);
       if (timer) timer->end();
       ++z.update_launches;
     }
     const int h1 = std::min(TS_R, rb);
-    trsv64_cols(L + (int64_t)r0 * n + r0, n, h1, raw + (int64_t)r0 * ncols, ncols, ncols, st, packed(r0));
+    trsv64_cols(L + (int64_t)r0 * n + r0, n, h1, raw + (int64_t)r0 * ld, ld, ncols, st, packed(r0));
     if (rb > TS_R) {
       const int r1 = r0 + TS_R;
       if (timer) timer->begin();
-      z.update_flops += trsm_update(L + (int64_t)r1 * n + r0, n, rb - TS_R, TS_R, raw + (int64_t)r0 * ncols,
-                                    raw + (int64_t)r1 * ncols, ncols, st);
+      z.update_flops += trsm_update(L + (int64_t)r1 * n + r0, n, rb - TS_R, TS_R, raw + (int64_t)r0 * ld,
+                                    raw + (int64_t)r1 * ld, ncols, ld, st);
       if (timer) timer->end();
       ++z.update_launches;
-      trsv64_cols(L + (int64_t)r1 * n + r1, n, rb - TS_R, raw + (int64_t)r1 * ncols, ncols, ncols, st, packed(r1));
+      trsv64_cols(L + (int64_t)r1 * n + r1, n, rb - TS_R, raw + (int64_t)r1 * ld, ld, ncols, st, packed(r1));
     }
   }
   return z;
 }
 
-void tile_split(const double* B, int n, int64_t ncols, const int64_t* src, float* hi, float* lo, int64_t ld_out,
+void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* hi, float* lo, int64_t ld_out,
                 hipStream_t st) {
   if (n <= 0 || ld_out <= 0) return;
   if (ld_out % 1024) throw Error(-1, "tile_split: the tiled row length must be whole 32 x 32 tiles");
   for (int q0 = 0; q0 < n; q0 += 65535 * SPLIT_Q) {
     const int nq = std::min(65535 * SPLIT_Q, n - q0);
     const dim3 g((unsigned)(ld_out / 1024), (unsigned)((nq + SPLIT_Q - 1) / SPLIT_Q));
-    hipLaunchKernelGGL(tile_split_kernel, g, dim3(256), 0, st, B + (int64_t)q0 * ncols, ncols, nq, src,
+    hipLaunchKernelGGL(tile_split_kernel, g, dim3(256), 0, st, B + (int64_t)q0 * ld, ld, nq, src,
                        hi + (int64_t)q0 * ld_out, lo + (int64_t)q0 * ld_out, ld_out);
   }
 }
