@@ -674,70 +674,104 @@ void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* h
 }
 
 // ---------------------------------------------------------------------------
-// Cholesky of one diagonal block (nb <= 64) in LDS, plus its lower-triangular
-// inverse.  A non-positive pivot records its global index + 1 in *info.
+// Cholesky of one diagonal block (kb <= 64), plus its lower-triangular inverse.
+// A non-positive pivot records its global index + 1 in *info.  One workgroup and
+// a serial chain of 64 square roots and divisions: latency is all that counts.
+// In panels of 8 columns, one wave factors a panel with a row per lane in
+// registers (no barrier, the pivots by lane reads), then four waves update the
+// columns to its right in LDS; the inverse takes 8 rows at a time, four threads
+// per column for the sums over the rows above, one for the 8 x 8 triangle.
+// Every element takes the same operations in the same order as when each column
+// updated all later ones in LDS with a thread per row, 168 us a block; so 45.
 constexpr int CB = 64;
-__global__ void __launch_bounds__(64) potrf_diag_kernel(double* J, int n, int k0, int kb,
-                                                        double* Linv, int64_t ldx, int* info,
-                                                        const double* __restrict__ diag0) {
+constexpr int CP = 8;  // panel
+__global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k0, int kb,
+                                                         double* Linv, int64_t ldx, int* info,
+                                                         const double* __restrict__ diag0) {
   __shared__ double a[CB][CB + 1];
   __shared__ double x[CB][CB + 1];
-  const int t = threadIdx.x;
-  for (int i = 0; i < kb; ++i)
-    if (t < kb) a[i][t] = (t <= i) ? J[(int64_t)(k0 + i) * n + k0 + t] : 0.0;
+  __shared__ double sum[CP][CB + 1];
+  const int tid = threadIdx.x;
+  double* __restrict__ Jb = J + (int64_t)k0 * n + k0;
+  // rows and columns past kb: the identity
+  for (int e = tid; e < CB * CB; e += 256) {
+    const int i = e / CB, c = e % CB;
+    a[i][c] = (i < kb && c <= i) ? Jb[(int64_t)i * n + c] : (i == c ? 1.0 : 0.0);
+  }
   __syncthreads();
-  for (int j = 0; j < kb; ++j) {
-    if (t == 0) {
-      // a pivot that lost all but rounding noise of the original diagonal
-      // counts as non-positive: the metric is not numerically positive definite
-      const double d = a[j][j];
-      if (!(d > 1e-14 * diag0[k0 + j])) {
-        if (*info == 0) *info = k0 + j + 1;
-        a[j][j] = __builtin_nan("");
-      } else {
-        a[j][j] = sqrt(d);
+  for (int p = 0; p < CB; p += CP) {
+    if (tid < CB) {
+      const int t = tid;
+      double v[CP];
+#pragma unroll
+      for (int c = 0; c < CP; ++c) v[c] = a[t][p + c];
+#pragma unroll
+      for (int j = 0; j < CP; ++j) {
+        const double d = __shfl(v[j], p + j);
+        // a pivot that lost all but rounding noise of the original diagonal
+        // counts as non-positive: the metric is not numerically positive definite
+        double piv = 1.0;
+        if (p + j < kb) {
+          if (!(d > 1e-14 * diag0[k0 + p + j])) {
+            if (t == 0 && *info == 0) *info = k0 + p + j + 1;
+            piv = __builtin_nan("");
+          } else {
+            piv = sqrt(d);
+          }
+        }
+        v[j] = t == p + j ? piv : (t > p + j ? v[j] / piv : 0.0);
+#pragma unroll
+        for (int c = j + 1; c < CP; ++c) v[c] = fma(-v[j], __shfl(v[j], p + c), v[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < CP; ++c)
+        if (t >= p + c) a[t][p + c] = v[c];
+    }
+    __syncthreads();
+    // columns right of the panel: a_ic -= sum_j l_ij l_cj, j in order
+    const int r0 = p + CP, m = CB - r0;
+    for (int e = tid; e < m * m; e += 256) {
+      const int i = r0 + e / m, c = r0 + e % m;
+      if (c > i) continue;
+      double v = a[i][c];
+#pragma unroll
+      for (int j = 0; j < CP; ++j) v = fma(-a[i][p + j], a[c][p + j], v);
+      a[i][c] = v;
+    }
+    __syncthreads();
+  }
+  // inverse, X[i][c] = -(sum_{k=c}^{i-1} L[i][k] X[k][c]) / L[i][i], X[c][c] = 1 / L[c][c]
+  const int c = tid & 63, q = tid >> 6;
+  for (int g = 0; g < CB; g += CP) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < g; ++k) {
+      const double xk = x[k][c];
+      s0 = fma(a[g + 2 * q][k], xk, s0);
+      s1 = fma(a[g + 2 * q + 1][k], xk, s1);
+    }
+    sum[2 * q][c] = s0;
+    sum[2 * q + 1][c] = s1;
+    __syncthreads();
+    if (q == 0) {
+      double xg[CP];
+#pragma unroll
+      for (int r = 0; r < CP; ++r) {
+        double s = sum[r][c];
+#pragma unroll
+        for (int k = 0; k < r; ++k) s = fma(a[g + r][g + k], xg[k], s);
+        xg[r] = c > g + r ? 0.0 : (c == g + r ? 1.0 : -s) / a[g + r][g + r];
+        x[g + r][c] = xg[r];
       }
     }
     __syncthreads();
-    if (t > j && t < kb) a[t][j] /= a[j][j];
-    __syncthreads();
-    if (t > j && t < kb)
-      for (int c = j + 1; c <= t; ++c) a[t][c] -= a[t][j] * a[c][j];
-    __syncthreads();
   }
-  // inverse, one column per thread: X[c][c] = 1/L[c][c],
-  // X[i][c] = -(sum_{k=c}^{i-1} L[i][k] X[k][c]) / L[i][i]
-  if (t < kb) {
-    const int c = t;
-    for (int i = 0; i < kb; ++i) x[i][c] = 0.0;
-    x[c][c] = 1.0 / a[c][c];
-    for (int i = c + 1; i < kb; ++i) {
-      double s = 0.0;
-      for (int k = c; k < i; ++k) s += a[i][k] * x[k][c];
-      x[i][c] = -s / a[i][i];
-    }
+  for (int e = tid; e < kb * CB; e += 256) {
+    const int i = e / CB, k = e % CB;
+    if (k >= kb) continue;
+    Jb[(int64_t)i * n + k] = k <= i ? a[i][k] : 0.0;
+    Linv[(int64_t)i * ldx + k] = x[i][k];
   }
-  __syncthreads();
-  for (int i = 0; i < kb; ++i)
-    if (t < kb) {
-      J[(int64_t)(k0 + i) * n + k0 + t] = (t <= i) ? a[i][t] : 0.0;
-      Linv[(int64_t)i * ldx + t] = x[i][t];
-    }
-}
-
-__global__ void copy2d_kernel(const double* src, int64_t lds, double* dst, int64_t ldd, int rows,
-                              int cols) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)rows * cols) return;
-  const int r = (int)(idx / cols), c = (int)(idx % cols);
-  dst[r * ldd + c] = src[r * lds + c];
-}
-static void copy2d(const double* src, int64_t lds, double* dst, int64_t ldd, int rows, int cols,
-                   hipStream_t st) {
-  const int64_t n = (int64_t)rows * cols;
-  if (n <= 0) return;
-  hipLaunchKernelGGL(copy2d_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, lds, dst,
-                     ldd, rows, cols);
 }
 
 __global__ void fill_kernel(double* p, size_t n, double v) {
@@ -762,8 +796,8 @@ __global__ void diag_kernel(const double* A, int n, double* d) {
 
 // J (n x n, lower part used) -> L in place (upper zeroed), Linv = L^-1.
 // work: at least n * (CB + 1) doubles.
-// work: the panel (n x CB), the original diagonal (n), and the split-K partial
-// products of the inverse's block rows (8 x CB x n)
+// work: a block row of the inverse (n x CB), the original diagonal (n), and the
+// split-K partial products of the inverse's block rows (8 x CB x n)
 size_t cholesky_work_elems(int n) { return (size_t)n * (CB + 1) + std::max((size_t)8 * CB * n, (size_t)CB * CB); }
 
 // J = L L^T in place; with Linv, the inverses of the diagonal blocks go there
@@ -777,7 +811,7 @@ static void cholesky_factor_impl(double* J, int n, double* Linv, double* work, i
     const int kb = std::min(CB, n - k0);
     double* X = Linv ? Linv + (int64_t)k0 * n + k0 : xblk;
     const int64_t ldx = Linv ? n : CB;
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(64), 0, st, J, n, k0, kb, X, ldx, info, diag0);
+    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, J, n, k0, kb, X, ldx, info, diag0);
     const int r0 = k0 + kb, rows = n - r0;
     if (rows <= 0) break;
     // panel: L21 = A21 inv(L11)^T
@@ -785,15 +819,15 @@ static void cholesky_factor_impl(double* J, int n, double* Linv, double* work, i
     g.M = rows; g.N = kb; g.K = kb;
     g.A = J + (int64_t)r0 * n + k0; g.lda = n;
     g.B = X; g.ldb = ldx; g.tb = true;
-    g.C = work; g.ldc = kb;
+    // in place: one workgroup holds a row's 64 columns, all read before it stores
+    g.C = J + (int64_t)r0 * n + k0; g.ldc = n;
     g.alpha = 1.0; g.beta = 0.0; g.batch = 1;
     dgemm(g, st);
-    copy2d(work, kb, J + (int64_t)r0 * n + k0, n, rows, kb, st);
     // trailing update of the lower triangle: A22 -= L21 L21^T
     GemmF64 u{};
     u.M = rows; u.N = rows; u.K = kb;
-    u.A = work; u.lda = kb;
-    u.B = work; u.ldb = kb; u.tb = true;
+    u.A = J + (int64_t)r0 * n + k0; u.lda = n;
+    u.B = u.A; u.ldb = n; u.tb = true;
     u.C = J + (int64_t)r0 * n + r0; u.ldc = n;
     u.alpha = -1.0; u.beta = 1.0; u.batch = 1; u.lowerC = true;
     dgemm(u, st);
