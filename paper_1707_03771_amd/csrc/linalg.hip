@@ -794,6 +794,10 @@ __global__ void diag_kernel(const double* A, int n, double* d) {
   if (i < n) d[i] = A[(int64_t)i * n + i];
 }
 
+void diag_f64(const double* A, int n, double* d, hipStream_t st) {
+  hipLaunchKernelGGL(diag_kernel, dim3((n + 255) / 256), dim3(256), 0, st, A, n, d);
+}
+
 // J (n x n, lower part used) -> L in place (upper zeroed), Linv = L^-1.
 // work: at least n * (CB + 1) doubles.
 // work: a block row of the inverse (n x CB), the original diagonal (n), and the
