@@ -661,42 +661,235 @@ static bool diis_solve(const std::vector<double>& Bm, int m, std::vector<double>
   return true;
 }
 
-// K(D) = K(C+) - K(C-) with D = V diag(lambda) V^T, C+- = V_+- sqrt(|lambda_+-|);
-// eigenvalues below 1e-14 max|lambda| are dropped.  Columns go to k_build in
-// chunks of at most 512.  Synchronous.
+// ---- D = L L^T by Cholesky with diagonal pivoting (N. J. Higham, "Accuracy and
+// Stability of Numerical Algorithms", 2nd ed., sec. 10.3), left-looking, one
+// launch per column.  L's columns are rows of Lc [r][n]; res the residual
+// diagonal, -1 at chosen pivots; pm / pi the largest residual and its row in
+// each workgroup, double-buffered over the steps.  state[0] the columns so far,
+// state[1] whether the largest residual has fallen to tol (later launches then
+// do nothing).  A workgroup takes 64 rows, its four waves every fourth of the
+// earlier columns; each finds the pivot from pm / pi itself.
+constexpr int PC_R = 64;
+__global__ void __launch_bounds__(64) pchol_init_kernel(const double* __restrict__ D, int n, double* __restrict__ res,
+                                                        double* __restrict__ pm, int* __restrict__ pi,
+                                                        int* __restrict__ state) {
+  const int i = blockIdx.x * PC_R + threadIdx.x;
+  double m = -1.0;
+  int at = 0x7fffffff;
+  if (i < n) {
+    m = D[(int64_t)i * n + i];
+    at = i;
+    res[i] = m;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double m2 = __shfl_xor(m, o);
+    const int a2 = __shfl_xor(at, o);
+    if (m2 > m || (m2 == m && a2 < at)) {
+      m = m2;
+      at = a2;
+    }
+  }
+  if (threadIdx.x == 0) {
+    pm[blockIdx.x] = m;
+    pi[blockIdx.x] = at;
+    if (blockIdx.x == 0) state[0] = state[1] = 0;
+  }
+}
+
+__global__ void __launch_bounds__(256) pchol_step_kernel(const double* __restrict__ D, int n, int k, double rel_tol,
+                                                         double* __restrict__ Lc, double* __restrict__ res,
+                                                         double* __restrict__ pm, int* __restrict__ pi,
+                                                         int* __restrict__ state, double* __restrict__ dmax0) {
+  __shared__ double part[4][PC_R];
+  __shared__ double lp[256];
+  __shared__ double s_m;
+  __shared__ int s_p, s_done;
+  const int nb = gridDim.x, tid = threadIdx.x, r = tid & 63, g = tid >> 6;
+  const double* __restrict__ pm0 = pm + (k & 1) * nb;
+  const int* __restrict__ pi0 = pi + (k & 1) * nb;
+  if (tid < 64) {
+    double m = -1.0;
+    int at = 0x7fffffff;
+    for (int b = tid; b < nb; b += 64)
+      if (pm0[b] > m || (pm0[b] == m && pi0[b] < at)) {
+        m = pm0[b];
+        at = pi0[b];
+      }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double m2 = __shfl_xor(m, o);
+      const int a2 = __shfl_xor(at, o);
+      if (m2 > m || (m2 == m && a2 < at)) {
+        m = m2;
+        at = a2;
+      }
+    }
+    if (tid == 0) {
+      // the first pivot is the scale of the tolerance
+      const double top = k == 0 ? m : dmax0[0];
+      if (k == 0 && blockIdx.x == 0) dmax0[0] = m;
+      s_m = m;
+      s_p = at;
+      s_done = state[1] != 0 || !(m > rel_tol * top) || at >= n;
+    }
+  }
+  __syncthreads();
+  if (s_done) {
+    // every workgroup sees the same pm: none steps past this point
+    if (blockIdx.x == 0 && tid == 0) state[1] = 1;
+    return;
+  }
+  const int p = s_p, i = blockIdx.x * PC_R + r;
+  double s = 0.0;
+  for (int j0 = 0; j0 < k; j0 += 256) {
+    const int nj = min(256, k - j0);
+    __syncthreads();
+    if (tid < nj) lp[tid] = Lc[(int64_t)(j0 + tid) * n + p];
+    __syncthreads();
+    if (i < n) {
+#pragma unroll 8
+      for (int j = g; j < nj; j += 4) s = fma(Lc[(int64_t)(j0 + j) * n + i], lp[j], s);
+    }
+  }
+  part[g][r] = s;
+  __syncthreads();
+  if (g != 0) return;
+  double m = -1.0;
+  int at = 0x7fffffff;
+  if (i < n) {
+    const double piv = sqrt(s_m);
+    const double d = D[(int64_t)p * n + i] - ((part[0][r] + part[1][r]) + (part[2][r] + part[3][r]));
+    const double ri = res[i];
+    double l = ri < 0.0 ? 0.0 : d / piv;  // rows chosen before have nothing left
+    double left = ri < 0.0 ? -1.0 : fmax(ri - l * l, 0.0);
+    if (i == p) {
+      l = piv;
+      left = -1.0;
+    }
+    Lc[(int64_t)k * n + i] = l;
+    res[i] = left;
+    m = left;
+    at = i;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double m2 = __shfl_xor(m, o);
+    const int a2 = __shfl_xor(at, o);
+    if (m2 > m || (m2 == m && a2 < at)) {
+      m = m2;
+      at = a2;
+    }
+  }
+  if (r == 0) {
+    pm[((k + 1) & 1) * nb + blockIdx.x] = m;
+    pi[((k + 1) & 1) * nb + blockIdx.x] = at;
+    if (blockIdx.x == 0) state[0] = k + 1;
+  }
+}
+
+// C[mu][j] = Lc[c0 + j][mu]
+__global__ void pchol_cols_kernel(const double* __restrict__ Lc, int n, int c0, int r, double* __restrict__ C) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= (int64_t)n * r) return;
+  const int mu = (int)(e / r), j = (int)(e % r);
+  C[e] = Lc[(int64_t)(c0 + j) * n + mu];
+}
+
+constexpr int KD_CH = 512;  // columns per K build
+
+// K(D) for a symmetric density D.  A density of occupied orbitals is positive
+// semidefinite of low rank: its pivoted Cholesky factor L gives D = L L^T in as
+// many small launches as D has rank (C10H22, 250 functions, rank 41: 0.3 ms,
+// where the block Jacobi eigensolver takes 27 ms), and K = K(L).  The factor is
+// taken only if max |D - L L^T| <= 1e-14 max |D|, the threshold of the other route;
+// any other D (indefinite, unsymmetric, not finite) goes by its signed
+// eigen-factorisation: K(C+) - K(C-) with D = V diag(lambda) V^T, C+- = V_+-
+// sqrt(|lambda_+-|), eigenvalues below 1e-14 max|lambda| dropped.  Columns go to
+// k_build in chunks of at most 512.  Synchronous.
 void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st) {
   const int n = a.nbf;
   const int64_t n2 = (int64_t)n * n;
   Scf S;
   S.st = st;
-  DevMem W(8 * n2), lam(8 * (size_t)n);
-  DFX_HIP(hipMemcpyAsync(W.p, D, 8 * n2, hipMemcpyDeviceToDevice, st));
-  S.syevd(W.as<double>(), n, lam.as<double>());
-  std::vector<double> l(n);
-  DFX_HIP(hipMemcpyAsync(l.data(), lam.p, 8 * (size_t)n, hipMemcpyDeviceToHost, st));
-  DFX_HIP(hipStreamSynchronize(st));
-  double lmax = 0.0;
-  for (double x : l) lmax = std::max(lmax, std::fabs(x));
-  std::vector<int> pos, neg;
-  for (int k = 0; k < n; ++k) {
-    if (l[k] > 1e-14 * lmax) pos.push_back(k);
-    else if (l[k] < -1e-14 * lmax) neg.push_back(k);
+  DevMem W(8 * n2), lam(8 * (size_t)n), Kt(8 * n2);
+  DevMem idx_d(sizeof(int) * KD_CH), sc_d(8 * KD_CH);
+  const int nb = (n + PC_R - 1) / PC_R;
+  int rank = -1;
+  {
+    // pm, dmax0 and the reduction's 512 partial sums; pi and state
+    DevMem pd(8 * (size_t)(2 * nb + 1 + 512)), pn(sizeof(int) * (size_t)(2 * nb + 2));
+    double *pm = pd.as<double>(), *dmax0 = pm + 2 * nb, *part = dmax0 + 1;
+    int *pi = pn.as<int>(), *state = pi + 2 * nb;
+    hipLaunchKernelGGL(pchol_init_kernel, dim3(nb), dim3(64), 0, st, D, n, lam.as<double>(), pm, pi, state);
+    int h[2] = {0, 0};
+    for (int k = 0; k < n && !h[1];) {
+      const int stop = std::min(n, k + 32);
+      for (; k < stop; ++k)
+        hipLaunchKernelGGL(pchol_step_kernel, dim3(nb), dim3(256), 0, st, D, n, k, 1e-15, W.as<double>(),
+                           lam.as<double>(), pm, pi, state, dmax0);
+      DFX_HIP(hipMemcpyAsync(h, state, sizeof h, hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+    }
+    // the residual D - L L^T against max |D|; |D|^2 shows whether D is finite (the
+    // maximum passes over NaN)
+    std::vector<double> hp(512);
+    auto partials = [&]() {
+      DFX_HIP(hipMemcpyAsync(hp.data(), part, 8 * 512, hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+    };
+    auto maxabs = [&](const double* A) {
+      hipLaunchKernelGGL(maxabs_partial_kernel, dim3(512), dim3(256), 0, st, A, n2, part);
+      partials();
+      return *std::max_element(hp.begin(), hp.end());
+    };
+    hipLaunchKernelGGL(dot_partial_kernel, dim3(512), dim3(256), 0, st, D, D, (const double*)nullptr, n2, part);
+    partials();
+    double norm2 = 0.0;
+    for (double x : hp) norm2 += x;
+    DFX_HIP(hipMemcpyAsync(Kt.p, D, 8 * n2, hipMemcpyDeviceToDevice, st));
+    if (h[0] > 0) S.gemm(n, n, h[0], W.as<double>(), n, true, W.as<double>(), n, false, Kt.as<double>(), n, -1.0, 1.0);
+    if (std::isfinite(norm2) && maxabs(Kt.as<double>()) <= 1e-14 * maxabs(D)) rank = h[0];
   }
-  constexpr int CH = 512;
-  DevMem Cs(8 * (size_t)n * CH), Kt(8 * n2), idx_d(sizeof(int) * CH), sc_d(8 * CH);
-  DevMem work(k_work_bytes(a, std::min(CH, std::max(1, (int)std::max(pos.size(), neg.size())))));
-  fill_f64(K, (size_t)n2, 0.0, st);
+  std::vector<int> pos, neg;
+  std::vector<double> l;
+  if (rank < 0) {
+    DFX_HIP(hipMemcpyAsync(W.p, D, 8 * n2, hipMemcpyDeviceToDevice, st));
+    S.syevd(W.as<double>(), n, lam.as<double>());
+    l.resize(n);
+    DFX_HIP(hipMemcpyAsync(l.data(), lam.p, 8 * (size_t)n, hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    double lmax = 0.0;
+    for (double x : l) lmax = std::max(lmax, std::fabs(x));
+    for (int k = 0; k < n; ++k) {
+      if (l[k] > 1e-14 * lmax) pos.push_back(k);
+      else if (l[k] < -1e-14 * lmax) neg.push_back(k);
+    }
+  } else {
+    pos.resize(rank);
+  }
+  DevMem Cs(8 * (size_t)n * KD_CH);
+  DevMem work(k_work_bytes(a, std::min(KD_CH, std::max(1, (int)std::max(pos.size(), neg.size())))));
+  const bool one = neg.empty() && !pos.empty() && pos.size() <= (size_t)KD_CH;  // K is a single build
+  if (!one) fill_f64(K, (size_t)n2, 0.0, st);
   for (int sign = 1; sign >= -1; sign -= 2) {
     const std::vector<int>& sel = sign > 0 ? pos : neg;
-    for (size_t c0 = 0; c0 < sel.size(); c0 += CH) {
-      const int r = (int)std::min<size_t>(CH, sel.size() - c0);
-      std::vector<int> id(sel.begin() + c0, sel.begin() + c0 + r);
-      std::vector<double> sc(r);
-      for (int j = 0; j < r; ++j) sc[j] = std::sqrt(std::fabs(l[id[j]]));
-      DFX_HIP(hipMemcpyAsync(idx_d.p, id.data(), sizeof(int) * r, hipMemcpyHostToDevice, st));
-      DFX_HIP(hipMemcpyAsync(sc_d.p, sc.data(), 8 * (size_t)r, hipMemcpyHostToDevice, st));
-      hipLaunchKernelGGL(gather_evec_kernel, dim3(nblk((int64_t)n * r)), dim3(256), 0, st, W.as<double>(), n,
-                         idx_d.as<int>(), sc_d.as<double>(), r, Cs.as<double>());
+    for (size_t c0 = 0; c0 < sel.size(); c0 += KD_CH) {
+      const int r = (int)std::min<size_t>(KD_CH, sel.size() - c0);
+      if (rank >= 0) {
+        hipLaunchKernelGGL(pchol_cols_kernel, dim3(nblk((int64_t)n * r)), dim3(256), 0, st, W.as<double>(), n,
+                           (int)c0, r, Cs.as<double>());
+      } else {
+        std::vector<int> id(sel.begin() + c0, sel.begin() + c0 + r);
+        std::vector<double> sc(r);
+        for (int j = 0; j < r; ++j) sc[j] = std::sqrt(std::fabs(l[id[j]]));
+        DFX_HIP(hipMemcpyAsync(idx_d.p, id.data(), sizeof(int) * r, hipMemcpyHostToDevice, st));
+        DFX_HIP(hipMemcpyAsync(sc_d.p, sc.data(), 8 * (size_t)r, hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(gather_evec_kernel, dim3(nblk((int64_t)n * r)), dim3(256), 0, st, W.as<double>(), n,
+                           idx_d.as<int>(), sc_d.as<double>(), r, Cs.as<double>());
+        DFX_HIP(hipStreamSynchronize(st));  // the host vectors go out of scope
+      }
+      if (one) {
+        k_build(a, Cs.as<double>(), r, K, work.p, st);
+        continue;
+      }
       k_build(a, Cs.as<double>(), r, Kt.as<double>(), work.p, st);
       Comb cb{};
       cb.m = 2;
@@ -705,9 +898,9 @@ void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st)
       cb.F[1] = Kt.as<double>();
       cb.c[1] = (double)sign;
       hipLaunchKernelGGL(lincomb_kernel, dim3(nblk(n2)), dim3(256), 0, st, cb, K, n2);
-      DFX_HIP(hipStreamSynchronize(st));  // host vectors of this chunk go out of scope
     }
   }
+  DFX_HIP(hipStreamSynchronize(st));  // the scratch goes out of scope
 }
 
 // The arena over opts.workspace (null without one).  The size is checked

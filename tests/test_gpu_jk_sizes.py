@@ -1,0 +1,109 @@
+"""J and K at the sizes where their tiles, slices and column blocks end, and K of a
+density by every route, against plain FP64 products of the dense rows of B
+(dfx_B_unpack), which the parity tests tie to the oracle.
+
+Tolerances: J and K are sums of at most naux nbf^2 and naux nocc nbf products in
+FP64, in another order than the reference's; each element then differs by at
+most about its count of terms times the unit roundoff times the sum of their
+absolute values, which for these random densities stays far below 1e-11 of the
+largest element.  The eigen-factorised route drops eigenvalues below 1e-14 of the
+largest and multiplies rounded eigenvectors: 1e-10.
+"""
+import numpy as np
+import pytest
+
+import systems
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dfx():
+    import paper_1707_03771_amd as m
+    return m
+
+
+def _line(nfun):
+    """A system of exactly nfun orbital functions along a line long enough for
+    distant pairs to be screened (whole tiles of B without a kept pair)."""
+    sh, ax = [], []
+    n = k = 0
+    while n < nfun:
+        l = 1 if nfun - n >= 3 and k % 3 == 1 else 0
+        c = [0.9 * k, 0.1 * (k % 2), 0.0]
+        sh.append(systems.shell(c, l, [0.9 + 0.01 * k]))
+        if k % 4 == 0:
+            ax.append(systems.shell(c, k % 3, [0.8]))
+        n += 2 * l + 1
+        k += 1
+    return sh, ax
+
+
+def _fit(dfx, nfun):
+    sh, ax = _line(nfun)
+    B = dfx.eri3(sh, ax)
+    assert B.nbf == nfun
+    return B, B.unpack()
+
+
+def _reference(rows, C):
+    D = C @ C.T
+    J = torch.tensordot((rows * D).sum((1, 2)), rows, dims=1)
+    X = torch.matmul(rows, C).permute(1, 0, 2).reshape(rows.shape[1], -1)
+    return J, X @ X.T
+
+
+@pytest.mark.parametrize("nfun", [1, 31, 33, 64, 65, 129, 200])
+def test_fock_matrices_at_the_edges(dfx, nfun):
+    B, rows = _fit(dfx, nfun)
+    g = torch.Generator().manual_seed(nfun)
+    for nocc in sorted({n for n in (1, 15, 16, 17, 48, 64, 65, 128, 129, 160, 161, nfun) if n <= nfun}):
+        C = torch.randn((nfun, nocc), generator=g, dtype=torch.float64).cuda()
+        J, K = dfx.jk(B, C)
+        Jr, Kr = _reference(rows, C)
+        assert (J - Jr).abs().max() <= 1e-11 * Jr.abs().max(), nocc
+        assert (K - Kr).abs().max() <= 1e-11 * Kr.abs().max(), nocc
+        assert torch.equal(K, K.T) and torch.equal(J, J.T)
+    B.free()
+
+
+def test_screened_tiles_are_skipped_and_zero(dfx):
+    B, rows = _fit(dfx, 200)
+    nt = (200 + 31) // 32
+    kept = [(i, j) for i in range(nt) for j in range(i + 1)
+            if rows[:, 32 * i:32 * i + 32, 32 * j:32 * j + 32].abs().max() > 0]
+    assert len(kept) < nt * (nt + 1) // 2  # the case is there
+    J, _ = dfx.jk(B, torch.ones((200, 1), dtype=torch.float64, device="cuda"), want_k=False)
+    for i in range(nt):
+        for j in range(i):
+            if (i, j) not in kept:
+                assert J[32 * i:32 * i + 32, 32 * j:32 * j + 32].abs().max() == 0.0
+    B.free()
+
+
+@pytest.mark.parametrize("kind", ["projector", "weighted", "full", "zero", "indefinite", "nearly"])
+def test_k_from_density(dfx, kind):
+    n = 70
+    B, rows = _fit(dfx, n)
+    g = torch.Generator().manual_seed(5)
+    Q = torch.linalg.qr(torch.randn((n, n), generator=g, dtype=torch.float64))[0].cuda()
+    w = torch.zeros(n, dtype=torch.float64)
+    if kind == "projector":
+        w[:13] = 1.0
+    elif kind == "weighted":
+        w[:40] = torch.logspace(0, -6, 40, dtype=torch.float64)
+    elif kind == "full":
+        w[:] = torch.linspace(0.1, 2.0, n, dtype=torch.float64)
+    elif kind == "indefinite":
+        w[:20] = torch.linspace(-1.0, 1.0, 20, dtype=torch.float64)
+    elif kind == "nearly":  # one small negative eigenvalue: the factor must not be taken
+        w[:10] = 1.0
+        w[10] = -1e-7
+    D = (Q * w.cuda()) @ Q.T
+    D = (D + D.T) / 2
+    K = dfx.jk(B, D, kind=dfx.DENSITY, want_j=False)[1]
+    ref = torch.matmul(torch.matmul(rows, D), rows).sum(0)
+    assert (K - ref).abs().max() <= 1e-10 * max(1.0, ref.abs().max().item())
+    B.free()
