@@ -9,14 +9,14 @@
 // blocks.  A sweep runs nb - 1 rounds; a round pairs the blocks into nb / 2
 // disjoint pairs by the circle method.  Per round:
 //   1. ej_pair_kernel: per pair (a, b), one workgroup loads the 64 x 64
-//      principal submatrix of blocks a and b into LDS and runs one cyclic
-//      Jacobi sweep over it (63 rounds of 32 disjoint rotations, each
-//      rotation zeroing its element exactly; a round updates S by 2 x 2
-//      blocks, one thread per block, so rows and columns need no barrier in
-//      between), accumulating the orthogonal U with U^T S U the reduced
-//      submatrix.  S goes back in place, U to a buffer.  One local sweep per
-//      visit converges in as many outer sweeps as solving the pair problem
-//      to the end (measured in a CPU model of the scheme).
+//      principal submatrix of blocks a and b into LDS and rotates every element
+//      of its off-diagonal block once (32 rounds of 32 disjoint rotations, each
+//      rotation zeroing its element exactly; a round updates S by 2 x 2 blocks,
+//      one thread per block, so rows and columns need no barrier in between),
+//      accumulating the orthogonal U with U^T S U the reduced submatrix.  In the
+//      first round of a sweep the elements inside both blocks are rotated first
+//      (31 rounds), so that a sweep meets every element once.  S goes back in
+//      place, U to a buffer.
 //   2. ej_apply_kernel: the off-diagonal 64 x 64 blocks between pairs,
 //      A_IJ <- U_I^T A_IJ U_J (one workgroup per block I > J, writing both
 //      A_IJ and A_JI), and the eigenvector columns V_:I <- V_:I U_I.
@@ -29,6 +29,7 @@
 // diagonal is a_pp - t a_pq and a_qq + t a_pq (Golub & Van Loan, Alg. 8.5.1).
 #include <algorithm>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "host.h"
@@ -45,18 +46,35 @@ constexpr double EJ_TOL = 1e-15;
 
 __device__ __forceinline__ int ej_g(int i, int2 ab) { return i < EJB ? ab.x * EJB + i : ab.y * EJB + (i - EJB); }
 
-// circle method on the 64 local indices: round r in [0, 63), pair k in [0, 32)
-__device__ __forceinline__ void ej_local_pair(int r, int k, int& p, int& q) {
-  int a, b;
-  if (k == 0) {
-    a = r;
-    b = EJP - 1;
-  } else {
-    a = (r + k) % (EJP - 1);
-    b = (r - k + (EJP - 1)) % (EJP - 1);
+// Round r of a visit, rotation k in [0, 32), as local indices p < q.  cross: p in
+// the first block, q in the second, r in [0, 32).  Otherwise inside the blocks,
+// 16 rotations each by the circle method on 32 indices, r in [0, 31).
+__device__ __forceinline__ void ej_local_pair(bool cross, int r, int k, int& p, int& q) {
+  if (cross) {
+    p = k;
+    q = EJB + ((k + r) & (EJB - 1));
+    return;
   }
-  p = a < b ? a : b;
-  q = a < b ? b : a;
+  const int blk = k & EJB / 2 ? EJB : 0, j = k & (EJB / 2 - 1);
+  int a = r + j, b = r - j + (EJB - 1);
+  if (a >= EJB - 1) a -= EJB - 1;
+  if (b >= EJB - 1) b -= EJB - 1;
+  if (j == 0) b = EJB - 1;
+  p = blk + (a < b ? a : b);
+  q = blk + (a < b ? b : a);
+}
+
+// 1 / sqrt(x) and 1 / x for x in [1e-280, 1e280]: the hardware's estimates and
+// two Newton steps, half the latency of the library's
+__device__ __forceinline__ double ej_rsqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+__device__ __forceinline__ double ej_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
 }
 
 // Aw = (A + A^T) / 2 zero-padded to N x N, V = I
@@ -69,127 +87,163 @@ __global__ void ej_init_kernel(const double* __restrict__ A, int n, int N, doubl
   V[e] = i == j ? 1.0 : 0.0;
 }
 
-__global__ void __launch_bounds__(EJT) ej_pair_kernel(double* __restrict__ A, int N, const int2* __restrict__ pr,
-                                                      double* __restrict__ Ub, int* __restrict__ nrot,
-                                                      int* __restrict__ moved) {
+// What bounds it: the chain of one round after the other, so the work is arranged
+// by latency.  Wave 0 forms a round's rotations (three divisions, a square root
+// and an inverse square root, one rotation per lane) while the other seven apply
+// the round before to U; then all eight update S.  A round moves S and U through
+// LDS once, 128 KB, which is about half of its time.  Four waves doing one after
+// the other, 63 rounds a visit: 150 us; the 32 rounds of a visit now 45 (105 with
+// the rounds inside the blocks).  A visit that finds nothing to rotate ends at once.
+constexpr int EJPT = 512;
+__global__ void __launch_bounds__(EJPT) ej_pair_kernel(double* __restrict__ A, int N, const int2* __restrict__ pr,
+                                                       int inside, double* __restrict__ Ub, int* __restrict__ nrot,
+                                                       int* __restrict__ moved) {
   __shared__ double S[EJP][EJP + 1];
   __shared__ double Ut[EJP][EJP + 1];  // Ut[r][k] = U[k][r]: its rows rotate like those of S
-  __shared__ double cs_c[EJP / 2], cs_s[EJP / 2], d_p[EJP / 2], d_q[EJP / 2];
-  __shared__ unsigned char lp[EJP - 1][EJP / 2], lq[EJP - 1][EJP / 2];  // the local pairs of every round
-  __shared__ int any;
+  // rotations of a round, two buffers: U lags S by one round
+  __shared__ double cs_c[2][EJP / 2], cs_s[2][EJP / 2], d_p[EJP / 2], d_q[EJP / 2];
+  __shared__ int any, todo;
   const int2 ab = pr[blockIdx.x];
   const int t = threadIdx.x;
-  for (int e = t; e < EJP * EJP; e += EJT) {
+  if (t == 0) any = todo = 0;
+#pragma unroll
+  for (int e = t; e < EJP * EJP; e += EJPT) {
     const int i = e / EJP, j = e % EJP;
     S[i][j] = A[(int64_t)ej_g(i, ab) * N + ej_g(j, ab)];
     Ut[i][j] = i == j ? 1.0 : 0.0;
   }
-  for (int e = t; e < (EJP - 1) * (EJP / 2); e += EJT) {
-    int p, q;
-    ej_local_pair(e / (EJP / 2), e % (EJP / 2), p, q);
-    lp[e / (EJP / 2)][e % (EJP / 2)] = (unsigned char)p;
-    lq[e / (EJP / 2)][e % (EJP / 2)] = (unsigned char)q;
-  }
-  if (t == 0) any = 0;
   __syncthreads();
-  for (int r = 0; r < EJP - 1; ++r) {
-    // the rotation of local pair t, and its rotated diagonal
-    if (t < EJP / 2) {
-      const int p = lp[r][t], q = lq[r][t];
-      const double apq = S[p][q], app = S[p][p], aqq = S[q][q];
-      double c = 1.0, s = 0.0, dp = app, dq = aqq;
-      if (apq != 0.0 && fabs(apq) > EJ_TOL * sqrt(fabs(app * aqq))) {
-        const double th = (aqq - app) / (2.0 * apq);
-        double tt = 1.0 / (fabs(th) + sqrt(1.0 + th * th));
-        if (th < 0.0) tt = -tt;
-        c = 1.0 / sqrt(1.0 + tt * tt);
-        s = tt * c;
-        dp = app - tt * apq;
-        dq = aqq + tt * apq;
-        any = 1;  // every writer stores the same value
+  bool some = false;
+#pragma unroll
+  for (int e = t; e < EJP * EJP; e += EJPT) {
+    const int i = e / EJP, j = e % EJP;
+    if (i >= j || (!inside && (i >= EJB || j < EJB))) continue;
+    const double x = S[i][j];
+    some |= x != 0.0 && !(fabs(x) <= EJ_TOL * sqrt(fabs(S[i][i] * S[j][j])));
+  }
+  if (some) todo = 1;  // every writer stores the same value
+  __syncthreads();
+  if (!todo) {  // U is the identity (its partner's block may still need it)
+    for (int e = t; e < EJP * EJP; e += EJPT) Ub[(int64_t)blockIdx.x * EJP * EJP + e] = Ut[e / EJP][e % EJP];
+    if (t == 0) moved[blockIdx.x] = 0;
+    return;
+  }
+  // rotations of round r into buffer b
+  auto rotations = [&](bool cross, int r, int b) {
+    if (t >= EJP / 2) return;
+    int p, q;
+    ej_local_pair(cross, r, t, p, q);
+    const double apq = S[p][q], app = S[p][p], aqq = S[q][q];
+    double c = 1.0, s = 0.0, dp = app, dq = aqq;
+    if (apq != 0.0 && fabs(apq) > EJ_TOL * sqrt(fabs(app * aqq))) {
+      double tt;
+      const double big = fabs(apq) > 1e-250 ? (aqq - app) * ej_rcp(2.0 * apq) : (aqq - app) / (2.0 * apq);
+      const double th = fabs(big);
+      if (th < 1e130) {
+        const double w = fma(th, th, 1.0);
+        tt = ej_rcp(th + w * ej_rsqrt(w));
+      } else {  // also where it overflowed
+        tt = 0.5 / th;
       }
-      cs_c[t] = c;
-      cs_s[t] = s;
-      d_p[t] = dp;
-      d_q[t] = dq;
+      if (big < 0.0) tt = -tt;
+      c = ej_rsqrt(fma(tt, tt, 1.0));
+      s = tt * c;
+      dp = app - tt * apq;
+      dq = aqq + tt * apq;
+      any = 1;
     }
-    __syncthreads();
-    // S <- J^T S J as 2 x 2 blocks (rows p_k, q_k) x (columns p_k2, q_k2): every
-    // element is read and written by one thread, so rows and columns need no
-    // barrier between them; the diagonal blocks take the exact rotated values.
-    // Thread t takes the column pair k2 = t % 32 and the row pairs t / 32 + 8 m,
-    // and issues all its loads before its stores.
-    {
-      const int k2 = t % (EJP / 2);
-      const double c2 = cs_c[k2], s2 = cs_s[k2];
-      const int p2 = lp[r][k2], q2 = lq[r][k2];
-      int pk[4], qk[4];
-      double ck[4], sk[4], x[4][4];
+    cs_c[b][t] = c;
+    cs_s[b][t] = s;
+    d_p[t] = dp;
+    d_q[t] = dq;
+  };
+  // rows p, q of U^T for the rotations in buffer b, by the waves from w0 on: a
+  // wave takes every (8 - w0)th rotation, a lane a column; all loads first
+  auto rotate_u = [&](bool cross, int r, int b, auto w0c) {
+    constexpr int W0 = decltype(w0c)::value, NW = EJPT / 64 - W0, NK = (EJP / 2 + NW - 1) / NW;
+    const int w = (t >> 6) - W0, j = t & 63;
+    double c[NK], s[NK], u[NK], v[NK];
+    int pk[NK], qk[NK];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int k = t / (EJP / 2) + 8 * m;
-        pk[m] = lp[r][k];
-        qk[m] = lq[r][k];
-        ck[m] = cs_c[k];
-        sk[m] = cs_s[k];
-      }
+    for (int m = 0; m < NK; ++m) {
+      const int k = min(w + NW * m, EJP / 2 - 1);
+      ej_local_pair(cross, r, k, pk[m], qk[m]);
+      c[m] = cs_c[b][k];
+      s[m] = cs_s[b][k];
+      u[m] = Ut[pk[m]][j];
+      v[m] = Ut[qk[m]][j];
+    }
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        x[m][0] = S[pk[m]][p2];
-        x[m][1] = S[pk[m]][q2];
-        x[m][2] = S[qk[m]][p2];
-        x[m][3] = S[qk[m]][q2];
-      }
+    for (int m = 0; m < NK; ++m) {
+      if (w + NW * m >= EJP / 2 || s[m] == 0.0) continue;
+      Ut[pk[m]][j] = c[m] * u[m] - s[m] * v[m];
+      Ut[qk[m]][j] = s[m] * u[m] + c[m] * v[m];
+    }
+  };
+  // S <- J^T S J as 2 x 2 blocks (rows p_k, q_k) x (columns p_k2, q_k2): every
+  // element is read and written by one thread, so rows and columns need no
+  // barrier between them; the diagonal blocks take the exact rotated values.
+  // Thread t takes the column pair k2 = t % 32 and the row pairs t / 32 + 16 m,
+  // and issues all its loads before its stores.
+  auto rotate_s = [&](bool cross, int r, int b) {
+    const int k2 = t % (EJP / 2);
+    const double c2 = cs_c[b][k2], s2 = cs_s[b][k2];
+    int p2, q2;
+    ej_local_pair(cross, r, k2, p2, q2);
+    int pk[2], qk[2];
+    double ck[2], sk[2], x[2][4];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int k = t / (EJP / 2) + 8 * m;
-        const int p = pk[m], q = qk[m];
-        if (k == k2) {
-          if (s2 != 0.0) {
-            S[p][p] = d_p[k];
-            S[q][q] = d_q[k];
-            S[p][q] = 0.0;
-            S[q][p] = 0.0;
-          }
-          continue;
+    for (int m = 0; m < 2; ++m) {
+      const int k = t / (EJP / 2) + 16 * m;
+      ej_local_pair(cross, r, k, pk[m], qk[m]);
+      ck[m] = cs_c[b][k];
+      sk[m] = cs_s[b][k];
+      x[m][0] = S[pk[m]][p2];
+      x[m][1] = S[pk[m]][q2];
+      x[m][2] = S[qk[m]][p2];
+      x[m][3] = S[qk[m]][q2];
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int k = t / (EJP / 2) + 16 * m;
+      const int p = pk[m], q = qk[m];
+      if (k == k2) {
+        if (s2 != 0.0) {
+          S[p][p] = d_p[k];
+          S[q][q] = d_q[k];
+          S[p][q] = 0.0;
+          S[q][p] = 0.0;
         }
-        const double c1 = ck[m], s1 = sk[m];
-        if (s1 == 0.0 && s2 == 0.0) continue;
-        // rows: J_k^T x, then columns: y J_k2
-        const double ypp = c1 * x[m][0] - s1 * x[m][2], ypq = c1 * x[m][1] - s1 * x[m][3];
-        const double yqp = s1 * x[m][0] + c1 * x[m][2], yqq = s1 * x[m][1] + c1 * x[m][3];
-        S[p][p2] = c2 * ypp - s2 * ypq;
-        S[p][q2] = s2 * ypp + c2 * ypq;
-        S[q][p2] = c2 * yqp - s2 * yqq;
-        S[q][q2] = s2 * yqp + c2 * yqq;
+        continue;
       }
+      const double c1 = ck[m], s1 = sk[m];
+      if (s1 == 0.0 && s2 == 0.0) continue;
+      // rows: J_k^T x, then columns: y J_k2
+      const double ypp = c1 * x[m][0] - s1 * x[m][2], ypq = c1 * x[m][1] - s1 * x[m][3];
+      const double yqp = s1 * x[m][0] + c1 * x[m][2], yqq = s1 * x[m][1] + c1 * x[m][3];
+      S[p][p2] = c2 * ypp - s2 * ypq;
+      S[p][q2] = s2 * ypp + c2 * ypq;
+      S[q][p2] = c2 * yqp - s2 * yqq;
+      S[q][q2] = s2 * yqp + c2 * yqq;
     }
-    // rows p, q of U^T: thread t takes column j = t % 64 of the pairs t / 64 + 4 m
-    {
-      const int j = t % EJP;
-      int pk[8], qk[8];
-      double u[8], v[8];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const int k = t / EJP + 4 * m;
-        pk[m] = lp[r][k];
-        qk[m] = lq[r][k];
-        u[m] = Ut[pk[m]][j];
-        v[m] = Ut[qk[m]][j];
-      }
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const int k = t / EJP + 4 * m;
-        const double s = cs_s[k];
-        if (s == 0.0) continue;
-        const double c = cs_c[k];
-        Ut[pk[m]][j] = c * u[m] - s * v[m];
-        Ut[qk[m]][j] = s * u[m] + c * v[m];
-      }
-    }
+  };
+  const int first = inside ? EJB - 1 : 0;  // rounds inside the blocks come first
+  const int rounds = first + EJB;
+  for (int n = 0; n < rounds; ++n) {
+    const bool cross = n >= first;
+    const int r = cross ? n - first : n;
+    if (t < 64)
+      rotations(cross, r, n & 1);
+    else if (n > 0)
+      rotate_u(n - 1 >= first, n - 1 >= first ? n - 1 - first : n - 1, (n - 1) & 1,
+               std::integral_constant<int, 1>{});
+    __syncthreads();
+    rotate_s(cross, r, n & 1);
     __syncthreads();
   }
-  for (int e = t; e < EJP * EJP; e += EJT) {
+  rotate_u(true, EJB - 1, (rounds - 1) & 1, std::integral_constant<int, 0>{});
+  __syncthreads();
+  for (int e = t; e < EJP * EJP; e += EJPT) {
     const int i = e / EJP, j = e % EJP;
     A[(int64_t)ej_g(i, ab) * N + ej_g(j, ab)] = S[i][j];
     Ub[(int64_t)blockIdx.x * EJP * EJP + e] = Ut[j][i];  // U[i][j]
@@ -200,17 +254,42 @@ __global__ void __launch_bounds__(EJT) ej_pair_kernel(double* __restrict__ A, in
   }
 }
 
+// C = A^T B of two 64 x 64 matrices in LDS, k the row index of both, on
+// v_mfma_f64_16x16x4f64: wave w has the 32 x 32 quadrant (w & 1, w >> 1);
+// acc[i][j][r] is C[32 (w & 1) + 16 i + 4 r + lk][32 (w >> 1) + 16 j + li]
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void ej_atb(const double (&A)[EJP][EJP + 1], const double (&B)[EJP][EJP + 1],
+                                       v4d (&acc)[2][2]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const int m0 = (w & 1) * 32 + li, n0 = (w >> 1) * 32 + li;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int k = lk; k < EJP; k += 4) {
+    const double a0 = A[k][m0], a1 = A[k][m0 + 16], b0 = B[k][n0], b1 = B[k][n0 + 16];
+    acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+  }
+}
+
 // blockIdx.x < ntri: off-diagonal block (I, J), I > J, of the pairs, A_IJ <- U_I^T A_IJ U_J
 // (and A_JI its transpose); else the eigenvector columns of pair I over 64 rows of V.
 // Pairs whose U is exactly the identity (moved[I] == 0) leave their blocks as they are.
+// On the matrix cores; with four results per thread on the vector units the two
+// products took 22 us a round at N = 448, this 13.
 __global__ void __launch_bounds__(EJT) ej_apply_kernel(double* __restrict__ A, double* __restrict__ V, int N,
                                                        const int2* __restrict__ pr, const double* __restrict__ Ub,
                                                        const int* __restrict__ moved, int np, int ntri) {
   __shared__ double X[EJP][EJP + 1];
   __shared__ double U[EJP][EJP + 1];
   const int t = threadIdx.x;
-  const int r0 = (t / 16) * 4, c0 = (t % 16) * 4;
-  double acc[4][4];
+  const int lane = t & 63, w = t >> 6, li = lane & 15, lk = lane >> 4;
+  const int m0 = (w & 1) * 32 + lk, n0 = (w >> 1) * 32 + li;
+  v4d acc[2][2];
   if ((int)blockIdx.x < ntri) {
     const int b = blockIdx.x;
     int I = (int)((sqrt(8.0 * b + 1.0) + 1.0) * 0.5);
@@ -219,60 +298,37 @@ __global__ void __launch_bounds__(EJT) ej_apply_kernel(double* __restrict__ A, d
     const int J = b - I * (I - 1) / 2;
     if (!moved[I] && !moved[J]) return;
     const int2 pI = pr[I], pJ = pr[J];
-    for (int e = t; e < EJP * EJP; e += EJT) {
-      const int i = e / EJP, j = e % EJP;
+    double uj[EJP * EJP / EJT];
+#pragma unroll
+    for (int e = 0; e < EJP * EJP / EJT; ++e) {
+      const int q = t + EJT * e, i = q / EJP, j = q % EJP;
       X[i][j] = A[(int64_t)ej_g(i, pI) * N + ej_g(j, pJ)];
-      U[i][j] = Ub[(int64_t)I * EJP * EJP + e];
+      U[i][j] = Ub[(int64_t)I * EJP * EJP + q];
+      uj[e] = Ub[(int64_t)J * EJP * EJP + q];
     }
     __syncthreads();
-    // T = U_I^T X: T[r][c] = sum_k U_I[k][r] X[k][c]
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int k = 0; k < EJP; ++k) {
-      double u[4], x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) u[i] = U[k][r0 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) x[j] = X[k][c0 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(u[i], x[j], acc[i][j]);
-    }
+    ej_atb(X, U, acc);  // T^T = X^T U_I
     __syncthreads();
-    // X <- T^T, U <- U_J
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int e = 0; e < EJP * EJP / EJT; ++e) U[(t + EJT * e) / EJP][(t + EJT * e) % EJP] = uj[e];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) X[c0 + j][r0 + i] = acc[i][j];
-    for (int e = t; e < EJP * EJP; e += EJT) U[e / EJP][e % EJP] = Ub[(int64_t)J * EJP * EJP + e];
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) X[m0 + 16 * i + 4 * r][n0 + 16 * j] = acc[i][j][r];
     __syncthreads();
-    // R = T U_J: R[r][c] = sum_k T^T[k][r] U_J[k][c]
+    ej_atb(X, U, acc);  // R = T U_J
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int k = 0; k < EJP; ++k) {
-      double u[4], x[4];
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = X[k][r0 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) u[j] = U[k][c0 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(x[i], u[j], acc[i][j]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int gr = ej_g(r0 + i, pI), gc = ej_g(c0 + j, pJ);
-        A[(int64_t)gr * N + gc] = acc[i][j];
-        A[(int64_t)gc * N + gr] = acc[i][j];
-      }
+        for (int r = 0; r < 4; ++r) {
+          const int gr = ej_g(m0 + 16 * i + 4 * r, pI), gc = ej_g(n0 + 16 * j, pJ);
+          A[(int64_t)gr * N + gc] = acc[i][j][r];
+          A[(int64_t)gc * N + gr] = acc[i][j][r];
+        }
     return;
   }
   // eigenvectors: rows [64 s, 64 s + 64) of V, columns of pair I: V_:I <- V_:I U_I
@@ -280,31 +336,21 @@ __global__ void __launch_bounds__(EJT) ej_apply_kernel(double* __restrict__ A, d
   const int I = b % np, strip = b / np;
   if (!moved[I]) return;
   const int2 pI = pr[I];
-  for (int e = t; e < EJP * EJP; e += EJT) {
-    const int i = e / EJP, k = e % EJP;
+#pragma unroll
+  for (int e = 0; e < EJP * EJP / EJT; ++e) {
+    const int q = t + EJT * e, i = q / EJP, k = q % EJP;
     X[k][i] = V[(int64_t)(strip * EJP + i) * N + ej_g(k, pI)];  // X[k][i] = V[row i][col k]
-    U[i][k] = Ub[(int64_t)I * EJP * EJP + e];
+    U[i][k] = Ub[(int64_t)I * EJP * EJP + q];
   }
   __syncthreads();
+  ej_atb(X, U, acc);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  for (int k = 0; k < EJP; ++k) {
-    double x[4], u[4];
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = X[k][r0 + i];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) u[j] = U[k][c0 + j];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = fma(x[i], u[j], acc[i][j]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) V[(int64_t)(strip * EJP + r0 + i) * N + ej_g(c0 + j, pI)] = acc[i][j];
+      for (int r = 0; r < 4; ++r)
+        V[(int64_t)(strip * EJP + m0 + 16 * i + 4 * r) * N + ej_g(n0 + 16 * j, pI)] = acc[i][j][r];
 }
 
 __global__ void ej_diag_kernel(const double* __restrict__ Aw, int N, int n, double* __restrict__ d) {
@@ -377,8 +423,8 @@ int sym_eig(double* A, int n, double* w, hipStream_t st) {
     DFX_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int), st));
     for (int r = 0; r < nb - 1; ++r) {
       const int2* pr = reinterpret_cast<const int2*>(prd.as<int>() + 2 * (size_t)r * np);
-      hipLaunchKernelGGL(ej_pair_kernel, dim3(np), dim3(EJT), 0, st, Aw.as<double>(), N, pr, Ub.as<double>(),
-                         cnt.as<int>(), mv.as<int>());
+      hipLaunchKernelGGL(ej_pair_kernel, dim3(np), dim3(EJPT), 0, st, Aw.as<double>(), N, pr, r == 0 ? 1 : 0,
+                         Ub.as<double>(), cnt.as<int>(), mv.as<int>());
       hipLaunchKernelGGL(ej_apply_kernel, dim3(ntri + nstrip * np), dim3(EJT), 0, st, Aw.as<double>(),
                          V.as<double>(), N, pr, Ub.as<double>(), mv.as<int>(), np, ntri);
     }
