@@ -4,11 +4,9 @@
 #pragma once
 #include <type_traits>
 
-#include "common.h"
+#include "gemm_small.h"
 
 namespace dfx {
-
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int GK = 16, GT = 256;  // k-width of a stage, threads of a workgroup
 

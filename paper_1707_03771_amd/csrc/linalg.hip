@@ -229,16 +229,51 @@ __global__ void __launch_bounds__(GT, 2) dgemm_kernel(GemmF64 g) {
   }
 }
 
+// ---- the same in tiles of 32 with the k-range over the waves (gemm_small.h) --------
+// For products that the tiles above leave most of the chip idle on, at any stride
+// and alignment.  192 x 192 x 192: 11.7 us in tiles of 64, 5.1 so; 394 x 394 x 394:
+// 20.5 and 7.1; 394 x 65 x 394 with odd strides: 76 (dgemm_any_kernel) and 7.
+// Every tile reads its 64 rows of A and B again, through L2: from some 700 rows on
+// the larger tiles win (1024 x 1024 x 1024: 44 and 62; 4096: 1970 and 2970).
+template <bool TA, bool TB>
+__global__ void __launch_bounds__(64 * SG_W) dgemm_small_kernel(GemmF64 g) {
+  __shared__ double red[SG_W * SG_T * SG_T];
+  const int MB = (g.M + SG_T - 1) / SG_T, NB = (g.N + SG_T - 1) / SG_T;
+  const int t = xcd_tile(blockIdx.x, MB * NB);
+  const int m0 = (t % MB) * SG_T, n0 = (t / MB) * SG_T;
+  if (g.lowerC && n0 > m0 + SG_T - 1) return;
+  const int z = blockIdx.z;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int kmax = g.K;
+  if (g.lowerA && m0 + SG_T < kmax) kmax = m0 + SG_T;
+  RegOp<!TA> a;
+  RegOp<TB> b;
+  a.init(g.A + z * g.sA, g.lda, m0, g.M, w, lane & 15, lane >> 4);
+  b.init(g.B + z * g.sB, g.ldb, n0, g.N, w, lane & 15, lane >> 4);
+  double v[2];
+  small_gemm<!TA, TB>(a, b, kmax, w, lane, red, v);
+  double* __restrict__ C = g.C + z * g.sC;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = threadIdx.x + 512 * h, m = m0 + sg_row(e), n = n0 + sg_col(e);
+    if (m >= g.M || n >= g.N) continue;
+    double* c = C + (int64_t)m * g.ldc + n;
+    double x = g.alpha * v[h];
+    if (g.beta != 0.0) x = fma(g.beta, *c, x);
+    *c = x;
+  }
+}
+
 // Tile of an M x N product over K: the one with the least time on the busiest
 // CU.  In cycles: a stage is (TM / 32)(TN / 32) 4 MFMAs of 64 cycles per wave,
 // slower when a CU has one workgroup only, and a workgroup costs some 6000 more
 // to fill its pipeline and to store its tile.
 struct GemmTile {
   int tm, tn;
+  double t;
 };
 static GemmTile gemm_tile(int M, int N, int K, int batch) {
-  GemmTile best{128, 128};
-  double tbest = 0.0;
+  GemmTile best{128, 128, 0.0};
   for (int tm = 128; tm >= 64; tm -= 64)
     for (int tn = 128; tn >= 64; tn -= 64) {
       const int64_t wgs = (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * std::max(1, batch);
@@ -246,12 +281,22 @@ static GemmTile gemm_tile(int M, int N, int K, int batch) {
       const double mf = (tm / 32) * (tn / 32) * 4 * 64.0;
       const double stage = per_cu == 1 ? mf / 0.85 + 700.0 : mf / 0.85 + 100.0;
       const double t = (double)per_cu * (((K + GK - 1) / GK) * stage + 3000.0 + (per_cu == 1 ? 3000.0 : 0.0) + mf);
-      if (tbest == 0.0 || t < tbest) {
-        best = GemmTile{tm, tn};
-        tbest = t;
-      }
+      if (best.t == 0.0 || t < best.t) best = GemmTile{tm, tn, t};
     }
   return best;
+}
+
+// Cycles of the same in tiles of 32 over the waves, 30 per k and workgroup where
+// the matrix cores need 16, and in the tiles of dgemm_any_kernel: both as measured
+// at 2.4 GHz over M, N = 32 .. 16384 and K = 40 .. 4096, to within 1.3.
+static double small_cycles(int M, int N, int K, int batch) {
+  const int64_t wgs = (int64_t)((M + SG_T - 1) / SG_T) * ((N + SG_T - 1) / SG_T) * std::max(1, batch);
+  return (double)((wgs + 255) / 256) * (4500.0 + K * 30.0) + 2000.0;
+}
+
+static double any_cycles(int M, int N, int K, int batch) {
+  const int64_t wgs = (int64_t)((M + GM - 1) / GM) * ((N + GN - 1) / GN) * std::max(1, batch);
+  return (double)((wgs + 255) / 256) * (K * 410.0 + 4000.0) + 4000.0;
 }
 
 static int gemm_tiles(int M, int N) { return ((M + GM - 1) / GM) * ((N + GN - 1) / GN); }
@@ -264,9 +309,25 @@ static bool gemm_aligned(const GemmF64& g) {
   return ok(g.A, g.lda, g.batch > 1 ? g.sA : 0) && ok(g.B, g.ldb, g.batch > 1 ? g.sB : 0);
 }
 
+// Tiles of 32 where they take less time than the other kernel that these strides
+// allow would, t cycles (and the lanes' byte offsets fit 32 bits).  Not for C in
+// place of A, the Cholesky panel: there one workgroup has to hold all columns.
+static double other_cycles(const GemmF64& g, int K, int batch) {
+  return gemm_aligned(g) ? gemm_tile(g.M, g.N, K, batch).t : any_cycles(g.M, g.N, K, batch);
+}
+static bool take_small(const GemmF64& g, double t) {
+  return g.C != g.A && g.lda < (1 << 23) && g.ldb < (1 << 23) && small_cycles(g.M, g.N, g.K, std::max(1, g.batch)) < t;
+}
+
 template <bool TA, bool TB, int EPI>
 static void gemm_launch(const GemmF64& g, hipStream_t st) {
   const int nz = g.batch > 0 ? g.batch : 1;
+  // the updates of a substitution keep one order of summation at every width
+  if (EPI == EPI_F64 && take_small(g, other_cycles(g, g.K, nz))) {
+    const unsigned tiles = (unsigned)(((g.M + SG_T - 1) / SG_T) * ((g.N + SG_T - 1) / SG_T));
+    hipLaunchKernelGGL((dgemm_small_kernel<TA, TB>), dim3(tiles, 1, nz), dim3(64 * SG_W), 0, st, g);
+    return;
+  }
   if (!gemm_aligned(g)) {
     hipLaunchKernelGGL((dgemm_any_kernel<TA, TB, EPI>), dim3(gemm_tiles(g.M, g.N), 1, nz), dim3(GT), 0, st, g);
     return;
@@ -311,7 +372,9 @@ void dgemm_sk(const GemmF64& g, double* work, int64_t work_elems, hipStream_t st
   const int64_t mn = (int64_t)g.M * g.N;
   int ns = 1;
   while (ns < 8 && tiles * ns < 512 && g.K / (2 * ns) >= 128 && 2 * ns * mn <= work_elems) ns *= 2;
-  if (ns == 1 || g.batch > 1 || g.lowerA || g.lowerC || !work) {
+  // in tiles of 32 the k-range is split as it is, without a second launch
+  if (ns == 1 || g.batch > 1 || g.lowerA || g.lowerC || !work ||
+      take_small(g, other_cycles(g, (g.K + ns - 1) / ns, ns) + 12000.0)) {
     dgemm(g, st);
     return;
   }
@@ -824,6 +887,7 @@ static void cholesky_factor_impl(double* J, int n, double* Linv, double* work, i
     g.A = J + (int64_t)r0 * n + k0; g.lda = n;
     g.B = X; g.ldb = ldx; g.tb = true;
     // in place: one workgroup holds a row's 64 columns, all read before it stores
+    // (dgemm never takes tiles of 32 for C = A)
     g.C = J + (int64_t)r0 * n + k0; g.ldc = n;
     g.alpha = 1.0; g.beta = 0.0; g.batch = 1;
     dgemm(g, st);

@@ -107,3 +107,18 @@ def test_k_from_density(dfx, kind):
     ref = torch.matmul(torch.matmul(rows, D), rows).sum(0)
     assert (K - ref).abs().max() <= 1e-10 * max(1.0, ref.abs().max().item())
     B.free()
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 71, 97, 130, 257, 394])
+def test_cholesky_product_edges(dfx, n):
+    """The products of a factorisation and its inverse at the edges of the tiles, odd row
+    strides included.  A = G G^T / n + I has a condition below 6, so both residuals stay
+    within some n units of rounding."""
+    dev = torch.device("cuda:0")
+    g = torch.randn(n, n, dtype=torch.float64, generator=torch.Generator().manual_seed(n)).to(dev)
+    A = g @ g.T / n + torch.eye(n, dtype=torch.float64, device=dev)
+    L, Li = dfx.cholesky(A.clone())
+    L, Li = torch.tril(L), torch.tril(Li)
+    tol = 8 * (n + 8) * 2.0 ** -53
+    assert float((L @ L.T - A).abs().max()) <= tol * float(A.abs().max())
+    assert float((Li @ L - torch.eye(n, dtype=torch.float64, device=dev)).abs().max()) <= tol * 6.0
