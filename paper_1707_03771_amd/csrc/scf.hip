@@ -24,6 +24,7 @@
 #include <cstring>
 #include <map>
 
+#include "gemm_small.h"
 #include "host.h"
 
 namespace dfx {
@@ -246,6 +247,147 @@ __global__ void trace2_kernel(const double* __restrict__ P, const double* __rest
   }
 }
 
+// ---- one step of the purification in one launch ----------------------------------
+// P (m x m, exactly symmetric) is stepped by workgroups of one 32 x 32 tile of its
+// lower triangle each: the tile of P^2 (gemm_small.h), the decision between P^2
+// and 2 P - P^2, and the tile of the new P, stored with its mirror image.  The
+// decision needs tr P and tr P^2 = sum P_ij^2, of which every workgroup of the
+// step before left its share in part; each adds the shares up in the same order.
+// The state (steps done, settled steps, done, ok) goes from launch to launch on
+// the device, so that no step waits for the host; launches after the last step
+// end at once.
+// What bounds it: launches and the latency of one tile's loads.  With the product,
+// the sum of its slices, the traces, their copy to the host and the raise of every
+// step apart, purification and Cholesky QR took 38.9 us a step at m = 192 and 58.0 at
+// 394; so 15.7 and 29.0.
+struct Tc2State {
+  int steps, settled, done, ok;
+};
+
+__device__ __forceinline__ void tc2_tile(int bid, int& ti, int& tj) {
+  ti = (int)((sqrt(8.0 * bid + 1.0) - 1.0) * 0.5);
+  while ((ti + 1) * (ti + 2) / 2 <= bid) ++ti;
+  while (ti * (ti + 1) / 2 > bid) --ti;
+  tj = bid - ti * (ti + 1) / 2;
+}
+
+// the tile's elements v of thread t (e = t, t + 512) to P, to the mirror image, and
+// the workgroup's share of (tr P, sum P_ij^2) to part.  red: 32 x 33 + 16 doubles.
+__device__ __forceinline__ void tc2_store(const double (&v)[2], int ti, int tj, int m, double* __restrict__ P,
+                                          double* __restrict__ part, double* red) {
+  const int m0 = ti * SG_T, n0 = tj * SG_T;
+  double tr = 0.0, fr = 0.0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = threadIdx.x + 512 * h, r = sg_row(e), c = sg_col(e);
+    red[r * 33 + c] = v[h];
+    if (m0 + r < m && n0 + c < m) {
+      P[(int64_t)(m0 + r) * m + n0 + c] = v[h];
+      fr = fma(v[h], v[h], fr);
+      if (ti == tj && r == c) tr += v[h];
+    }
+  }
+  __syncthreads();
+  if (ti != tj) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = threadIdx.x + 512 * h, r = e >> 5, c = e & 31;  // row n0 + r, column m0 + c
+      if (n0 + r < m && m0 + c < m) P[(int64_t)(n0 + r) * m + m0 + c] = red[c * 33 + r];
+    }
+    fr *= 2.0;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    tr += __shfl_xor(tr, o);
+    fr += __shfl_xor(fr, o);
+  }
+  double* ws = red + 32 * 33;
+  if ((threadIdx.x & 63) == 0) {
+    ws[threadIdx.x >> 6] = tr;
+    ws[SG_W + (threadIdx.x >> 6)] = fr;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    tr = fr = 0.0;
+    for (int x = 0; x < SG_W; ++x) {
+      tr += ws[x];
+      fr += ws[SG_W + x];
+    }
+    part[2 * blockIdx.x] = tr;
+    part[2 * blockIdx.x + 1] = fr;
+  }
+}
+
+// P0 = (emax I - F) / (emax - emin) from the bounds b = (emin, emax), F symmetrised
+__global__ void __launch_bounds__(64 * SG_W) tc2_start_kernel(const double* __restrict__ F, int m,
+                                                              const double* __restrict__ b, double* __restrict__ P,
+                                                              double* __restrict__ part, Tc2State* __restrict__ state) {
+  __shared__ double red[32 * 33 + 2 * SG_W];
+  const double emax = b[1], w = b[1] - b[0];
+  const bool bad = !(w > 0.0) || !isfinite(w);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *state = Tc2State{0, 0, bad ? 1 : 0, 0};
+  if (bad) return;
+  const double inv_w = 1.0 / w;
+  int ti, tj;
+  tc2_tile(blockIdx.x, ti, tj);
+  double v[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = threadIdx.x + 512 * h, r = ti * SG_T + sg_row(e), c = tj * SG_T + sg_col(e);
+    v[h] = 0.0;
+    if (r < m && c < m)
+      v[h] = ((r == c ? emax : 0.0) - 0.5 * (F[(int64_t)r * m + c] + F[(int64_t)c * m + r])) * inv_w;
+  }
+  tc2_store(v, ti, tj, m, P, part, red);
+}
+
+__global__ void __launch_bounds__(64 * SG_W) tc2_step_kernel(const double* __restrict__ P, int m, int nocc, int ntl,
+                                                             const double* __restrict__ part,
+                                                             const Tc2State* __restrict__ state,
+                                                             double* __restrict__ Pn, double* __restrict__ part_n,
+                                                             Tc2State* __restrict__ state_n) {
+  __shared__ double red[SG_W * SG_T * SG_T];
+  const Tc2State s = *state;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (s.done) {
+    if (first) *state_n = s;
+    return;
+  }
+  int ti, tj;
+  tc2_tile(blockIdx.x, ti, tj);
+  const int m0 = ti * SG_T, n0 = tj * SG_T;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double tr = 0.0, tr2 = 0.0;
+  for (int i = lane; i < ntl; i += 64) {
+    tr += part[2 * i];
+    tr2 += part[2 * i + 1];
+  }
+  RegOp<false> a, b;  // P is symmetric: its columns are read as rows
+  a.init(P, m, m0, m, w, lane & 15, lane >> 4);
+  b.init(P, m, n0, m, w, lane & 15, lane >> 4);
+  double v[2], p[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = threadIdx.x + 512 * h, r = m0 + sg_row(e), c = n0 + sg_col(e);
+    p[h] = r < m && c < m ? P[(int64_t)r * m + c] : 0.0;
+  }
+  small_gemm<false, false>(a, b, m, w, lane, red, v);
+  for (int o = 32; o > 0; o >>= 1) {
+    tr += __shfl_xor(tr, o);
+    tr2 += __shfl_xor(tr2, o);
+  }
+  const bool fin = isfinite(tr) && isfinite(tr2), conv = tr - tr2 < 1e-9 * nocc;
+  Tc2State t{s.steps + 1, s.settled + (conv ? 1 : 0), 0, 0};
+  if (!fin || (conv && t.settled > 3)) t = Tc2State{s.steps, t.settled, 1, fin && fabs(tr - nocc) < 1e-6 ? 1 : 0};
+  if (first) *state_n = t;
+  if (t.done) return;
+  if (!(fabs(tr2 - nocc) < fabs(2.0 * tr - tr2 - nocc))) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) v[h] = 2.0 * p[h] - v[h];
+  }
+  __syncthreads();  // red has been read
+  tc2_store(v, ti, tj, m, Pn, part_n, red);
+}
+
 // P <- 2 P - P2
 __global__ void tc2_raise_kernel(double* __restrict__ P, const double* __restrict__ P2, int64_t n2) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -260,8 +402,9 @@ __global__ void rows_to_cols_kernel(const double* __restrict__ V, int m, int row
   Y[i] = V[(int64_t)(row0 + j) * m + k];
 }
 
-// out[0] = min_i |G_ii|, out[1] = max_i |G_ii| (one block)
-__global__ void diag_minmax_kernel(const double* __restrict__ G, int k, double* __restrict__ out) {
+// out[0] = min_i |G_ii|, out[1] = max_i |G_ii|, out[2] = *info (one block)
+__global__ void diag_minmax_kernel(const double* __restrict__ G, int k, const int* __restrict__ info,
+                                   double* __restrict__ out) {
   __shared__ double a[256], b[256];
   double x = 1e300, y = 0.0;
   for (int i = threadIdx.x; i < k; i += blockDim.x) {
@@ -282,6 +425,7 @@ __global__ void diag_minmax_kernel(const double* __restrict__ G, int k, double* 
   if (threadIdx.x == 0) {
     out[0] = a[0];
     out[1] = b[0];
+    out[2] = *info;
   }
 }
 
@@ -469,6 +613,64 @@ struct Scf {
     else
       gemm(m, m, m, P, m, false, P, m, false, P2, m);
   }
+  // The purification's steps up to TC2_MAX rows, a launch each (tc2_step_kernel);
+  // the host looks at the state every TC2_BATCH steps.  The bounds are in part; the
+  // shares of the traces and the state, of two steps, in gw.  P: the projector.
+  static constexpr int TC2_MAX = 1536, TC2_BATCH = 8;
+  bool tc2_steps(const double* F, double*& P, double*& P2, int& steps, const char*& why) {
+    const int mt = (m + SG_T - 1) / SG_T, ntl = mt * (mt + 1) / 2;
+    double* buf[2] = {P, P2};
+    double* parts[2] = {gw.as<double>(), gw.as<double>() + 2 * ntl};
+    Tc2State* state = reinterpret_cast<Tc2State*>(gw.as<double>() + 4 * ntl);
+    hipLaunchKernelGGL(tc2_start_kernel, dim3(ntl), dim3(64 * SG_W), 0, st, F, m, part.as<double>(), P, parts[0], state);
+    Tc2State h{};
+    for (int s = 0; s < 100 && !h.done;) {
+      const int end = std::min(100, s + (s ? TC2_BATCH : 2 * TC2_BATCH));
+      for (; s < end; ++s) {
+        const int i = s & 1, j = i ^ 1;
+        hipLaunchKernelGGL(tc2_step_kernel, dim3(ntl), dim3(64 * SG_W), 0, st, buf[i], m, nocc, ntl, parts[i],
+                           state + i, buf[j], parts[j], state + j);
+      }
+      DFX_HIP(hipMemcpyAsync(&h, state + (s & 1), sizeof h, hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+    }
+    steps = h.steps;
+    why = !h.done ? "not settled" : h.steps == 0 ? "spectral bounds" : "trace";
+    P = buf[steps & 1];
+    P2 = buf[(steps & 1) ^ 1];
+    return h.done && h.ok;
+  }
+  // The same for larger m, where the tiles of 64 and 128 of the symmetric product
+  // take less time (every tile of 32 reads 64 rows of P again, through L2): a step
+  // took 76 us so and 62 in one launch at m = 1450, a tenth less so at 1930.
+  bool tc2_steps_large(const double* F, double*& P, double*& P2, int& steps, const char*& why) {
+    double b[2];
+    DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    const double w = b[1] - b[0];
+    why = "spectral bounds";
+    if (!(w > 0.0) || !std::isfinite(w)) return false;
+    const int64_t mm = (int64_t)m * m;
+    hipLaunchKernelGGL(tc2_init_kernel, dim3(nblk(mm)), dim3(256), 0, st, F, m, b[1], 1.0 / w, P);
+    int settled = 0;
+    for (steps = 0; steps < 100; ++steps) {
+      square_sym(P, P2);
+      hipLaunchKernelGGL(trace2_kernel, dim3(1), dim3(256), 0, st, P, P2, m, part.as<double>());
+      DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+      if (!std::isfinite(b[0]) || !std::isfinite(b[1])) return false;
+      if (b[0] - b[1] < 1e-9 * nocc && ++settled > 3) {
+        why = "trace";
+        return std::fabs(b[0] - nocc) < 1e-6;
+      }
+      why = "not settled";
+      if (std::fabs(b[1] - nocc) < std::fabs(2.0 * b[0] - b[1] - nocc))
+        std::swap(P, P2);
+      else
+        hipLaunchKernelGGL(tc2_raise_kernel, dim3(nblk(mm)), dim3(256), 0, st, P, P2, mm);
+    }
+    return false;
+  }
   // Occupied space of the symmetric m x m matrix F (the nocc lowest levels) by
   // trace-correcting purification: P0 = (e_max I - F) / (e_max - e_min) with
   // Gershgorin bounds, then P <- P^2 or 2P - P^2, whichever moves tr P toward
@@ -482,37 +684,15 @@ struct Scf {
   // 1e-4 of the largest).
   bool purify_occ(const double* F, double* P, double* P2, double* Y, double* Z, double* G, double* lohi,
                   int& steps, const char*& why) {
-    double b[2];
+    double b[6];
     hipLaunchKernelGGL(gersh_kernel, dim3(m), dim3(256), 0, st, F, m, lohi, lohi + m);
     hipLaunchKernelGGL(minmax_kernel, dim3(1), dim3(256), 0, st, lohi, lohi + m, m, part.as<double>());
-    DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
-    DFX_HIP(hipStreamSynchronize(st));
-    const double w = b[1] - b[0];
-    why = "spectral bounds";
-    if (!(w > 0.0) || !std::isfinite(w)) return false;
-    if (verbose) std::fprintf(stderr, "dfx_scf purification: Gershgorin [%.3f, %.3f]\n", b[0], b[1]);
-    const int64_t mm = (int64_t)m * m;
-    hipLaunchKernelGGL(tc2_init_kernel, dim3(nblk(mm)), dim3(256), 0, st, F, m, b[1], 1.0 / w, P);
-    int settled = 0;
-    bool ok = false;
-    for (steps = 0; steps < 100; ++steps) {
-      square_sym(P, P2);
-      hipLaunchKernelGGL(trace2_kernel, dim3(1), dim3(256), 0, st, P, P2, m, part.as<double>());
-      DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
+    if (verbose) {
+      DFX_HIP(hipMemcpyAsync(b, part.p, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
       DFX_HIP(hipStreamSynchronize(st));
-      if (!std::isfinite(b[0]) || !std::isfinite(b[1])) return false;
-      if (b[0] - b[1] < 1e-9 * nocc && ++settled > 3) {
-        ok = std::fabs(b[0] - nocc) < 1e-6;
-        why = "trace";
-        break;
-      }
-      why = "not settled";
-      if (std::fabs(b[1] - nocc) < std::fabs(2.0 * b[0] - b[1] - nocc))
-        std::swap(P, P2);
-      else
-        hipLaunchKernelGGL(tc2_raise_kernel, dim3(nblk(mm)), dim3(256), 0, st, P, P2, mm);
+      std::fprintf(stderr, "dfx_scf purification: Gershgorin [%.3f, %.3f]\n", b[0], b[1]);
     }
-    if (!ok) return false;
+    if (!(m <= TC2_MAX ? tc2_steps(F, P, P2, steps, why) : tc2_steps_large(F, P, P2, steps, why))) return false;
     // Cholesky QR, twice, with the library's own factorisation: G = Z^T Z = L L^T,
     // Z <- Z L^-T (then Z^T Z = L^-1 G L^-T = I)
     const size_t mo = (size_t)m * nocc;
@@ -527,16 +707,18 @@ struct Scf {
     for (int pass = 0; pass < 2; ++pass) {
       gemm(nocc, nocc, m, Zc, nocc, true, Zc, nocc, false, G, nocc);  // G = Z^T Z
       cholesky_inverse(G, nocc, qr_linv.as<double>(), qr_work.as<double>(), qr_info.as<int>(), st);
-      hipLaunchKernelGGL(diag_minmax_kernel, dim3(1), dim3(256), 0, st, G, nocc, part.as<double>());  // diag of L
-      int info = 0;
-      DFX_HIP(hipMemcpyAsync(&info, qr_info.p, sizeof(int), hipMemcpyDeviceToHost, st));
-      DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
-      DFX_HIP(hipStreamSynchronize(st));
-      why = "Cholesky QR";
-      if (info != 0 || !(b[0] > 1e-4 * b[1])) return false;
+      hipLaunchKernelGGL(diag_minmax_kernel, dim3(1), dim3(256), 0, st, G, nocc, qr_info.as<int>(),
+                         part.as<double>() + 3 * pass);  // diag of L
       gemm(m, nocc, nocc, Zc, nocc, false, qr_linv.as<double>(), nocc, true, Zn, nocc);  // Z L^-T
       std::swap(Zc, Zn);
     }
+    // both passes are looked at together: after a failed first one the second
+    // works on what it left, and neither is used
+    DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    why = "Cholesky QR";
+    for (int pass = 0; pass < 2; ++pass)
+      if (b[3 * pass + 2] != 0.0 || !(b[3 * pass] > 1e-4 * b[3 * pass + 1])) return false;
     DFX_HIP(hipMemcpyAsync(Y, Zc, sizeof(double) * mo, hipMemcpyDeviceToDevice, st));
     return true;
   }
