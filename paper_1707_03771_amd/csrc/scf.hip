@@ -23,6 +23,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <numeric>
 
 #include "gemm_small.h"
 #include "host.h"
@@ -116,6 +117,28 @@ __global__ void maxabs_partial_kernel(const double* a, int64_t n, double* part) 
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
+struct Comb {
+  const double* F[16];
+  double c[16];
+  int m;
+};
+// partial sums of F_k . b: grid (DOT_NB, m), part[k][DOT_NB], fixed order
+constexpr int DOT_NB = 32;
+__global__ void __launch_bounds__(256) dots_partial_kernel(Comb cb, const double* __restrict__ b, int64_t n,
+                                                           double* __restrict__ part) {
+  __shared__ double red[256];
+  const double* __restrict__ a = cb.F[blockIdx.y];
+  double s = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += DOT_NB * 256) s = fma(a[i], b[i], s);
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.y * DOT_NB + blockIdx.x] = red[0];
+}
+
 // E = A - A^T
 __global__ void antisym_kernel(const double* A, double* E, int n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -124,11 +147,6 @@ __global__ void antisym_kernel(const double* A, double* E, int n) {
   E[i] = A[i] - A[(int64_t)c * n + r];
 }
 
-struct Comb {
-  const double* F[16];
-  double c[16];
-  int m;
-};
 __global__ void lincomb_kernel(Comb cb, double* out, int64_t n2) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n2) return;
@@ -486,20 +504,31 @@ __global__ void scale_kernel(double* __restrict__ A, int64_t cnt, double a) {
   if (e < cnt) A[e] *= a;
 }
 
-// y = A x (n x n), one workgroup per row, fixed-order reduction
-__global__ void matvec_kernel(const double* __restrict__ A, int n, const double* __restrict__ x,
-                              double* __restrict__ y) {
-  __shared__ double red[256];
-  const int i = blockIdx.x;
-  double s = 0.0;
-  for (int j = threadIdx.x; j < n; j += 256) s = fma(A[(int64_t)i * n + j], x[j], s);
-  red[threadIdx.x] = s;
+// y = A x / |x| (n x n), one workgroup per row, fixed-order reductions.  Every
+// workgroup forms |x| beside its row's product, so that a power iteration is one
+// launch a step (3 us at n = 192) and nothing waits for the host; two sums with a
+// wait each, a scaling and a product took seven launches and copies a step.
+__global__ void __launch_bounds__(256) power_step_kernel(const double* __restrict__ A, int n,
+                                                         const double* __restrict__ x, double* __restrict__ y) {
+  __shared__ double red[2][256];
+  const int i = blockIdx.x, t = threadIdx.x;
+  double s = 0.0, q = 0.0;
+  for (int j = t; j < n; j += 256) {
+    const double v = x[j];
+    s = fma(A[(int64_t)i * n + j], v, s);
+    q = fma(v, v, q);
+  }
+  red[0][t] = s;
+  red[1][t] = q;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    if (t < o) {
+      red[0][t] += red[0][t + o];
+      red[1][t] += red[1][t + o];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) y[i] = red[0];
+  if (t == 0) y[i] = red[0][0] / sqrt(red[1][0]);
 }
 
 // ---- driver ---------------------------------------------------------------------------
@@ -512,25 +541,44 @@ struct Scf {
   EventSpans* eig_spans = nullptr;
   int verbose = 0;
 
-  double reduce_sum(const double* a, const double* b, const double* c, int64_t cnt) {
-    const int nb = 512;
-    hipLaunchKernelGGL(dot_partial_kernel, dim3(nb), dim3(256), 0, st, a, b, c, cnt, part.as<double>());
+  // sums and maxima: part has room for 512 partial results, which the host adds up in order
+  static constexpr int NPART = 512;
+  void sum_part(const double* a, const double* b, const double* c, int64_t cnt, int off, int nb) {
+    hipLaunchKernelGGL(dot_partial_kernel, dim3(nb), dim3(256), 0, st, a, b, c, cnt, part.as<double>() + off);
+  }
+  void max_part(const double* a, int64_t cnt, int off, int nb) {
+    hipLaunchKernelGGL(maxabs_partial_kernel, dim3(nb), dim3(256), 0, st, a, cnt, part.as<double>() + off);
+  }
+  void fetch_part(int nb) {
     hpart.resize(nb);
     DFX_HIP(hipMemcpyAsync(hpart.data(), part.p, sizeof(double) * nb, hipMemcpyDeviceToHost, st));
     DFX_HIP(hipStreamSynchronize(st));
+  }
+  double added(int off, int nb) const { return std::accumulate(hpart.begin() + off, hpart.begin() + off + nb, 0.0); }
+  double largest(int off, int nb) const {
     double s = 0.0;
-    for (double v : hpart) s += v;
+    for (int k = off; k < off + nb; ++k) s = std::max(s, hpart[k]);
     return s;
   }
+  double reduce_sum(const double* a, const double* b, const double* c, int64_t cnt) {
+    sum_part(a, b, c, cnt, 0, NPART);
+    fetch_part(NPART);
+    return added(0, NPART);
+  }
   double reduce_max(const double* a, int64_t cnt) {
-    const int nb = 512;
-    hipLaunchKernelGGL(maxabs_partial_kernel, dim3(nb), dim3(256), 0, st, a, cnt, part.as<double>());
-    hpart.resize(nb);
-    DFX_HIP(hipMemcpyAsync(hpart.data(), part.p, sizeof(double) * nb, hipMemcpyDeviceToHost, st));
-    DFX_HIP(hipStreamSynchronize(st));
-    double s = 0.0;
-    for (double v : hpart) s = std::max(s, v);
-    return s;
+    max_part(a, cnt, 0, NPART);
+    fetch_part(NPART);
+    return largest(0, NPART);
+  }
+  // out[k] += a[stride k] . b for k < count <= 16: one launch and one wait
+  void dots(const std::vector<DevMem>& a, int first, int stride, int count, const double* b, int64_t cnt, double* out) {
+    static_assert(16 * DOT_NB <= NPART, "");
+    Comb cb{};
+    cb.m = count;
+    for (int k = 0; k < count; ++k) cb.F[k] = a[first + (size_t)stride * k].as<double>();
+    hipLaunchKernelGGL(dots_partial_kernel, dim3(DOT_NB, count), dim3(256), 0, st, cb, b, cnt, part.as<double>());
+    fetch_part(count * DOT_NB);
+    for (int k = 0; k < count; ++k) out[k] += added(k * DOT_NB, DOT_NB);
   }
   void gemm(int M, int N, int K, const double* A, int lda, bool ta, const double* B, int ldb, bool tb,
             double* C, int ldc, double alpha = 1.0, double beta = 0.0) {
@@ -592,15 +640,12 @@ struct Scf {
     double* v = vw.as<double>();
     double* w = v + nn;
     hipLaunchKernelGGL(rand_fill_kernel, dim3(nblk(nn)), dim3(256), 0, st, v, (int64_t)nn, (uint64_t)0x2545F4914F6CDD1Dull);
-    double nrm = 0.0;
     for (int k = 0; k < 40; ++k) {
-      const double vv = reduce_sum(v, v, nullptr, nn);
-      if (!(vv > 0.0)) return false;
-      hipLaunchKernelGGL(scale_kernel, dim3(nblk(nn)), dim3(256), 0, st, v, (int64_t)nn, 1.0 / std::sqrt(vv));
-      hipLaunchKernelGGL(matvec_kernel, dim3(nn), dim3(256), 0, st, Z, nn, v, w);
-      nrm = std::sqrt(reduce_sum(w, w, nullptr, nn));
+      hipLaunchKernelGGL(power_step_kernel, dim3(nn), dim3(256), 0, st, Z, nn, v, w);
       std::swap(v, w);
     }
+    const double nrm = std::sqrt(reduce_sum(v, v, nullptr, nn));
+    if (!(nrm > 0.0)) return false;
     lmin = 1.0 / (nrm * nrm);
     return true;
   }
@@ -1175,7 +1220,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
     hipStream_t st = S.st;
     S.n = n;
     S.nocc = nocc;
-    S.part.alloc(sizeof(double) * 512);
+    S.part.alloc(sizeof(double) * Scf::NPART);
     S.gw.alloc(sizeof(double) * std::max<size_t>(4 * (size_t)n * n, syrk_f64_work_elems(n)));
     S.verbose = o.verbose;
     EventSpans sp_eig_all, sp_pur;
@@ -1453,7 +1498,8 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       k_build(ja, Cocc.as<double>(), nocc, Km.as<double>(), w, st, &ktimer);
       hipLaunchKernelGGL(fock_kernel, dim3(nblk(n2)), dim3(256), 0, st, h.as<double>(), Jm.as<double>(),
                          Km.as<double>(), F.as<double>(), n2);
-      E = S.reduce_sum(D.as<double>(), h.as<double>(), F.as<double>(), n2) + Enuc;
+      constexpr int NP2 = Scf::NPART / 2;  // the energy's partial sums and those of the error, fetched together
+      S.sum_part(D.as<double>(), h.as<double>(), F.as<double>(), n2, 0, NP2);
       // e = X^T (F D S - S D F) X
       S.gemm(n, n, n, F.as<double>(), n, false, D.as<double>(), n, false, t1.as<double>(), n);
       S.gemm(n, n, n, t1.as<double>(), n, false, Sm.as<double>(), n, false, t2.as<double>(), n);
@@ -1461,7 +1507,10 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       S.gemm(m, n, n, X.as<double>(), m, true, t1.as<double>(), n, false, t2.as<double>(), n);
       double* e_new = Eh[hpos].as<double>();
       S.gemm(m, m, n, t2.as<double>(), n, false, X.as<double>(), m, false, e_new, m);
-      emax = S.reduce_max(e_new, (int64_t)m * m);
+      S.max_part(e_new, (int64_t)m * m, NP2, NP2);
+      S.fetch_part(Scf::NPART);
+      E = S.added(0, NP2) + Enuc;
+      emax = S.largest(NP2, NP2);
       if (ih <= DFX_MAXHIST) {
         inf.E_hist[ih - 1] = E;
         inf.err_hist[ih - 1] = emax;
@@ -1525,7 +1574,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       hcount = std::min(hcount + 1, dsz);
       // overlaps of the new error with every stored one
       std::vector<double> Bn(dsz, 0.0);
-      for (int k = 0; k < hcount; ++k) Bn[k] = S.reduce_sum(Eh[k].as<double>(), e_new, nullptr, (int64_t)m * m);
+      S.dots(Eh, 0, 1, hcount, e_new, (int64_t)m * m, Bn.data());
       for (int k = 0; k < hcount; ++k) Bdiis[(size_t)hpos * dsz + k] = Bdiis[(size_t)k * dsz + hpos] = Bn[k];
       const double* Fuse = F.as<double>();
       if (hcount > 1) {
@@ -1680,7 +1729,7 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
     hipStream_t st = S.st;
     S.n = n;
     S.nocc = na;
-    S.part.alloc(sizeof(double) * 512);
+    S.part.alloc(sizeof(double) * Scf::NPART);
     S.gw.alloc(sizeof(double) * std::max<size_t>(4 * (size_t)n * n, syrk_f64_work_elems(n)));
     const int64_t n2 = (int64_t)n * n;
 
@@ -1931,12 +1980,10 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
         for (int s2 = 0; s2 < 2; ++s2)
           DFX_HIP(hipMemcpyAsync(Fh[2 * hpos + s2].p, F[s2].p, 8 * n2, hipMemcpyDeviceToDevice, st));
       hcount = std::min(hcount + 1, dsz);
-      for (int k = 0; k < hcount; ++k) {
-        double b = 0.0;
-        for (int s2 = 0; s2 < nsp; ++s2)
-          b += S.reduce_sum(Eh[2 * k + s2].as<double>(), Eh[2 * hpos + s2].as<double>(), nullptr, m2);
-        Bdiis[(size_t)hpos * dsz + k] = Bdiis[(size_t)k * dsz + hpos] = b;
-      }
+      std::vector<double> Bn(hcount, 0.0);
+      for (int s2 = 0; s2 < nsp; ++s2)
+        S.dots(Eh, s2, 2, hcount, Eh[2 * hpos + s2].as<double>(), m2, Bn.data());
+      for (int k = 0; k < hcount; ++k) Bdiis[(size_t)hpos * dsz + k] = Bdiis[(size_t)k * dsz + hpos] = Bn[k];
       const double* Fuse[2] = {restricted ? Feff.as<double>() : F[0].as<double>(), F[1].as<double>()};
       DevMem* Fext[2] = {&t1, &t2};
       if (hcount > 1) {
@@ -2070,7 +2117,7 @@ int dfx_lowdin(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dou
     Scf S;
     S.st = (hipStream_t)stream;
     hipStream_t st = S.st;
-    S.part.alloc(sizeof(double) * 512);
+    S.part.alloc(sizeof(double) * Scf::NPART);
     DevMem W(8 * n2), Tm(8 * n2), Vm(8 * n2), sv(8 * (size_t)n);
     int1e_build(hb, geom, W.as<double>(), Tm.as<double>(), Vm.as<double>(), st);
     // S^1/2 by Newton-Schulz; by the eigen-decomposition where S is too close to singular for it
