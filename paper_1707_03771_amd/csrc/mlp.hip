@@ -9,123 +9,261 @@
 
 namespace dfx {
 
-// ---- tiled SGEMM on FP32 matrix cores: C = op(A) op(B) (+ C), row-major.
-// A workgroup owns a 64 x 64 tile of C; its four waves own 32 x 32 quarters,
-// each as 2 x 2 tiles of v_mfma_f32_16x16x4f32 (FP32 products, FP32 sums).
-// K goes through LDS in slices of 16.  MFMA operands: lane (li, lk) = (lane %
-// 16, lane / 16) gives A[row li][k lk] and B[k lk][col li]; the result's
-// element r of that lane is C[row 4 lk + r][col li].
-constexpr int SG = 64, SK = 16;
+// ---- products on FP32 matrix cores (v_mfma_f32_16x16x4f32: FP32 products and sums) ----
+// A workgroup owns a T x T tile of the result, T = 16, 32 or 64; its eight waves take
+// blocks of 16 k in turn, operands straight from memory to registers (two to
+// four blocks in flight), and their sums are added in LDS in a fixed order.
+// MFMA operands: lane (li, lk) = (lane % 16, lane / 16) gives A[row li][k lk] and
+// B[k lk][col li]; the result's element r of that lane is C[row 4 lk + r][col li].
+// Within a block of 16 the lane has k = 4 lk .. 4 lk + 3, one MFMA each.
+// What bounds it: launches and the latency of a tile's loads, since a minibatch
+// has few tiles (128 x 256: 32 of 32 x 32).  So what follows a product is in its
+// epilogue: bias and SiLU, the loss and its gradient, the factor SiLU'(Z); the
+// bias gradient is summed from the operands of the weight gradient, and both
+// products that read a layer's gradient are one launch.  Training step of 454 x
+// 256^3 x 70, batch 128: 435 us with 64 x 64 tiles through LDS and all of these
+// launches apart, 100 so.
+constexpr int MW = 8, MT = 64 * MW;  // waves and threads of a workgroup
 typedef float v4f __attribute__((ext_vector_type(4)));
-template <bool TA, bool TB>
-__global__ void __launch_bounds__(256) sgemm_kernel(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                   const float* __restrict__ B, int ldb, float* __restrict__ C,
-                                                   int ldc, int accumulate) {
-  __shared__ float As[SG][SK + 1];  // As[m][k]
-  __shared__ float Bs[SK][SG + 1];  // Bs[k][n]
-  const int m0 = blockIdx.y * SG, n0 = blockIdx.x * SG;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
-  v4f acc[2][2];
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// x(row, k) = KC ? p[row ld + k] : p[k ld + row], n rows
+struct MatOp {
+  const float* p;
+  int64_t ld;
+  int n;
+};
+
+// the 16 F rows from x0 of an operand as a wave reads them: blocks of 16 k, MW apart
+template <bool KC, int F>
+struct TileOp {
+  const float* p;  // x0 and the wave's first block (wave-uniform)
+  int64_t ld;
+  int64_t vo[F];   // the lane's k = 4 lk of its row in fragment f
+  __device__ __forceinline__ void init(const MatOp& m, int x0, int w, int li, int lk) {
+    ld = m.ld;
+    p = KC ? m.p + x0 * ld + 16 * w : m.p + 16 * w * ld + x0;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += SK) {
-    for (int e = threadIdx.x; e < SG * SK; e += 256) {
-      const int mm = e / SK, kk = e % SK;
-      const int m = m0 + mm, k = k0 + kk;
-      As[mm][kk] = (m < M && k < K) ? (TA ? A[(int64_t)k * lda + m] : A[(int64_t)m * lda + k]) : 0.0f;
-      const int nn = e / SK, n = n0 + nn;
-      Bs[kk][nn] = (n < N && k < K) ? (TB ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.0f;
+    for (int f = 0; f < F; ++f) {
+      const int r = min(16 * f + li, m.n - 1 - x0);  // rows past the end: not stored
+      vo[f] = KC ? r * ld + 4 * lk : 4 * lk * ld + r;
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < SK; kk += 4) {
-      float fa[2], fb[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) fa[a] = As[wm + a * 16 + li][kk + lk];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) fb[b] = Bs[kk + lk][wn + b * 16 + li];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    }
-    __syncthreads();
   }
+  __device__ __forceinline__ void load(int64_t i, float (&v)[F][4]) const {
+    const float* q = p + i * (KC ? 16 * MW : 16 * MW * ld);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int f = 0; f < F; ++f) {
+      if (KC) {
+        const f4u x = *reinterpret_cast<const f4u*>(q + vo[f]);
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+        for (int t = 0; t < 4; ++t) v[f][t] = x[t];
+      } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + a * 16 + 4 * lk + r, n = n0 + wn + b * 16 + li;
-        if (m < M && n < N) {
-          float* c = C + (int64_t)m * ldc + n;
-          *c = accumulate ? *c + acc[a][b][r] : acc[a][b][r];
-        }
+        for (int t = 0; t < 4; ++t) v[f][t] = q[vo[f] + t * ld];
       }
-}
-
-static void sgemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C,
-                  int ldc, bool accumulate, hipStream_t st) {
-  if (M <= 0 || N <= 0) return;
-  const dim3 g((N + SG - 1) / SG, (M + SG - 1) / SG);
-#define SGL(X, Y) hipLaunchKernelGGL((sgemm_kernel<X, Y>), g, dim3(256), 0, st, M, N, K, A, lda, B, ldb, C, ldc, accumulate ? 1 : 0)
-  if (!ta && !tb) SGL(false, false);
-  else if (!ta && tb) SGL(false, true);
-  else if (ta && !tb) SGL(true, false);
-  else SGL(true, true);
-#undef SGL
-}
-
-// Z = Z + b (per column); A = silu(Z) (or A = Z for the output layer)
-__global__ void bias_act_kernel(float* Z, float* Aout, const float* __restrict__ b, int rows, int cols, int act) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)rows * cols) return;
-  const float z = Z[i] + b[i % cols];
-  Z[i] = z;
-  Aout[i] = act ? z / (1.0f + expf(-z)) : z;
-}
-
-// G *= silu'(Z)
-__global__ void dsilu_kernel(float* G, const float* __restrict__ Z, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float z = Z[i];
-  const float s = 1.0f / (1.0f + expf(-z));
-  G[i] *= s * (1.0f + z * (1.0f - s));
-}
-
-// db[c] = sum_r G[r][c], fixed order
-__global__ void colsum_kernel(const float* __restrict__ G, int rows, int cols, float* db) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.0f;
-  for (int r = 0; r < rows; ++r) s += G[(int64_t)r * cols + c];
-  db[c] = s;
-}
-
-// G = 2 (Y - T) / n ; per-block partial sums of (Y - T)^2
-__global__ void mse_kernel(const float* __restrict__ Y, const float* __restrict__ T, float* G, int64_t n,
-                           double* part) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float d = Y[i] - T[i];
-    G[i] = 2.0f * d / (float)n;
-    s += (double)d * d;
+    }
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  // the last block, of which k < kr exist
+  __device__ __forceinline__ void load_tail(int64_t i, int kr, int lk, float (&v)[F][4]) const {
+    const float* q = p + i * (KC ? 16 * MW : 16 * MW * ld);
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[f][t] = 4 * lk + t < kr ? q[vo[f] + (KC ? t : t * ld)] : 0.0f;
+  }
+};
+
+// element e of a tile, as its partial sums lie in LDS: fragment, register, lane
+template <int F>
+__device__ __forceinline__ int tile_row(int e) { return (e >> 8) / F * 16 + 4 * ((e & 63) >> 4) + ((e >> 6) & 3); }
+template <int F>
+__device__ __forceinline__ int tile_col(int e) { return (e >> 8) % F * 16 + (e & 15); }
+
+// The tile's product over k < K: element e = threadIdx.x + MT h < 256 F^2 in out[h].
+// rsum (ROWSUM): the sums of A's 16 F rows over k, in threads 0 .. 16 F - 1.
+template <bool KA, bool KB, int F, bool ROWSUM>
+__device__ __forceinline__ void tile_gemm(const MatOp& A, const MatOp& B, int m0, int n0, int K, float* red,
+                                          float (&out)[(F * F + 1) / 2], float& rsum) {
+  constexpr int D = F == 4 ? 2 : 4;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  v4f acc[F][F];
+  float rs[F];
+#pragma unroll
+  for (int i = 0; i < F; ++i) {
+    rs[i] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < F; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  float a[D][F][4], b[D][F][4];
+  TileOp<KA, F> oa;
+  TileOp<KB, F> ob;
+  oa.init(A, m0, w, li, lk);
+  ob.init(B, n0, w, li, lk);
+  auto step = [&](const float (&x)[F][4], const float (&y)[F][4]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < F; ++i) {
+        if (ROWSUM) rs[i] += x[i][t];
+#pragma unroll
+        for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][t], y[j][t], acc[i][j], 0, 0, 0);
+      }
+  };
+  const int full = K >> 4, kr = K & 15;
+  const int nb = full > w ? (full - w + MW - 1) / MW : 0;  // whole blocks of this wave
+  if (nb > 0) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      oa.load(min(d, nb - 1), a[d]);
+      ob.load(min(d, nb - 1), b[d]);
+    }
+    int i = 0;
+    for (; i + D <= nb; i += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        step(a[d], b[d]);
+        // past the end: the last block again, not used
+        oa.load(min(i + D + d, nb - 1), a[d]);
+        ob.load(min(i + D + d, nb - 1), b[d]);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (i + d < nb) step(a[d], b[d]);
+  }
+  if (kr && full % MW == w) {
+    oa.load_tail(nb, kr, lk, a[0]);
+    ob.load_tail(nb, kr, lk, b[0]);
+    step(a[0], b[0]);
+  }
+  // in chunks of RX fragment rows, EC elements
+  constexpr int RX = F == 4 ? 1 : F, EC = 256 * F * RX, HC = (EC + MT - 1) / MT;
+#pragma unroll
+  for (int q = 0; q < F / RX; ++q) {
+    if (q) __syncthreads();
+#pragma unroll
+    for (int x = 0; x < RX; ++x)
+#pragma unroll
+      for (int y = 0; y < F; ++y)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[w * EC + ((x * F + y) * 4 + r) * 64 + lane] = acc[q * RX + x][y][r];
     __syncthreads();
+#pragma unroll
+    for (int h = 0; h < HC; ++h) {
+      const int e = threadIdx.x + MT * h;
+      float s = 0.0f;
+      if (e < EC) {
+        s = red[e];
+#pragma unroll
+        for (int x = 1; x < MW; ++x) s += red[x * EC + e];
+      }
+      out[q * HC + h] = s;
+    }
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (ROWSUM) {
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+      float s = rs[x] + __shfl_xor(rs[x], 16);
+      s += __shfl_xor(s, 32);
+      if (lk == 0) red[w * 16 * F + x * 16 + li] = s;
+    }
+    __syncthreads();
+    rsum = 0.0f;
+    if (threadIdx.x < 16 * F)
+      for (int x = 0; x < MW; ++x) rsum += red[x * 16 * F + threadIdx.x];
+  }
 }
+
+// Layer forward: z = a W^T + b.  hidden: Z = z, out = silu(z).  Otherwise out = z, or
+// with T the loss: out = 2 (z - T) / n over all n = rows x cols outputs, and the
+// workgroup's sum of (z - T)^2 to part.
+template <int F>
+__global__ void __launch_bounds__(MT) layer_forward_kernel(int rows, int cols, int K, const float* __restrict__ a,
+                                                           const float* __restrict__ W, const float* __restrict__ bias,
+                                                           int hidden, float* __restrict__ Z, float* __restrict__ out,
+                                                           const float* __restrict__ T, double* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) float red[MW * 256 * F * (F == 4 ? 1 : F)];
+  const int nt = (cols + 16 * F - 1) / (16 * F);
+  const int m0 = blockIdx.x / nt * 16 * F, n0 = blockIdx.x % nt * 16 * F;
+  float v[(F * F + 1) / 2], rsum;
+  tile_gemm<true, true, F, false>(MatOp{a, K, rows}, MatOp{W, K, cols}, m0, n0, K, red, v, rsum);
+  double s = 0.0;
+#pragma unroll
+  for (int h = 0; h < (F * F + 1) / 2; ++h) {
+    const int e = threadIdx.x + MT * h, r = m0 + tile_row<F>(e), c = n0 + tile_col<F>(e);
+    if (e >= 256 * F * F || r >= rows || c >= cols) continue;
+    const int64_t i = (int64_t)r * cols + c;
+    const float z = v[h] + bias[c];
+    if (hidden) {
+      Z[i] = z;
+      out[i] = z / (1.0f + expf(-z));
+    } else if (T) {
+      const float d = z - T[i];
+      out[i] = 2.0f * d / (float)((int64_t)rows * cols);
+      s += (double)d * d;
+    } else {
+      out[i] = z;
+    }
+  }
+  if (!T) return;
+  double* ws = reinterpret_cast<double*>(red);
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s = 0.0;
+    for (int x = 0; x < MW; ++x) s += ws[x];
+    part[blockIdx.x] = s;
+  }
+}
+
+// Layer backward from G = dL/dz (rows x no): workgroups below nda the tiles of
+// (G W) silu'(Zin) (rows x ni, the layer before), the others those of dW = G^T a, of
+// which the first column of tiles also leaves db.
+template <int F>
+__global__ void __launch_bounds__(MT) layer_backward_kernel(int rows, int no, int ni, int nda,
+                                                            const float* __restrict__ G, const float* __restrict__ W,
+                                                            const float* __restrict__ Zin,
+                                                            const float* __restrict__ a, float* __restrict__ Gin,
+                                                            float* __restrict__ dW, float* __restrict__ db) {
+  __shared__ __attribute__((aligned(16))) float red[MW * 256 * F * (F == 4 ? 1 : F)];
+  const int nt = (ni + 16 * F - 1) / (16 * F);
+  const bool da = (int)blockIdx.x < nda;
+  const int t = da ? blockIdx.x : blockIdx.x - nda;
+  const int m0 = t / nt * 16 * F, n0 = t % nt * 16 * F;
+  float v[(F * F + 1) / 2], rsum;
+  if (da)
+    tile_gemm<true, false, F, false>(MatOp{G, no, rows}, MatOp{W, ni, ni}, m0, n0, no, red, v, rsum);
+  else
+    tile_gemm<false, false, F, true>(MatOp{G, no, no}, MatOp{a, ni, ni}, m0, n0, rows, red, v, rsum);
+#pragma unroll
+  for (int h = 0; h < (F * F + 1) / 2; ++h) {
+    const int e = threadIdx.x + MT * h, r = m0 + tile_row<F>(e), c = n0 + tile_col<F>(e);
+    if (e >= 256 * F * F || r >= (da ? rows : no) || c >= ni) continue;
+    const int64_t i = (int64_t)r * ni + c;
+    if (da) {
+      const float z = Zin[i];
+      const float s = 1.0f / (1.0f + expf(-z));
+      Gin[i] = v[h] * (s * (1.0f + z * (1.0f - s)));
+    } else {
+      dW[i] = v[h];
+    }
+  }
+  if (!da && n0 == 0 && threadIdx.x < 16 * F && m0 + (int)threadIdx.x < no) db[m0 + threadIdx.x] = rsum;
+}
+
+static int tiles_of(int64_t m, int64_t n, int F) { return (int)(((m + 16 * F - 1) / (16 * F)) * ((n + 16 * F - 1) / (16 * F))); }
+
+// 16 F is the tile of a launch with so many tiles of 16: small ones while the chip is
+// not full, larger ones, which read their operands less often, beyond.  Loss and
+// gradient with all launches in tiles of 16 / 32 / 64, us: 454 x 256^3 x 70, batch 128
+// (128 tiles) 100 / 117 / 159; 454 x 512^2 x 70, batch 1024 (2048) 188 / 157 / 208;
+// 1024^3 x 256, batch 1024 (4096) 454 / 320 / 290; batch 4096 1841 / 1236 / 1023.
+static int tile_frags(int64_t tiles16) { return tiles16 >= 4096 ? 4 : tiles16 > 1024 ? 2 : 1; }
 
 __global__ void adam_kernel(float* theta, const float* __restrict__ g, float* m, float* v, int64_t n, float lr,
                             float b1, float b2, float eps, float c1, float c2) {
@@ -164,78 +302,72 @@ size_t mlp_work_floats(const std::vector<int>& w, int batch) {
   return s + 2 * (size_t)batch * mx + 1024;                           // two gradient buffers + partials
 }
 
-// forward: A_L = network(X); Z/A of every layer kept in work for the backward pass
-static const float* forward_impl(const std::vector<int>& w, const float* theta, const float* X, int batch,
-                                 float* work, hipStream_t st) {
+// Network on X: Z and A of every hidden layer kept in work for the backward pass.
+// out: the outputs, or with T the gradient of the loss in them, and the loss's
+// partial sums (their number returned) in part
+static int forward_impl(const std::vector<int>& w, const float* theta, const float* X, int batch, float* work,
+                        float* out, const float* T, double* part, hipStream_t st) {
   const int nl = (int)w.size() - 1;
   const float* a = X;
   const float* p = theta;
   float* wp = work;
+  int tiles = 0;
   for (int l = 0; l < nl; ++l) {
-    const int ni = w[l], no = w[l + 1];
+    const int ni = w[l], no = w[l + 1], hidden = l < nl - 1 ? 1 : 0;
     float* Z = wp;
-    float* A = wp + (size_t)batch * no;
+    float* A = hidden ? wp + (size_t)batch * no : out;
     wp += 2 * (size_t)batch * no;
-    sgemm(false, true, batch, no, ni, a, ni, p, ni, Z, no, false, st);  // Z = a W^T
-    hipLaunchKernelGGL(bias_act_kernel, dim3(nb((int64_t)batch * no)), dim3(256), 0, st, Z, A,
-                       p + (size_t)ni * no, batch, no, l < nl - 1 ? 1 : 0);
+    const float* b = p + (size_t)ni * no;
+    const float* Tl = hidden ? nullptr : T;
+    const int F = tile_frags(tiles_of(batch, no, 1));
+    tiles = tiles_of(batch, no, F);
+    hipLaunchKernelGGL(F == 4 ? layer_forward_kernel<4> : F == 2 ? layer_forward_kernel<2> : layer_forward_kernel<1>,
+                       dim3(tiles), dim3(MT), 0, st, batch, no, ni, a, p, b, hidden, Z, A, Tl, part);
     p += (size_t)ni * no + no;
     a = A;
   }
-  return a;
+  return tiles;
 }
 
 void mlp_forward(const std::vector<int>& w, const float* theta, const float* X, int batch, float* Y, float* work,
                  hipStream_t st) {
-  const float* out = forward_impl(w, theta, X, batch, work, st);
-  DFX_HIP(hipMemcpyAsync(Y, out, sizeof(float) * (size_t)batch * w.back(), hipMemcpyDeviceToDevice, st));
+  // a single layer reads X while it writes: Y may lie in X
+  float* out = w.size() == 2 ? work : Y;
+  forward_impl(w, theta, X, batch, work, out, nullptr, nullptr, st);
+  if (out != Y)
+    DFX_HIP(hipMemcpyAsync(Y, out, sizeof(float) * (size_t)batch * w.back(), hipMemcpyDeviceToDevice, st));
 }
 
-// acc[0] += sum of the 64 partial sums / n  (one thread, fixed order)
-__global__ void loss_accumulate_kernel(const double* __restrict__ part, int64_t n, double* acc) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// acc[0] += sum of the partial sums / n  (one wave, fixed order)
+__global__ void __launch_bounds__(64) loss_accumulate_kernel(const double* __restrict__ part, int np, int64_t n,
+                                                             double* acc) {
   double s = 0.0;
-  for (int i = 0; i < 64; ++i) s += part[i];
-  acc[0] += s / (double)n;
+  for (int i = threadIdx.x; i < np; i += 64) s += part[i];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (threadIdx.x == 0) acc[0] += s / (double)n;
 }
 
-static void loss_grad_impl(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
-                           float* grad, float* work, double*& part_out, int64_t& nout_out, hipStream_t st);
+struct LossParts {
+  const double* p;
+  int np;
+  int64_t nout;
+};
 
-double mlp_loss_grad(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
-                     float* grad, float* work, hipStream_t st) {
-  double* part = nullptr;
-  int64_t nout = 0;
-  loss_grad_impl(w, theta, X, T, batch, grad, work, part, nout, st);
-  std::vector<double> hp(64);
-  DFX_HIP(hipMemcpyAsync(hp.data(), part, sizeof(double) * 64, hipMemcpyDeviceToHost, st));
-  DFX_HIP(hipStreamSynchronize(st));
-  double s = 0.0;
-  for (double v : hp) s += v;
-  return s / (double)nout;
-}
-
-void mlp_loss_grad_acc(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
-                       float* grad, float* work, double* loss_acc, hipStream_t st) {
-  double* part = nullptr;
-  int64_t nout = 0;
-  loss_grad_impl(w, theta, X, T, batch, grad, work, part, nout, st);
-  hipLaunchKernelGGL(loss_accumulate_kernel, dim3(1), dim3(64), 0, st, part, nout, loss_acc);
-}
-
-static void loss_grad_impl(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
-                           float* grad, float* work, double*& part_out, int64_t& nout_out, hipStream_t st) {
+static LossParts loss_grad_impl(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
+                                float* grad, float* work, hipStream_t st) {
   const int nl = (int)w.size() - 1;
-  const float* Y = forward_impl(w, theta, X, batch, work, st);
   size_t act = 0;
   for (int l = 1; l <= nl; ++l) act += 2 * (size_t)batch * w[l];
   int mx = 0;
   for (int x : w) mx = std::max(mx, x);
   float* G = work + act;
   float* G2 = G + (size_t)batch * mx;
-  double* part = reinterpret_cast<double*>(work + ((act + 2 * (size_t)batch * mx + 1) & ~(size_t)1));
-  const int64_t nout = (int64_t)batch * w.back();
-  hipLaunchKernelGGL(mse_kernel, dim3(64), dim3(256), 0, st, Y, T, G, nout, part);
+  // the loss's partial sums: behind the gradients up to 511 of them, else in the
+  // output layer's place for Z, which has more than 8 floats for each
+  size_t po = act + 2 * (size_t)batch * mx;
+  if (tiles_of(batch, w[nl], 1) > 511) po = act - 2 * (size_t)batch * w[nl];
+  double* part = reinterpret_cast<double*>(work + ((po + 1) & ~(size_t)1));
+  const int np = forward_impl(w, theta, X, batch, work, G, T, part, st);
   // parameter offsets
   std::vector<size_t> off(nl);
   size_t o = 0;
@@ -252,20 +384,37 @@ static void loss_grad_impl(const std::vector<int>& w, const float* theta, const 
   }
   for (int l = nl - 1; l >= 0; --l) {
     const int ni = w[l], no = w[l + 1];
-    if (l < nl - 1)
-      hipLaunchKernelGGL(dsilu_kernel, dim3(nb((int64_t)batch * no)), dim3(256), 0, st, G, work + zofs[l],
-                         (int64_t)batch * no);
-    const float* a_in = (l == 0) ? X : work + zofs[l - 1] + (size_t)batch * w[l];
-    sgemm(true, false, no, ni, batch, G, no, a_in, ni, grad + off[l], ni, false, st);  // dW = G^T a
-    hipLaunchKernelGGL(colsum_kernel, dim3((no + 255) / 256), dim3(256), 0, st, G, batch, no,
-                       grad + off[l] + (size_t)ni * no);
-    if (l > 0) {
-      sgemm(false, false, batch, ni, no, G, no, theta + off[l], ni, G2, ni, false, st);  // dA_in = G W
-      std::swap(G, G2);
-    }
+    const float* zin = l == 0 ? nullptr : work + zofs[l - 1];
+    const float* a_in = l == 0 ? X : zin + (size_t)batch * ni;
+    float *dW = grad + off[l], *db = dW + (size_t)ni * no;
+    const float* W = theta + off[l];
+    int F = tile_frags(tiles_of(no, ni, 1) + (l ? tiles_of(batch, ni, 1) : 0));
+    // a long batch over few tiles of dW: smaller ones (300^3 x 30, batch 20000: 1985
+    // us in tiles of 64, 1150 of 16)
+    while (F > 1 && batch > no && tiles_of(no, ni, F) < 128) F /= 2;
+    const int nda = l ? tiles_of(batch, ni, F) : 0, grid = nda + tiles_of(no, ni, F);
+    hipLaunchKernelGGL(F == 4 ? layer_backward_kernel<4> : F == 2 ? layer_backward_kernel<2> : layer_backward_kernel<1>,
+                       dim3(grid), dim3(MT), 0, st, batch, no, ni, nda, G, W, zin, a_in, G2, dW, db);
+    std::swap(G, G2);
   }
-  part_out = part;
-  nout_out = nout;
+  return LossParts{part, np, (int64_t)batch * w[nl]};
+}
+
+double mlp_loss_grad(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
+                     float* grad, float* work, hipStream_t st) {
+  const LossParts p = loss_grad_impl(w, theta, X, T, batch, grad, work, st);
+  std::vector<double> hp(p.np);
+  DFX_HIP(hipMemcpyAsync(hp.data(), p.p, sizeof(double) * p.np, hipMemcpyDeviceToHost, st));
+  DFX_HIP(hipStreamSynchronize(st));
+  double s = 0.0;
+  for (double v : hp) s += v;
+  return s / (double)p.nout;
+}
+
+void mlp_loss_grad_acc(const std::vector<int>& w, const float* theta, const float* X, const float* T, int batch,
+                       float* grad, float* work, double* loss_acc, hipStream_t st) {
+  const LossParts p = loss_grad_impl(w, theta, X, T, batch, grad, work, st);
+  hipLaunchKernelGGL(loss_accumulate_kernel, dim3(1), dim3(64), 0, st, p.p, p.np, p.nout, loss_acc);
 }
 
 void mlp_adam(float* theta, const float* grad, float* m, float* v, int64_t n, int step, float lr, hipStream_t st) {

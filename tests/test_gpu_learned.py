@@ -68,6 +68,28 @@ def test_mlp_gradient_matches_oracle(widths, batch):
         o += k
 
 
+@pytest.mark.parametrize("widths,batch", [
+    ([17, 33, 5], 1), ([65, 16, 31], 33),     # tiles of 16, k below a block and past it
+    ([70, 600, 610, 33], 520),                # of 32, and of 16 in the last layer
+    ([40, 1100, 1030, 15], 1000),             # of 64, 32 and 16
+    ([9, 24, 8200], 3)])                      # more than 511 partial sums of the loss
+def test_mlp_tiles(widths, batch):
+    """The tiles of 16, 32 and 64 of the network's products, with remainders in every
+    direction; tolerances as above."""
+    import paper_1707_03771_amd as dfx
+    rng = np.random.default_rng(5)
+    th = seeded_net(widths, 6)
+    X = rng.normal(size=(batch, widths[0])).astype(np.float32)
+    T = rng.normal(size=(batch, widths[-1])).astype(np.float32)
+    Y = dfx.mlp_forward(widths, dev(th), dev(X)).cpu().numpy()
+    Yo, _ = L.forward(th.astype(np.float64), widths, X.astype(np.float64))
+    assert np.linalg.norm(Y - Yo) <= 1e-5 * np.linalg.norm(Yo)
+    loss, g = dfx.mlp_loss_grad(widths, dev(th), dev(X), dev(T))
+    lo, go = L.loss_and_grad(th.astype(np.float64), widths, X.astype(np.float64), T.astype(np.float64))
+    assert abs(loss - lo) <= 1e-5 * lo
+    assert np.linalg.norm(g.cpu().numpy() - go) <= 1e-4 * np.linalg.norm(go)
+
+
 def test_mlp_adam_matches_oracle():
     import paper_1707_03771_amd as dfx
     rng = np.random.default_rng(5)
