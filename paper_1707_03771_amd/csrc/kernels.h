@@ -45,7 +45,8 @@ struct GemmF64 {
   int batch;
   bool ta, tb;     // op(A) = A^T, op(B) = B^T
   bool lowerA;     // A is lower triangular (skip zero k-blocks)
-  bool lowerC;     // only the lower triangle of C is needed (skip blocks above)
+  bool lowerC;     // only columns n <= m + lowerOff of C are needed (skip blocks above)
+  int lowerOff;
 };
 void dgemm(const GemmF64& g, hipStream_t st);
 // dgemm, with the k-range split over up to 8 partial products (work: ns M N

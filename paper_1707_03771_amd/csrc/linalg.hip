@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(GT, 2) dgemm_any_kernel(GemmF64 g) {
   const int MB = (g.M + GM - 1) / GM, NB = (g.N + GN - 1) / GN;
   const int t = xcd_tile(blockIdx.x, MB * NB);
   const int m0 = (t % MB) * GM, n0 = (t / MB) * GN;
-  if (g.lowerC && n0 > m0 + GM - 1) return;
+  if (g.lowerC && n0 > m0 + GM - 1 + g.lowerOff) return;
   const int z = blockIdx.z;
   const double* __restrict__ A = g.A + z * g.sA;
   const double* __restrict__ B = g.B + z * g.sB;
@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(GT, 2) dgemm_kernel(GemmF64 g) {
   const int MB = (g.M + TM - 1) / TM, NB = (g.N + TN - 1) / TN;
   const int t = xcd_tile(blockIdx.x, MB * NB);
   const int m0 = (t % MB) * TM, n0 = (t / MB) * TN;
-  if (g.lowerC && n0 > m0 + TM - 1) return;
+  if (g.lowerC && n0 > m0 + TM - 1 + g.lowerOff) return;
   const int z = blockIdx.z;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (w & 1) * (TM / 2), wn = (w >> 1) * (TN / 2);
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(64 * SG_W) dgemm_small_kernel(GemmF64 g) {
   const int MB = (g.M + SG_T - 1) / SG_T, NB = (g.N + SG_T - 1) / SG_T;
   const int t = xcd_tile(blockIdx.x, MB * NB);
   const int m0 = (t % MB) * SG_T, n0 = (t / MB) * SG_T;
-  if (g.lowerC && n0 > m0 + SG_T - 1) return;
+  if (g.lowerC && n0 > m0 + SG_T - 1 + g.lowerOff) return;
   const int z = blockIdx.z;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int kmax = g.K;
