@@ -259,6 +259,21 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
       std::vector<std::vector<double>> cq(16);
       for (int cls = 0; cls < 16; ++cls)
         for (size_t p = 0; p < cf[cls].size(); ++p) cq[cls].push_back(B->Qab[(size_t)cf[cls][p] * bas.nsh + cs[cls][p]]);
+      // sums over the launches: per pair and (centre, axis), per auxiliary shell the
+      // same as ket, and per auxiliary shell and axis as the moved shell of the metric
+      size_t pofs[16], kofs[5], npall = 0, nka = 0;
+      for (int cls = 0; cls < 16; ++cls) {
+        pofs[cls] = npall;
+        npall += cf[cls].size();
+      }
+      for (int l = 0; l <= 4; ++l) {
+        kofs[l] = nka;
+        nka += auxby[l].size();
+      }
+      DevMem pacc(8 * (6 * npall + 1)), kacc(8 * 6 * (size_t)axs.nsh), macc(8 * 3 * (size_t)axs.nsh);
+      fill_f64(pacc.as<double>(), 6 * npall, 0.0, st);
+      fill_f64(kacc.as<double>(), 6 * (size_t)axs.nsh, 0.0, st);
+      fill_f64(macc.as<double>(), 3 * (size_t)axs.nsh, 0.0, st);
       sp_3.begin();
       for (int cls = 0; cls < 16; ++cls) {
         if (cf[cls].empty()) continue;
@@ -297,24 +312,8 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
               grad3_dispatch(LA, LB, lc, w, ax, ga, grid, ps, ks, st);
             }
           DFX_HIP(hipGetLastError());
-          std::vector<double> h((size_t)per * 6);
-          DFX_HIP(hipMemcpyAsync(h.data(), part.p, 8 * h.size(), hipMemcpyDeviceToHost, st));
-          DFX_HIP(hipStreamSynchronize(st));
-          for (int w = 0; w < 2; ++w)
-            for (int ax = 0; ax < 3; ++ax) {
-              const double* base = h.data() + (int64_t)(w * 3 + ax) * per;
-              for (int gi = 0; gi < ng; ++gi) {
-                const double* pb = base + gi * ps;
-                for (unsigned y = 0; y < grid.y; ++y)
-                  for (int p = 0; p < e.npairs; ++p) {
-                    const int sh = w == 0 ? cf[cls][p] : cs[cls][p];
-                    g[3 * atb[sh] + ax] += pb[(int64_t)y * e.npairs + p];
-                  }
-                const double* kb = base + (int64_t)ng * ps + gi * ks;
-                for (int ci = 0; ci < e.nk; ++ci)
-                  for (unsigned x = 0; x < grid.x; ++x) g[3 * ata[auxby[lc][ci]] + ax] += kb[(int64_t)ci * grid.x + x];
-              }
-            }
+          grad_fold(part.as<double>(), 6, ng, e.npairs, (int)grid.y, e.nk, (int)grid.x, pacc.as<double>() + 6 * pofs[cls],
+                    kacc.as<double>() + 6 * kofs[lc], 6, st);
         }
       }
       sp_3.end();
@@ -350,21 +349,28 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
             grad2_dispatch(la, lc, ax, ga, grid, ps, ks, st);
           }
           DFX_HIP(hipGetLastError());
-          std::vector<double> h((size_t)per * 3);
-          DFX_HIP(hipMemcpyAsync(h.data(), part.p, 8 * h.size(), hipMemcpyDeviceToHost, st));
-          DFX_HIP(hipStreamSynchronize(st));
-          for (int ax = 0; ax < 3; ++ax) {
-            const double* base = h.data() + (int64_t)ax * per;
-            for (int gi = 0; gi < ng; ++gi) {
-              const double* pb = base + gi * ps;
-              for (unsigned y = 0; y < grid.y; ++y)
-                for (int p = 0; p < e.npairs; ++p) g[3 * ata[auxby[la][p]] + ax] += pb[(int64_t)y * e.npairs + p];
-              const double* kb = base + (int64_t)ng * ps + gi * ks;
-              for (int ci = 0; ci < e.nk; ++ci)
-                for (unsigned x = 0; x < grid.x; ++x) g[3 * ata[auxby[lc][ci]] + ax] += kb[(int64_t)ci * grid.x + x];
-            }
-          }
+          grad_fold(part.as<double>(), 3, ng, e.npairs, (int)grid.y, e.nk, (int)grid.x, macc.as<double>() + 3 * kofs[la],
+                    kacc.as<double>() + 6 * kofs[lc], 6, st);
         }
+      // all sums at once
+      std::vector<double> hp((size_t)6 * npall), hk((size_t)6 * axs.nsh), hm((size_t)3 * axs.nsh);
+      if (npall) DFX_HIP(hipMemcpyAsync(hp.data(), pacc.p, 8 * hp.size(), hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipMemcpyAsync(hk.data(), kacc.p, 8 * hk.size(), hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipMemcpyAsync(hm.data(), macc.p, 8 * hm.size(), hipMemcpyDeviceToHost, st));
+      DFX_HIP(hipStreamSynchronize(st));
+      for (int cls = 0; cls < 16; ++cls)
+        for (size_t p = 0; p < cf[cls].size(); ++p)
+          for (int ax = 0; ax < 3; ++ax) {
+            const double* v = hp.data() + 6 * (pofs[cls] + p);
+            g[3 * atb[cf[cls][p]] + ax] += v[ax];
+            g[3 * atb[cs[cls][p]] + ax] += v[3 + ax];
+          }
+      for (int l = 0; l <= 4; ++l)
+        for (size_t c = 0; c < auxby[l].size(); ++c)
+          for (int ax = 0; ax < 3; ++ax) {
+            const size_t k = kofs[l] + c;
+            g[3 * ata[auxby[l][c]] + ax] += hk[6 * k + ax] + hk[6 * k + 3 + ax] + hm[3 * k + ax];
+          }
       sp_2.end();
     }
     Gam.release();

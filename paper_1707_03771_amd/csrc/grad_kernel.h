@@ -274,6 +274,8 @@ void onee_grad_dispatch(int LA, int LB, OneEGradArgs g, const double* Dw, const 
                         double* wD, double* wW, hipStream_t st);
 void gam_pack(const double* T, const double* D, int nbf, const double* gam, const int* cmu, const int* cnu,
               int64_t ncols, int nq, double* out, int64_t ld, hipStream_t st);
+void grad_fold(const double* part, int nq, int ng, int np, int ny, int nk, int nx, double* pacc, double* kacc, int kst,
+               hipStream_t st);
 void rank1_sub2(double* M, const double* gam, int n, hipStream_t st);
 void transpose_sq(const double* A, double* B, int n, hipStream_t st);
 void scale_cols(const double* C, const double* eps, int n, int no, double* Ce, hipStream_t st);
