@@ -204,10 +204,12 @@ int dfx_B_free(dfx_B* b);
  * utilities"): J = sum_Q B_Q gamma_Q with gamma_Q = sum B_Q D (Eqs. 3a, 3b);
  * K = sum_Q X_Q X_Q^T with X_Q = B_Q C_occ (Eqs. 1a, 2a).
  *   dev_in     kind = DFX_COCC: C_occ [nbf][nocc]; DFX_DENSITY: D [nbf][nbf]
- *              (symmetric).  For a density, K = sum_Q B_Q D B_Q through the
- *              signed factorisation D = C+ C+^T - C- C-^T from D's
- *              eigenvectors (eigenvalues below 1e-14 of the largest dropped);
- *              that call synchronises the stream.
+ *              (symmetric).  For a density, K = sum_Q B_Q D B_Q through its
+ *              pivoted Cholesky factor, D = L L^T, where that reproduces D to
+ *              1e-14 of its largest element, else through the signed
+ *              factorisation D = C+ C+^T - C- C-^T from D's eigenvectors
+ *              (eigenvalues below 1e-14 of the largest dropped); that call
+ *              synchronises the stream.
  *   precision  DFX_FP64 | DFX_FP32 | DFX_BF16, for K.  J reads both words of B
  *              in every precision: it is bandwidth-bound, and from the hi word
  *              alone its error, amplified by the conditioning of the metric,

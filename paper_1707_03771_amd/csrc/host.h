@@ -97,7 +97,8 @@ struct DevCtx {
 };
 DevCtx& thread_ctx();
 
-// K from a symmetric density by signed eigen-factorisation (scf.hip); synchronous
+// K from a symmetric density by its pivoted Cholesky factor, or else by signed
+// eigen-factorisation (scf.hip); synchronous
 void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st);
 
 // learned starting guess (guess.cpp): predicted density, host [nbf][nbf]

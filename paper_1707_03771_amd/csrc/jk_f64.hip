@@ -1,11 +1,11 @@
 // Exchange build K = sum_Q (B_Q C)(B_Q C)^T (Eqs. 1a, 2a) in FP64 on gfx950
 // v_mfma_f64_16x16x4f64, with B_Q = hi + lo (two FP32 words per element).
 // Phase 1 (half transform) streams each packed 32x32 tile of B_Q once per
-// block of 64 or 128 rows as vector loads, transposing tiles of the upper
-// triangle in LDS, and multiplies it by all occupied columns of C at once.
-// Phase 2 is a split-K SYRK over the (Q, i) index into FP64 partial sums with
-// an XCD-aware tile map, reduced in a fixed order.  Both phases issue the
-// global loads of the next k-stage before the MFMAs of the current one.
+// block of 64 or 128 rows and multiplies it by all occupied columns of C at
+// once: kx64s_kernel up to 160 columns, from the kept tiles only, kx64_kernel
+// beyond.  Phase 2 is a split-K SYRK over the (Q, i) index, from memory straight
+// to LDS (gemm_dma.h), into FP64 partial sums with an XCD-aware tile map,
+// reduced in a fixed order.
 #include <algorithm>
 
 #include <string>

@@ -745,7 +745,14 @@ void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* h
 // columns to its right in LDS; the inverse takes 8 rows at a time, four threads
 // per column for the sums over the rows above, one for the 8 x 8 triangle.
 // Every element takes the same operations in the same order as when each column
-// updated all later ones in LDS with a thread per row, 168 us a block; so 45.
+// updated all later ones in LDS with a thread per row, 168 us a block; so 36 (42 with
+// the pivots broadcast through LDS and the original diagonal read inside the chain).
+// lane l's value, l wave-uniform: two scalar reads, where __shfl goes through LDS
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 constexpr int CB = 64;
 constexpr int CP = 8;  // panel
 __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k0, int kb,
@@ -756,6 +763,8 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k
   __shared__ double sum[CP][CB + 1];
   const int tid = threadIdx.x;
   double* __restrict__ Jb = J + (int64_t)k0 * n + k0;
+  // the smallest pivots, lane t's of column t: no memory in the chain
+  const double small = tid < kb ? 1e-14 * diag0[k0 + tid] : 0.0;
   // rows and columns past kb: the identity
   for (int e = tid; e < CB * CB; e += 256) {
     const int i = e / CB, c = e % CB;
@@ -770,12 +779,12 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k
       for (int c = 0; c < CP; ++c) v[c] = a[t][p + c];
 #pragma unroll
       for (int j = 0; j < CP; ++j) {
-        const double d = __shfl(v[j], p + j);
+        const double d = lane_f64(v[j], p + j);
         // a pivot that lost all but rounding noise of the original diagonal
         // counts as non-positive: the metric is not numerically positive definite
         double piv = 1.0;
         if (p + j < kb) {
-          if (!(d > 1e-14 * diag0[k0 + p + j])) {
+          if (!(d > lane_f64(small, p + j))) {
             if (t == 0 && *info == 0) *info = k0 + p + j + 1;
             piv = __builtin_nan("");
           } else {
@@ -784,22 +793,25 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k
         }
         v[j] = t == p + j ? piv : (t > p + j ? v[j] / piv : 0.0);
 #pragma unroll
-        for (int c = j + 1; c < CP; ++c) v[c] = fma(-v[j], __shfl(v[j], p + c), v[c]);
+        for (int c = j + 1; c < CP; ++c) v[c] = fma(-v[j], lane_f64(v[j], p + c), v[c]);
       }
 #pragma unroll
       for (int c = 0; c < CP; ++c)
         if (t >= p + c) a[t][p + c] = v[c];
     }
     __syncthreads();
-    // columns right of the panel: a_ic -= sum_j l_ij l_cj, j in order
-    const int r0 = p + CP, m = CB - r0;
-    for (int e = tid; e < m * m; e += 256) {
-      const int i = r0 + e / m, c = r0 + e % m;
-      if (c > i) continue;
-      double v = a[i][c];
+    // columns right of the panel: a_ic -= sum_j l_ij l_cj, j in order; four threads a row
+    const int r0 = p + CP, i = tid >> 2;
+    if (i >= r0) {
+      double l[CP];
 #pragma unroll
-      for (int j = 0; j < CP; ++j) v = fma(-a[i][p + j], a[c][p + j], v);
-      a[i][c] = v;
+      for (int j = 0; j < CP; ++j) l[j] = a[i][p + j];
+      for (int c = r0 + (tid & 3); c <= i; c += 4) {
+        double v = a[i][c];
+#pragma unroll
+        for (int j = 0; j < CP; ++j) v = fma(-l[j], a[c][p + j], v);
+        a[i][c] = v;
+      }
     }
     __syncthreads();
   }

@@ -1025,7 +1025,7 @@ constexpr int KD_CH = 512;  // columns per K build
 // K(D) for a symmetric density D.  A density of occupied orbitals is positive
 // semidefinite of low rank: its pivoted Cholesky factor L gives D = L L^T in as
 // many small launches as D has rank (C10H22, 250 functions, rank 41: 0.3 ms,
-// where the block Jacobi eigensolver takes 27 ms), and K = K(L).  The factor is
+// where the block Jacobi eigensolver takes some 5), and K = K(L).  The factor is
 // taken only if max |D - L L^T| <= 1e-14 max |D|, the threshold of the other route;
 // any other D (indefinite, unsymmetric, not finite) goes by its signed
 // eigen-factorisation: K(C+) - K(C-) with D = V diag(lambda) V^T, C+- = V_+-
