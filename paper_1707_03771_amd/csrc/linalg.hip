@@ -736,6 +736,13 @@ void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* h
   }
 }
 
+// lane l's value, l wave-uniform: two scalar reads, where __shfl goes through LDS
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // ---------------------------------------------------------------------------
 // Cholesky of one diagonal block (kb <= 64), plus its lower-triangular inverse.
 // A non-positive pivot records its global index + 1 in *info.  One workgroup and
@@ -747,12 +754,6 @@ void tile_split(const double* B, int n, int64_t ld, const int64_t* src, float* h
 // Every element takes the same operations in the same order as when each column
 // updated all later ones in LDS with a thread per row, 168 us a block; so 36 (42 with
 // the pivots broadcast through LDS and the original diagonal read inside the chain).
-// lane l's value, l wave-uniform: two scalar reads, where __shfl goes through LDS
-__device__ __forceinline__ double lane_f64(double v, int l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
 constexpr int CB = 64;
 constexpr int CP = 8;  // panel
 __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k0, int kb,
