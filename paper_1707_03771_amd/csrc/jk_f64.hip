@@ -517,7 +517,7 @@ static SyrkPlan syrk_plan(int n, int64_t kdim, int64_t most_slices) {
       const int64_t per_xcd = ns > 1 ? (int64_t)ntl * ns / 8 : (ntl + 7) / 8;
       const int64_t per_cu = (per_xcd + 31) / 32;
       const double stages = (double)((kdim + (int64_t)ns * S64 - 1) / ((int64_t)ns * S64));
-      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.75) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.62 : 0.78);
+      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.83) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.62 : 0.78);
       double t = (double)per_cu * (stages * (tm == 128 ? 4096.0 : 1024.0) / eff + 3000.0);
       if (ns > 1) t += 12000.0 + (double)ns * n * n * 8.0 / 5.0e12 * 2.4e9;
       if (!best.tm || t < tbest) {
