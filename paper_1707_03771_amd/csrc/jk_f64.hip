@@ -502,6 +502,9 @@ void k_reduce(const double* P, int ns, int nbf, double* K, bool accumulate, hipS
 // more workgroups on the CU; the workgroups are dealt to 32 CUs on each of 8
 // XCDs, so the CU with the most of them sets the time; every slice is written
 // and read again once, and more than one slice takes another launch (5 us).
+// Tiles of 64 read X through L2 twice as often, which begins to tell between 1200
+// functions (11.0 ms, no slower than 128) and 1354 and 1536 (22.9 and 22.6 ms in
+// tiles of 64, 22.2 and 20.7 of 128).
 // Before, 128-tiles and about 2048 workgroups at any size: nbf = 192, kdim =
 // 33920 (3 tiles, 688 slices): 72 us + 255 us for the sum.
 struct SyrkPlan {
@@ -517,7 +520,7 @@ static SyrkPlan syrk_plan(int n, int64_t kdim, int64_t most_slices) {
       const int64_t per_xcd = ns > 1 ? (int64_t)ntl * ns / 8 : (ntl + 7) / 8;
       const int64_t per_cu = (per_xcd + 31) / 32;
       const double stages = (double)((kdim + (int64_t)ns * S64 - 1) / ((int64_t)ns * S64));
-      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.83) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.62 : 0.78);
+      const double eff = tm == 128 ? (per_cu == 1 ? 0.6 : 0.83) : (per_cu == 1 ? 0.45 : per_cu == 2 ? 0.62 : n > 1300 ? 0.73 : 0.78);
       double t = (double)per_cu * (stages * (tm == 128 ? 4096.0 : 1024.0) / eff + 3000.0);
       if (ns > 1) t += 12000.0 + (double)ns * n * n * 8.0 / 5.0e12 * 2.4e9;
       if (!best.tm || t < tbest) {
