@@ -899,8 +899,8 @@ int dfx_jk(const dfx_B* bc, const double* dev_in, int kind, int nocc, int precis
     if (dev_J) need = std::max(need, j_work_bytes(nbf, b->naux, b->ncols_t));
     if (dev_K && kind == DFX_COCC) need = std::max(need, k_work_bytes(a, nocc));
     char* w = static_cast<char*>(b->ensure_work(need));
-    if (dev_J && kind == DFX_COCC) j_build_cocc(a, dev_in, nocc, dev_J, reinterpret_cast<double*>(w), st);
-    if (dev_J && kind == DFX_DENSITY) j_build(a, dev_in, dev_J, reinterpret_cast<double*>(w), st);
+    if (dev_J && kind == DFX_COCC) j_build_cocc(a, dev_in, nocc, dev_J, reinterpret_cast<double*>(w), b->work.n, st);
+    if (dev_J && kind == DFX_DENSITY) j_build(a, dev_in, dev_J, reinterpret_cast<double*>(w), b->work.n, st);
     if (dev_K && kind == DFX_COCC) k_build(a, dev_in, nocc, dev_K, w, st);
     if (dev_K && kind == DFX_DENSITY) k_from_density(a, dev_in, dev_K, st);
     DFX_HIP(hipGetLastError());

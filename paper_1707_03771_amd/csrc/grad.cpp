@@ -187,7 +187,7 @@ int dfx_rhf_grad(const dfx_geom* geom, const dfx_shell* shells, int nsh, const d
     gemm(n, n, nocc, Ce.as<double>(), nocc, false, Cd.as<double>(), nocc, true, Wm.as<double>(), n, 1.0);
     const JKArgs ja = B->jk_args(PREC_FP64);
     DevMem gam(8 * (size_t)naux), dvec(j_gamma_work_bytes(n, naux, B->ncols_t));
-    j_gamma(ja, D.as<double>(), gam.as<double>(), dvec.as<double>(), st);
+    j_gamma(ja, D.as<double>(), gam.as<double>(), dvec.as<double>(), dvec.n, st);
     dvec.release();
 
     // ---- Gam~ in raw's packed columns, b_Q = C^T X_Q, chunk by chunk of Q

@@ -7,6 +7,7 @@
 // B is stored as two FP32 words (hi, lo) per element in the packed 32x32 tile
 // layout (common.h).  The FP64 path reads hi + lo; the mixed path reads hi.
 #include <algorithm>
+#include <string>
 
 #include "kernels.h"
 
@@ -205,37 +206,48 @@ __global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict_
 // at least 32 Q, and the parts of J stay within 32 MB, so that their traffic is
 // small against B's.  Measured, gamma + J in one part each and cut: nbf = 192,
 // naux = 848: 78 + 320 and 29 + 24 us; 730 / 3106: 1.42 + 1.89 and 1.40 + 1.20 ms.
-struct JPlan {
-  int sg, tchunk, sb, qchunk;
-};
-static JPlan j_plan(int naux, int64_t ncols, int kept) {
-  JPlan p{};
-  const int all = (int)(ncols / TILE2), tiles = std::max(1, kept);
+// The scratch is reserved for every tile kept.  Rounding the parts to whole tiles and
+// functions is not monotone (36 tiles in 7 parts become 6, 33 stay 7), so with fewer
+// tiles the parts are limited by the rounded plan of all tiles: no more parts of
+// gamma than it has, and no more parts of J than its scratch holds of the kept
+// tiles.  Rounding only ever lowers the number of parts asked for.
+static JPlan j_cut(int naux, int64_t ncols, int tiles, int64_t sg_most, int64_t sb_most) {
   auto cut = [](int64_t want, int64_t have, int64_t most) {
     return (int)std::max<int64_t>(1, std::min<int64_t>((want + have - 1) / have, most));
   };
-  p.sg = cut(2048, (naux + JG_Q - 1) / JG_Q, tiles / 4);
+  JPlan p{};
+  p.sg = cut(2048, (naux + JG_Q - 1) / JG_Q, std::min<int64_t>(tiles / 4, sg_most));
   p.tchunk = (tiles + p.sg - 1) / p.sg;
   p.sg = (tiles + p.tchunk - 1) / p.tchunk;
-  // no more memory than with every tile kept
   const int64_t most = std::min<int64_t>(naux / 32, ((int64_t)4 << 20) / ncols);
-  p.sb = std::min<int>(cut(768, tiles, most), (int)((int64_t)cut(768, all, most) * all / tiles));
+  p.sb = cut(768, tiles, std::min(most, sb_most));
   p.qchunk = (naux + p.sb - 1) / p.sb;
   p.sb = (naux + p.qchunk - 1) / p.qchunk;
   return p;
 }
+JPlan j_plan(int naux, int64_t ncols, int kept) {
+  const int all = (int)(ncols / TILE2), tiles = std::max(1, kept);
+  const JPlan full = j_cut(naux, ncols, all, all, naux);
+  return tiles == all ? full : j_cut(naux, ncols, tiles, full.sg, (int64_t)full.sb * all / tiles);
+}
 
 static int64_t even4(int64_t n) { return (n + 3) & ~(int64_t)3; }
 
-// packed density (ncols), the parts of gamma (sg naux) and of J (sb ncols)
-size_t j_work_bytes(int nbf, int naux, int64_t ncols) {
-  const JPlan p = j_plan(naux, ncols, (int)(ncols / TILE2));
-  return sizeof(double) * (size_t)(ncols + even4((int64_t)p.sg * naux) + p.sb * ncols);
+// packed density (ncols) and the parts of gamma (sg naux)
+int64_t j_gamma_reach(const JPlan& p, int naux, int64_t ncols) { return ncols + (int64_t)p.sg * naux; }
+// the same and the parts of the kept tiles of J (sb kept TILE2)
+int64_t j_build_reach(const JPlan& p, int naux, int64_t ncols, int kept) {
+  return ncols + even4((int64_t)p.sg * naux) + (int64_t)p.sb * kept * TILE2;
 }
 
-// packed density and the parts of gamma
+// with every tile kept, which no other set reaches beyond (j_plan)
+size_t j_work_bytes(int nbf, int naux, int64_t ncols) {
+  const int all = (int)(ncols / TILE2);
+  return sizeof(double) * (size_t)j_build_reach(j_plan(naux, ncols, all), naux, ncols, all);
+}
+
 size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols) {
-  return sizeof(double) * (size_t)(ncols + (int64_t)j_plan(naux, ncols, (int)(ncols / TILE2)).sg * naux);
+  return sizeof(double) * (size_t)j_gamma_reach(j_plan(naux, ncols, (int)(ncols / TILE2)), naux, ncols);
 }
 
 // both words of B in every precision: J is bandwidth-bound, and with the hi
@@ -246,8 +258,16 @@ static void launch_gamma(const JKArgs& a, const JPlan& p, const double* dvec, do
                      a.naux, dvec, a.tiles, a.nt_kept, p.tchunk, gp);
 }
 
-void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStream_t st) {
+// the launches below write up to the plan's reach and no further
+static void check_reach(const char* what, int64_t reach, size_t work_bytes) {
+  if (sizeof(double) * (size_t)reach > work_bytes)
+    throw Error(DFX_ENOMEM, std::string(what) + ": needs " + std::to_string(sizeof(double) * (size_t)reach) +
+                                " bytes of scratch, " + std::to_string(work_bytes) + " passed in");
+}
+
+void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, size_t work_bytes, hipStream_t st) {
   const JPlan p = j_plan(a.naux, a.ncols, a.nt_kept);
+  check_reach("j_gamma", j_gamma_reach(p, a.naux, a.ncols), work_bytes);
   double* gp = work + a.ncols;
   if (a.nt_kept)
     hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
@@ -255,8 +275,13 @@ void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStr
   hipLaunchKernelGGL(j_gamma_sum_kernel, dim3((a.naux + 255) / 256), dim3(256), 0, st, gp, p.sg, a.naux, gam);
 }
 
-static void j_build_packed(const JKArgs& a, double* J, double* work, hipStream_t st) {
+static JPlan j_checked_plan(const JKArgs& a, size_t work_bytes) {
   const JPlan p = j_plan(a.naux, a.ncols, a.nt_kept);
+  check_reach("j_build", j_build_reach(p, a.naux, a.ncols, a.nt_kept), work_bytes);
+  return p;
+}
+
+static void j_build_packed(const JKArgs& a, const JPlan& p, double* J, double* work, hipStream_t st) {
   const unsigned tiles = (unsigned)(a.ncols / TILE2);
   double* gp = work + a.ncols;
   double* jp = gp + even4((int64_t)p.sg * a.naux);
@@ -267,16 +292,19 @@ static void j_build_packed(const JKArgs& a, double* J, double* work, hipStream_t
   hipLaunchKernelGGL(j_unpack_kernel, dim3(tiles), dim3(256), 0, st, jp, a.tpos, a.nt_kept, p.sb, a.nbf, J);
 }
 
-void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st) {
+void j_build(const JKArgs& a, const double* D, double* J, double* work, size_t work_bytes, hipStream_t st) {
+  const JPlan p = j_checked_plan(a, work_bytes);
   if (a.nt_kept)
     hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
-  j_build_packed(a, J, work, st);
+  j_build_packed(a, p, J, work, st);
 }
 
-void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, hipStream_t st) {
+void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, size_t work_bytes,
+                  hipStream_t st) {
+  const JPlan p = j_checked_plan(a, work_bytes);
   if (a.nt_kept)
     hipLaunchKernelGGL(pack_cocc_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, C, a.nbf, nocc, a.tiles, work);
-  j_build_packed(a, J, work, st);
+  j_build_packed(a, p, J, work, st);
 }
 
 // ---------------------------------------------------------------------------

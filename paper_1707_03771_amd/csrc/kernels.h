@@ -121,14 +121,25 @@ struct JKArgs {
   // even one auxiliary function per chunk does not fit.
   size_t ws_cap = 0;
 };
+// How the two passes of the Coulomb build are cut with `kept` of the tiles of B kept:
+// gamma in sg parts of tchunk tiles, J in sb parts of qchunk auxiliary functions
+struct JPlan {
+  int sg, tchunk, sb, qchunk;
+};
+JPlan j_plan(int naux, int64_t ncols, int kept);
+// doubles from the start of the work that a plan's gamma, and its J after it, reach to
+int64_t j_gamma_reach(const JPlan& p, int naux, int64_t ncols);
+int64_t j_build_reach(const JPlan& p, int naux, int64_t ncols, int kept);
 // bytes of work of the Coulomb builds below, for any set of kept tiles
 size_t j_work_bytes(int nbf, int naux, int64_t ncols);
-// J from a density, or from the occupied block C [nbf][nocc] (D = C C^T)
-void j_build(const JKArgs& a, const double* D, double* J, double* work, hipStream_t st);
-void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, hipStream_t st);
+// J from a density, or from the occupied block C [nbf][nocc] (D = C C^T); they throw
+// DFX_ENOMEM, launching nothing, where work_bytes is less than their plan needs
+void j_build(const JKArgs& a, const double* D, double* J, double* work, size_t work_bytes, hipStream_t st);
+void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, size_t work_bytes,
+                  hipStream_t st);
 // gamma_Q = sum B_Q,mu nu D_mu nu alone (Eq. 3a); work: j_gamma_work_bytes
 size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols);
-void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, hipStream_t st);
+void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, size_t work_bytes, hipStream_t st);
 // K from the occupied block C [nbf][nocc] (row-major); work >= k_work_bytes
 size_t k_work_bytes(const JKArgs& a, int nocc);
 // optional GPU timers around the two K phases (events are recorded on st)

@@ -1490,7 +1490,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       }
       void* w = B->ensure_work(need);
       sp_j.begin();
-      j_build(ja, D.as<double>(), Jm.as<double>(), reinterpret_cast<double*>(w), st);
+      j_build(ja, D.as<double>(), Jm.as<double>(), reinterpret_cast<double*>(w), B->work.n, st);
       sp_j.end();
       ktimer.x = &sp_kx[prec];
       ktimer.s = &sp_ks[prec];
@@ -1914,7 +1914,7 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
                                          k_work_bytes(ja, std::max(1, na)), k_work_bytes(ja, std::max(1, nb))}));
       hipLaunchKernelGGL(add_kernel, dim3(nblk(n2)), dim3(256), 0, st, D[0].as<double>(), D[1].as<double>(),
                          Dt.as<double>(), n2);
-      j_build(ja, Dt.as<double>(), J.as<double>(), reinterpret_cast<double*>(w), st);
+      j_build(ja, Dt.as<double>(), J.as<double>(), reinterpret_cast<double*>(w), B->work.n, st);
       double sum = 0.0;
       for (int s2 = 0; s2 < 2; ++s2) {
         if (nocc_s[s2] > 0)
