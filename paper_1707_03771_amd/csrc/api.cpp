@@ -901,7 +901,7 @@ int dfx_jk(const dfx_B* bc, const double* dev_in, int kind, int nocc, int precis
     char* w = static_cast<char*>(b->ensure_work(need));
     if (dev_J && kind == DFX_COCC) j_build_cocc(a, dev_in, nocc, dev_J, reinterpret_cast<double*>(w), b->work.n, st);
     if (dev_J && kind == DFX_DENSITY) j_build(a, dev_in, dev_J, reinterpret_cast<double*>(w), b->work.n, st);
-    if (dev_K && kind == DFX_COCC) k_build(a, dev_in, nocc, dev_K, w, st);
+    if (dev_K && kind == DFX_COCC) k_build(a, dev_in, nocc, dev_K, w, b->work.n, st);
     if (dev_K && kind == DFX_DENSITY) k_from_density(a, dev_in, dev_K, st);
     DFX_HIP(hipGetLastError());
   });

@@ -313,12 +313,27 @@ size_t k_work_bytes(const JKArgs& a, int nocc) {
   return a.prec == PREC_FP64 ? k_work_bytes_f64(a, nocc) : k_work_bytes_mixed(a, nocc);
 }
 
-void k_build(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
+void k_check_work(size_t need, size_t work_bytes) {
+  if (need > work_bytes)
+    throw Error(DFX_ENOMEM, "k_build: needs " + std::to_string(need) + " bytes of scratch, " +
+                                std::to_string(work_bytes) + " passed in");
+}
+
+size_t k_density_work_bytes(const JKArgs& a, size_t npos, size_t nneg) {
+  size_t most = 0;
+  for (size_t n : {npos, nneg}) {
+    if (n >= (size_t)KD_CH) most = std::max(most, k_work_bytes(a, KD_CH));
+    if (n % KD_CH) most = std::max(most, k_work_bytes(a, (int)(n % KD_CH)));
+  }
+  return most;
+}
+
+void k_build(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes, hipStream_t st,
              KTimer* timer) {
   if (a.prec == PREC_FP64)
-    k_build_f64(a, C, nocc, K, work, st, timer);
+    k_build_f64(a, C, nocc, K, work, work_bytes, st, timer);
   else
-    k_build_mixed(a, C, nocc, K, work, st, timer);
+    k_build_mixed(a, C, nocc, K, work, work_bytes, st, timer);
 }
 
 // ---------------------------------------------------------------------------

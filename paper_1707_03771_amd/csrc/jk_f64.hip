@@ -613,16 +613,16 @@ void half_transform_f64(const JKArgs& a, const double* C, int nocc, int q0, int 
   kx64_launch(a, nocc, q0, nq, Cp, X, ldx, st);
 }
 
-size_t k_work_bytes_f64(const JKArgs& a, int nocc) {
-  const F64Plan p = f64_plan(a, nocc);
-  return a256(p.x_bytes) + a256(p.p_bytes) + p.c_bytes + 256;
-}
+static size_t f64_work(const F64Plan& p) { return a256(p.x_bytes) + a256(p.p_bytes) + p.c_bytes + 256; }
 
-void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
-                 KTimer* timer) {
+size_t k_work_bytes_f64(const JKArgs& a, int nocc) { return f64_work(f64_plan(a, nocc)); }
+
+void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes,
+                 hipStream_t st, KTimer* timer) {
   const F64Plan p = f64_plan(a, nocc);
   const int ncb = (nocc + 63) / 64;
   if (ncb > 8) throw Error(-6, "k_build: more than 512 occupied orbitals");
+  k_check_work(f64_work(p), work_bytes);
   char* w = reinterpret_cast<char*>(work);
   double* X = reinterpret_cast<double*>(w);
   double* P = reinterpret_cast<double*>(w + a256(p.x_bytes));

@@ -374,18 +374,19 @@ static MixedPlan mixed_plan(const JKArgs& a, int nocc, size_t esize) {
   return p;
 }
 
+static size_t mixed_work(const MixedPlan& p) { return p.ct_bytes + p.x_bytes + p.p_bytes + 1024; }
+
 size_t k_work_bytes_mixed(const JKArgs& a, int nocc) {
-  const size_t es = a.prec == PREC_BF16 ? 2 : 4;
-  const MixedPlan p = mixed_plan(a, nocc, es);
-  return p.ct_bytes + p.x_bytes + p.p_bytes + 1024;
+  return mixed_work(mixed_plan(a, nocc, a.prec == PREC_BF16 ? 2 : 4));
 }
 
 template <class Tr>
-static void k_build_tr(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
-                       KTimer* timer) {
+static void k_build_tr(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes,
+                       hipStream_t st, KTimer* timer) {
   using E = typename Tr::E;
   const MixedPlan p = mixed_plan(a, nocc, sizeof(E));
   if (p.ncb > 8) throw Error(-6, "k_build: more than 512 occupied orbitals in reduced precision");
+  k_check_work(mixed_work(p), work_bytes);
   char* w = reinterpret_cast<char*>(work);
   E* Ct = reinterpret_cast<E*>(w);
   E* X = reinterpret_cast<E*>(w + ((p.ct_bytes + 255) & ~(size_t)255));
@@ -420,12 +421,12 @@ static void k_build_tr(const JKArgs& a, const double* C, int nocc, double* K, vo
   }
 }
 
-void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
-                   KTimer* timer) {
+void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes,
+                   hipStream_t st, KTimer* timer) {
   if (a.prec == PREC_BF16)
-    k_build_tr<Bf16Tr>(a, C, nocc, K, work, st, timer);
+    k_build_tr<Bf16Tr>(a, C, nocc, K, work, work_bytes, st, timer);
   else
-    k_build_tr<F32Tr>(a, C, nocc, K, work, st, timer);
+    k_build_tr<F32Tr>(a, C, nocc, K, work, work_bytes, st, timer);
 }
 
 }  // namespace dfx

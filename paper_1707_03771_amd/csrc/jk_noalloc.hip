@@ -69,7 +69,7 @@ int dfx_jk_noalloc(const dfx_B* b, const double* dev_C, int nocc, int precision,
     // J (Eqs. 3a, 3b) of D = C_occ C_occ^T
     if (dev_J) j_build_cocc(a, dev_C, nocc, dev_J, reinterpret_cast<double*>(w), NOALLOC_SCRATCH_BYTES, st);
     // K (Eqs. 1a, 2a) reuses the whole array: the stream orders it after J
-    if (dev_K) k_build(a, dev_C, nocc, dev_K, w, st);
+    if (dev_K) k_build(a, dev_C, nocc, dev_K, w, NOALLOC_SCRATCH_BYTES, st);
     DFX_HIP(hipGetLastError());
   });
 }

@@ -140,8 +140,15 @@ void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double*
 // gamma_Q = sum B_Q,mu nu D_mu nu alone (Eq. 3a); work: j_gamma_work_bytes
 size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols);
 void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, size_t work_bytes, hipStream_t st);
-// K from the occupied block C [nbf][nocc] (row-major); work >= k_work_bytes
+// K from the occupied block C [nbf][nocc] (row-major); throws DFX_ENOMEM, launching
+// nothing, where work_bytes < k_work_bytes(a, nocc).  Fewer columns can take more
+// work: the number of partial sums is the quickest one for the size, so work that
+// serves several counts is the largest over all of them.
 size_t k_work_bytes(const JKArgs& a, int nocc);
+// the largest over the builds of a density with npos positive and nneg negative
+// columns, each sign in chunks of KD_CH
+constexpr int KD_CH = 512;
+size_t k_density_work_bytes(const JKArgs& a, size_t npos, size_t nneg);
 // optional GPU timers around the two K phases (events are recorded on st)
 struct KTimer {
   virtual void begin_x() = 0;
@@ -150,7 +157,7 @@ struct KTimer {
   virtual void end_syrk() = 0;
   virtual ~KTimer() = default;
 };
-void k_build(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
+void k_build(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes, hipStream_t st,
              KTimer* timer = nullptr);
 // FP64 K (jk_f64.hip), dispatched by k_build for PREC_FP64
 size_t k_work_bytes_f64(const JKArgs& a, int nocc);
@@ -162,8 +169,10 @@ void half_transform_f64(const JKArgs& a, const double* C, int nocc, int q0, int 
 // DF-MP2 correlation energy from B and canonical orbitals (mp2.hip)
 double mp2_energy(const JKArgs& a, const double* C, int nmo, const double* eps, int nocc, int nfrozen,
                   hipStream_t st);
-void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
-                 KTimer* timer);
+// throws DFX_ENOMEM where the need of a plan of the exchange build exceeds the work passed in
+void k_check_work(size_t need, size_t work_bytes);
+void k_build_f64(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes,
+                 hipStream_t st, KTimer* timer);
 // K (+)= sum of the ns slices P (their lower triangles), both triangles written (jk_f64.hip)
 void k_reduce(const double* P, int ns, int nbf, double* K, bool accumulate, hipStream_t st);
 // C = A A^T (both triangles) for a row-major n x k A, even row stride lda,
@@ -172,8 +181,8 @@ size_t syrk_f64_work_elems(int n);
 void syrk_f64(const double* A, int64_t lda, int n, int64_t k, double* C, double* work, hipStream_t st);
 // reduced-precision K (jk_mixed.hip), dispatched by k_build for PREC_FP32 / PREC_BF16
 size_t k_work_bytes_mixed(const JKArgs& a, int nocc);
-void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* work, hipStream_t st,
-                   KTimer* timer);
+void k_build_mixed(const JKArgs& a, const double* C, int nocc, double* K, void* work, size_t work_bytes,
+                   hipStream_t st, KTimer* timer);
 // canonical packed rows [q1 - q0][ncols_p] (FP64) from the tiled storage;
 // toff[c] is the tile offset of packed column c
 // dense rows out[q1 - q0][nbf][nbf] (FP64 = hi + lo) from the tiled storage

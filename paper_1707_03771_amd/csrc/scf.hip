@@ -1020,8 +1020,6 @@ __global__ void pchol_cols_kernel(const double* __restrict__ Lc, int n, int c0, 
   C[e] = Lc[(int64_t)(c0 + j) * n + mu];
 }
 
-constexpr int KD_CH = 512;  // columns per K build
-
 // K(D) for a symmetric density D.  A density of occupied orbitals is positive
 // semidefinite of low rank: its pivoted Cholesky factor L gives D = L L^T in as
 // many small launches as D has rank (C10H22, 250 functions, rank 41: 0.3 ms,
@@ -1030,7 +1028,7 @@ constexpr int KD_CH = 512;  // columns per K build
 // any other D (indefinite, unsymmetric, not finite) goes by its signed
 // eigen-factorisation: K(C+) - K(C-) with D = V diag(lambda) V^T, C+- = V_+-
 // sqrt(|lambda_+-|), eigenvalues below 1e-14 max|lambda| dropped.  Columns go to
-// k_build in chunks of at most 512.  Synchronous.
+// k_build in chunks of at most KD_CH.  Synchronous.
 void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st) {
   const int n = a.nbf;
   const int64_t n2 = (int64_t)n * n;
@@ -1093,7 +1091,7 @@ void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st)
     pos.resize(rank);
   }
   DevMem Cs(8 * (size_t)n * KD_CH);
-  DevMem work(k_work_bytes(a, std::min(KD_CH, std::max(1, (int)std::max(pos.size(), neg.size())))));
+  DevMem work(std::max<size_t>(256, k_density_work_bytes(a, pos.size(), neg.size())));
   const bool one = neg.empty() && !pos.empty() && pos.size() <= (size_t)KD_CH;  // K is a single build
   if (!one) fill_f64(K, (size_t)n2, 0.0, st);
   for (int sign = 1; sign >= -1; sign -= 2) {
@@ -1114,10 +1112,10 @@ void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st)
         DFX_HIP(hipStreamSynchronize(st));  // the host vectors go out of scope
       }
       if (one) {
-        k_build(a, Cs.as<double>(), r, K, work.p, st);
+        k_build(a, Cs.as<double>(), r, K, work.p, work.n, st);
         continue;
       }
-      k_build(a, Cs.as<double>(), r, Kt.as<double>(), work.p, st);
+      k_build(a, Cs.as<double>(), r, Kt.as<double>(), work.p, work.n, st);
       Comb cb{};
       cb.m = 2;
       cb.F[0] = K;
@@ -1443,8 +1441,8 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
         JKArgs s64 = sub;
         s64.prec = PREC_FP64;
         void* ws = B->ensure_work(std::max(k_work_bytes(sub, nocc), k_work_bytes(s64, nocc)));
-        k_build(sub, Cocc.as<double>(), nocc, Km.as<double>(), ws, st, nullptr);
-        k_build(s64, Cocc.as<double>(), nocc, Jm.as<double>(), ws, st, nullptr);
+        k_build(sub, Cocc.as<double>(), nocc, Km.as<double>(), ws, B->work.n, st, nullptr);
+        k_build(s64, Cocc.as<double>(), nocc, Jm.as<double>(), ws, B->work.n, st, nullptr);
         Comb cd{};
         cd.m = 2;
         cd.F[0] = Km.as<double>();
@@ -1495,7 +1493,7 @@ int dfx_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh, const dfx_sh
       ktimer.x = &sp_kx[prec];
       ktimer.s = &sp_ks[prec];
       ++n_jk_p[prec];
-      k_build(ja, Cocc.as<double>(), nocc, Km.as<double>(), w, st, &ktimer);
+      k_build(ja, Cocc.as<double>(), nocc, Km.as<double>(), w, B->work.n, st, &ktimer);
       hipLaunchKernelGGL(fock_kernel, dim3(nblk(n2)), dim3(256), 0, st, h.as<double>(), Jm.as<double>(),
                          Km.as<double>(), F.as<double>(), n2);
       constexpr int NP2 = Scf::NPART / 2;  // the energy's partial sums and those of the error, fetched together
@@ -1918,7 +1916,7 @@ static int open_shell_scf(const dfx_geom* geom, const dfx_shell* shells, int nsh
       double sum = 0.0;
       for (int s2 = 0; s2 < 2; ++s2) {
         if (nocc_s[s2] > 0)
-          k_build(ja, Cocc[s2].as<double>(), nocc_s[s2], K[s2].as<double>(), w, st, nullptr);
+          k_build(ja, Cocc[s2].as<double>(), nocc_s[s2], K[s2].as<double>(), w, B->work.n, st, nullptr);
         else
           DFX_HIP(hipMemsetAsync(K[s2].p, 0, 8 * n2, st));
         hipLaunchKernelGGL(uhf_fock_kernel, dim3(nblk(n2)), dim3(256), 0, st, h.as<double>(), J.as<double>(),

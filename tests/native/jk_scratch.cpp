@@ -34,10 +34,40 @@ static long coulomb() {
   return seen;
 }
 
+// Exchange of a density: every pair of sign counts, as chunks of KD_CH columns, at sizes
+// around the tiles' edges and in all precisions
+static long exchange() {
+  long seen = 0, grows = 0;
+  for (int prec = PREC_FP64; prec <= PREC_BF16; ++prec)
+    for (int nbf : {1, 17, 31, 32, 33, 35, 45, 64, 65, 100, 127, 129, 200, 520, 700, 1100})
+      for (int naux : {1, 16, 40, 157, 202, 292, 600, 3 * nbf, 5 * nbf}) {
+        const JKArgs a{nullptr, nullptr, naux, nbf, tiled_cols(nbf), prec};
+        const int step = nbf <= 129 ? 1 : nbf / 40;
+        for (int np = 0; np <= nbf; np += step)
+          for (int nn = 0; np + nn <= nbf; nn += step, ++seen) {
+            if (np + nn == 0) continue;
+            const size_t have = k_density_work_bytes(a, np, nn);
+            for (int n : {np, nn})
+              for (int c0 = 0; c0 < n; c0 += KD_CH) {
+                const int r = std::min(KD_CH, n - c0);
+                const size_t need = k_work_bytes(a, r);
+                if (need > have) {
+                  std::printf("precision %d nbf %d naux %d: %d and %d columns reserve %zu bytes, %d need %zu\n", prec,
+                              nbf, naux, np, nn, have, r, need);
+                  std::exit(1);
+                }
+                grows += need > k_work_bytes(a, std::min(KD_CH, std::max(np, nn)));
+              }
+          }
+      }
+  return grows ? seen : 0;  // the case that the larger count does not cover is among them
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   long n = 0;
   if (!std::strcmp(what, "coulomb")) n = coulomb();
+  if (!std::strcmp(what, "exchange")) n = exchange();
   std::printf("%ld\n", n);
   return n > 0 ? 0 : 2;
 }

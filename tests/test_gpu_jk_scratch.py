@@ -88,3 +88,29 @@ def test_gradient_with_44_of_45_tiles(dfx):
     g0, _ = dfx.rhf_grad(xyz, Z, sh, ax, C, eps)
     g1, _ = dfx.rhf_grad(xyz, Z, [sh[s] for s in order], ax, C[rows], eps)
     assert np.abs(g0 - g1).max() <= 1e-8 * np.abs(g1).max()
+
+
+@pytest.mark.parametrize("prec,nbf,naux,npos,nneg,tol", [
+    (0, 100, 292, 47, 46, 1e-10), (0, 100, 292, 46, 47, 1e-10), (1, 65, 292, 29, 28, 1e-5),
+    (2, 65, 292, 29, 28, 2e-2), (0, 600, 40, 600, 0, 1e-10), (0, 600, 40, 520, 80, 1e-10)])
+def test_density_with_unequal_signs(dfx, prec, nbf, naux, npos, nneg, tol):
+    """K of an indefinite density whose smaller count of one sign takes more scratch than the
+    larger, and of densities of more than 512 columns.  FP64 as K of a density by its
+    eigenvectors elsewhere (1e-10), the others at what they reach against the oracle,
+    of the largest element of the positive part."""
+    sh = [systems.shell([0.9 * f, 0.1 * (f % 2), 0.0], 0, [0.9 + 0.001 * f]) for f in range(nbf)]
+    ax = [systems.shell([0.9 * nbf / naux * q, 0.0, 0.0], 0, [4.0 * (naux / nbf) ** 2]) for q in range(naux)]
+    B = dfx.eri3(sh, ax)
+    assert (B.nbf, B.naux) == (nbf, naux)
+    rows = B.unpack()
+    g = torch.Generator().manual_seed(11)
+    Q = torch.linalg.qr(torch.randn((nbf, nbf), generator=g, dtype=torch.float64))[0].cuda()
+    w = torch.zeros(nbf, dtype=torch.float64, device="cuda")
+    w[:npos] = torch.linspace(0.5, 2.0, npos, dtype=torch.float64)
+    w[npos:npos + nneg] = -torch.linspace(0.5, 1.5, nneg, dtype=torch.float64)
+    k_of = lambda w: torch.matmul(torch.matmul(rows, ((Q * w) @ Q.T).expand(naux, nbf, nbf)), rows).sum(0)  # noqa: E731
+    D = (Q * w) @ Q.T
+    K = dfx.jk(B, (D + D.T) / 2, kind=dfx.DENSITY, precision=prec, want_j=False)[1]
+    scale = max(1.0, k_of(w.clamp(min=0)).abs().max().item())
+    assert (K - k_of(w)).abs().max() <= tol * scale
+    B.free()

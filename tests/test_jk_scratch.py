@@ -29,3 +29,9 @@ def test_coulomb_plans_stay_inside_their_scratch(sweep):
     """With fewer tiles kept the rounded number of parts can be larger (33 of 36 tiles: 7
     parts of gamma, 36: 6), so a build must not be cut by rounding alone."""
     assert sweep("coulomb") > 1_000_000
+
+
+def test_density_exchange_scratch_holds_both_signs(sweep):
+    """A build of fewer columns can want more partial sums, so the scratch of an indefinite
+    density's two builds is not that of the larger count."""
+    assert sweep("exchange") > 100_000
