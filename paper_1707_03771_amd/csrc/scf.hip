@@ -1039,8 +1039,8 @@ void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st)
   const int nb = (n + PC_R - 1) / PC_R;
   int rank = -1;
   {
-    // pm, dmax0 and the reduction's 512 partial sums; pi and state
-    DevMem pd(8 * (size_t)(2 * nb + 1 + 512)), pn(sizeof(int) * (size_t)(2 * nb + 2));
+    // pm, dmax0 and four reductions' 512 partial results; pi and state
+    DevMem pd(8 * (size_t)(2 * nb + 1 + 4 * 512)), pn(sizeof(int) * (size_t)(2 * nb + 2));
     double *pm = pd.as<double>(), *dmax0 = pm + 2 * nb, *part = dmax0 + 1;
     int *pi = pn.as<int>(), *state = pi + 2 * nb;
     hipLaunchKernelGGL(pchol_init_kernel, dim3(nb), dim3(64), 0, st, D, n, lam.as<double>(), pm, pi, state);
@@ -1053,25 +1053,28 @@ void k_from_density(const JKArgs& a, const double* D, double* K, hipStream_t st)
       DFX_HIP(hipMemcpyAsync(h, state, sizeof h, hipMemcpyDeviceToHost, st));
       DFX_HIP(hipStreamSynchronize(st));
     }
-    // the residual D - L L^T against max |D|; |D|^2 shows whether D is finite (the
-    // maximum passes over NaN)
-    std::vector<double> hp(512);
-    auto partials = [&]() {
-      DFX_HIP(hipMemcpyAsync(hp.data(), part, 8 * 512, hipMemcpyDeviceToHost, st));
-      DFX_HIP(hipStreamSynchronize(st));
-    };
-    auto maxabs = [&](const double* A) {
-      hipLaunchKernelGGL(maxabs_partial_kernel, dim3(512), dim3(256), 0, st, A, n2, part);
-      partials();
-      return *std::max_element(hp.begin(), hp.end());
-    };
-    hipLaunchKernelGGL(dot_partial_kernel, dim3(512), dim3(256), 0, st, D, D, (const double*)nullptr, n2, part);
-    partials();
-    double norm2 = 0.0;
-    for (double x : hp) norm2 += x;
+    // the residual D - L L^T against max |D|.  The maximum passes over NaN, which the
+    // sums of squares do not: |D|^2 shows whether D is finite, and the residual's
+    // whether the factor is (rows of an indefinite D whose residual diagonal was cut
+    // off at zero can overflow while all others are reproduced)
     DFX_HIP(hipMemcpyAsync(Kt.p, D, 8 * n2, hipMemcpyDeviceToDevice, st));
     if (h[0] > 0) S.gemm(n, n, h[0], W.as<double>(), n, true, W.as<double>(), n, false, Kt.as<double>(), n, -1.0, 1.0);
-    if (std::isfinite(norm2) && maxabs(Kt.as<double>()) <= 1e-14 * maxabs(D)) rank = h[0];
+    const double* A[2] = {D, Kt.as<double>()};
+    for (int k = 0; k < 2; ++k) {
+      hipLaunchKernelGGL(dot_partial_kernel, dim3(512), dim3(256), 0, st, A[k], A[k], (const double*)nullptr, n2,
+                         part + 1024 * k);
+      hipLaunchKernelGGL(maxabs_partial_kernel, dim3(512), dim3(256), 0, st, A[k], n2, part + 1024 * k + 512);
+    }
+    std::vector<double> hp(4 * 512);
+    DFX_HIP(hipMemcpyAsync(hp.data(), part, 8 * hp.size(), hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    double norm2[2], most[2];
+    for (int k = 0; k < 2; ++k) {
+      const auto q = hp.begin() + 1024 * k;
+      norm2[k] = std::accumulate(q, q + 512, 0.0);
+      most[k] = *std::max_element(q + 512, q + 1024);
+    }
+    if (std::isfinite(norm2[0]) && std::isfinite(norm2[1]) && most[1] <= 1e-14 * most[0]) rank = h[0];
   }
   std::vector<int> pos, neg;
   std::vector<double> l;

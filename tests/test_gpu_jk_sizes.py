@@ -122,3 +122,18 @@ def test_cholesky_product_edges(dfx, n):
     tol = 8 * (n + 8) * 2.0 ** -53
     assert float((L @ L.T - A).abs().max()) <= tol * float(A.abs().max())
     assert float((Li @ L - torch.eye(n, dtype=torch.float64, device=dev)).abs().max()) <= tol * 6.0
+
+
+def test_factor_that_overflows_is_not_taken(dfx):
+    """An indefinite density on whose last row the Cholesky factor overflows to Inf and NaN
+    while it reproduces the other rows: K comes from the eigenvectors, as finite as D."""
+    n = 4
+    B, rows = _fit(dfx, n)
+    D = torch.diag(torch.tensor([1e-300, 3e-315, 2e-315, 0.0], dtype=torch.float64))
+    D[3, :3] = D[:3, 3] = 1e153
+    D = D.cuda()
+    K = dfx.jk(B, D, kind=dfx.DENSITY, want_j=False)[1]
+    ref = torch.matmul(torch.matmul(rows, D.expand(rows.shape[0], n, n)), rows).sum(0)
+    assert torch.isfinite(K).all()
+    assert (K - ref).abs().max() <= 1e-10 * ref.abs().max()
+    B.free()
