@@ -277,11 +277,13 @@ dfx::Eri3Need dfx::eri3_need(const HostShells& b, const HostShells& a, int flags
   const int64_t npall = nsh * (nsh + 1) / 2;
   z.bytes_B = 2 * pad256(4 * naux * nct);
   const int64_t nt = ntiles_for((int)nbf);
-  const int64_t tile_lists = pad256(8 * nt * ((nt + 63) / 64)) + 2 * pad256(4 * nct / TILE2);
+  z.lines = pad256(8 * naux * ((ncb + 15) / 16 * 16)) - raw;
+  z.stays = pad256(8 * nt * ((nt + 63) / 64)) + 2 * pad256(4 * nct / TILE2) + ((flags & DFX_KEEP_RAW) ? z.lines : 0);
+  z.beside = z.stays + z.lines + pad256(8 * naux);
   z.bytes_raw = raw;
   z.bytes_metric = 2 * m2;
   z.bottom = shells_bytes(b) + shells_bytes(a) + z.bytes_B + m2 + ((flags & DFX_KEEP_METRIC) ? m2 : 0) +
-             ((flags & DFX_KEEP_RAW) ? raw : 0) + tile_lists;
+             ((flags & DFX_KEEP_RAW) ? raw : 0);
   const int64_t lists = 16 * npall + 25 * npall + 20 * nauxsh + 256 * 256;
   // raw itself, or its working copy when raw is kept; L when not kept; the
   // Cholesky work (also the solve's packed diagonal blocks) and the tile map
@@ -289,9 +291,7 @@ dfx::Eri3Need dfx::eri3_need(const HostShells& b, const HostShells& a, int flags
             pad256(8 * (int64_t)cholesky_work_elems((int)naux)) + 256 + std::max(2 * pad256(8 * ncb), pad256(8 * nct));
   z.jk = jk_need((int)nbf, (int)naux, nct);
   const int64_t top = std::max(z.setup, z.jk + pad256(8 * ncb));
-  // 16 MB for fragmentation, which the tile lists come out of
-  z.total = z.bottom + top + top / 64 + ((int64_t)16 << 20) - tile_lists;
-  z.tile_lists = tile_lists;
+  z.total = z.bottom + top + ws_reserve(top, z.beside, (int64_t)16 << 20);
   return z;
 }
 
@@ -306,7 +306,7 @@ int64_t dfx::scf_need(const HostShells& b, const HostShells& a, int natom, int d
   const int64_t guess = (int64_t)natom * natom * 4 * 9842 + ((int64_t)1 << 20);
   const int64_t pre = 4 * n2 + 3 * 256;  // split-K partials and small buffers made before B
   const int64_t top = std::max(e.setup + pre, mats + guess + e.jk);
-  return e.bottom + top + top / 64 + ((int64_t)16 << 20) - e.tile_lists;
+  return e.bottom + top + ws_reserve(top, e.beside, (int64_t)16 << 20);
 }
 
 void* dfx_B::ensure_work(size_t bytes) {
@@ -792,7 +792,7 @@ int dfx_eri3_plan(const dfx_shell* shells, int nsh, const dfx_shell* aux, int na
     z.bytes_B = n.bytes_B;
     z.bytes_raw = n.bytes_raw;
     z.bytes_metric = n.bytes_metric;
-    z.bytes_persistent = n.bottom;
+    z.bytes_persistent = n.bottom + n.stays;
     z.bytes_jk = n.jk;
     z.bytes_workspace = n.total;
     *out = z;

@@ -106,7 +106,11 @@ int64_t grad_need(const HostShells& b, const HostShells& a, int natom, int nocc)
   // one-electron: Cartesian weights (two arrays) and partial sums
   w += 2 * p(8 * npall * 100) + p(8 * 6 * npall) + p(8 * (npall / 64 + 16) * natom * 3) + 64 * 256;
   const int64_t top = std::max(e.setup, w);
-  return e.bottom + top + top / 64 + ((int64_t)32 << 20) - e.tile_lists;
+  // beside them, the padding of Gam's rows and the derivatives' sums per auxiliary
+  // shell; their sums per pair, 48 bytes each, are gone before the one-electron
+  // weights, 1600 bytes each above, are laid out
+  const int64_t beside = e.beside + e.lines + p(48 * (int64_t)a.nsh) + p(24 * (int64_t)a.nsh);
+  return e.bottom + top + ws_reserve(top, beside, (int64_t)32 << 20);
 }
 
 }  // namespace dfx

@@ -206,9 +206,19 @@ struct Eri3Need {
   int64_t bottom;  // outlives the call: shells, B (hi, lo), J_PQ slot, kept metric / raw
   int64_t setup;   // released before the call returns
   int64_t jk;      // largest dfx_jk work on the result
-  int64_t tile_lists;  // of bottom: the lists of kept tiles
-  int64_t total;   // bottom + max(setup, jk + export map) + fragmentation slack
+  // in neither: the lists of kept tiles, L's diagonal, and what rows of whole 128-byte
+  // lines take beyond raw and a kept raw's copy
+  int64_t lines;   // the last, for one raw
+  int64_t beside;  // all of it
+  int64_t stays;   // what of it outlives the call
+  int64_t total;   // bottom + max(setup, jk + export map) + reserve
 };
+// What a workspace keeps beyond the arrays counted one by one: for the arena's
+// fragmentation, and at most half of it for `beside` bytes of small ones.  Counting
+// these outright would raise the sizes for which a workspace is already laid out.
+inline int64_t ws_reserve(int64_t top, int64_t beside, int64_t least) {
+  return std::max(top / 64 + least, 2 * beside);
+}
 Eri3Need eri3_need(const HostShells& b, const HostShells& a, int flags);
 int64_t jk_need(int nbf, int naux, int64_t ncols_t);
 // device bytes of dfx_scf / dfx_uhf / dfx_rohf inside a caller's workspace

@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "host.h"
 #include "kernels.h"
 
 using namespace dfx;
@@ -63,11 +64,42 @@ static long exchange() {
   return grows ? seen : 0;  // the case that the larger count does not cover is among them
 }
 
+// Workspace of a fit: the raw rows in whole lines, the lists of kept tiles and L's diagonal
+// have their place beside the arrays counted one by one, and leave half of the reserve
+static long fit() {
+  long seen = 0;
+  for (int nbf : {1, 2, 3, 33, 66, 67, 300, 2002})
+    for (int naux : {1, 7, 250, 5001})
+      for (int flags : {0, DFX_KEEP_RAW, DFX_KEEP_METRIC, DFX_KEEP_RAW | DFX_KEEP_METRIC}) {
+        HostShells b, a;
+        b.nsh = b.nbf = nbf;
+        a.nsh = a.nbf = naux;
+        b.l.assign(nbf, 0);
+        a.l.assign(naux, 0);
+        const Eri3Need z = eri3_need(b, a, flags);
+        const int64_t nc = (int64_t)nbf * (nbf + 1) / 2, row = (nc + 15) / 16 * 16, nt = ntiles_for(nbf);
+        const int64_t raw = 8 * naux * row;  // no pair screened
+        const int64_t lists = 8 * nt * ((nt + 63) / 64) + 8 * tiled_cols(nbf) / TILE2;
+        const bool kept = flags & DFX_KEEP_RAW;
+        const int64_t reserve = z.total - z.bottom - std::max(z.setup, z.jk + 8 * nc);
+        if (z.bytes_raw + z.lines < raw || z.stays < lists + (kept ? raw - z.bytes_raw : 0) ||
+            z.beside < z.stays + (raw - z.bytes_raw) + 8 * naux || reserve < 2 * z.beside ||
+            reserve < (int64_t)16 << 20) {
+          std::printf("nbf %d naux %d flags %d: beside %lld reserve %lld\n", nbf, naux, flags, (long long)z.beside,
+                      (long long)reserve);
+          std::exit(1);
+        }
+        ++seen;
+      }
+  return seen;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   long n = 0;
   if (!std::strcmp(what, "coulomb")) n = coulomb();
   if (!std::strcmp(what, "exchange")) n = exchange();
+  if (!std::strcmp(what, "fit")) n = fit();
   std::printf("%ld\n", n);
   return n > 0 ? 0 : 2;
 }

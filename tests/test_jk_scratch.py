@@ -35,3 +35,8 @@ def test_density_exchange_scratch_holds_both_signs(sweep):
     """A build of fewer columns can want more partial sums, so the scratch of an indefinite
     density's two builds is not that of the larger count."""
     assert sweep("exchange") > 100_000
+
+
+def test_fit_workspace_counts_padded_rows_and_lists(sweep):
+    """Raw's rows are whole 128-byte lines, so up to 15 doubles longer than its columns."""
+    assert sweep("fit") == 128
