@@ -564,31 +564,8 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     diag_f64(Lp, naux, dg.as<double>(), st);
     tc.stop();
 
-    // B = L^-1 raw by blocked forward substitution, in place (on a copy when the
-    // raw integrals are kept), then split into the two FP32 words.  The timed
-    // span holds these launches and nothing else; the update products are also
-    // timed on their own.
-    DevMem rawcopy;
-    double* Bw = B->raw.as<double>();
-    if (flags & DFX_KEEP_RAW) {
-      rawcopy.alloc(B->raw.n);
-      DFX_HIP(hipMemcpyAsync(rawcopy.p, B->raw.p, B->raw.n, hipMemcpyDeviceToDevice, st));
-      Bw = rawcopy.as<double>();
-    }
-    struct UpdTimer : TrsmTimer {
-      EventSpans sp;
-      void begin() override { sp.begin(); }
-      void end() override { sp.end(); }
-    } ut;
-    ut.sp.st = st;
-    GpuTimer tt(st);
-    tt.start();
-    // the Cholesky work (at least 65 naux doubles) holds the packed diagonal blocks
-    if (cw.n < sizeof(double) * trsm_work_elems(naux)) throw Error(-1, "eri3: Cholesky work too small for the solve");
-    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, B->ldr, cw.as<double>(), st, &ut);
-
-    // -- host work that nothing on the GPU waits for yet, done while it integrates,
-    // factors and solves: the counts of kept triplets, the export map, the tile map.
+    // -- host work that nothing on the GPU waits for yet, done while it integrates and
+    // factors: the counts of kept triplets, the export map, the tile map.
     std::vector<std::vector<double>> qc_by_l(5);
     for (int c = 0; c < nauxsh; ++c) qc_by_l[B->aux.l[c]].push_back(B->QC[c]);
     for (auto& v : qc_by_l) std::sort(v.begin(), v.end());
@@ -666,6 +643,37 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
       B->nt_kept = (int)tiles.size();
     }
 
+    // a metric that is not positive definite ends the call here, before its NaNs are
+    // solved with; the integrals and the factor have been at work on the GPU until now
+    int info = 0;
+    DFX_HIP(hipMemcpyAsync(&info, info_d.p, sizeof(int), hipMemcpyDeviceToHost, st));
+    DFX_HIP(hipStreamSynchronize(st));
+    if (info != 0)
+      throw Error(DFX_ENOTPOSDEF, "fitting metric is not positive definite (pivot " + std::to_string(info - 1) + ")");
+
+    // B = L^-1 raw by blocked forward substitution, in place (on a copy when the
+    // raw integrals are kept), then split into the two FP32 words.  The timed
+    // span holds these launches and nothing else; the update products are also
+    // timed on their own.
+    DevMem rawcopy;
+    double* Bw = B->raw.as<double>();
+    if (flags & DFX_KEEP_RAW) {
+      rawcopy.alloc(B->raw.n);
+      DFX_HIP(hipMemcpyAsync(rawcopy.p, B->raw.p, B->raw.n, hipMemcpyDeviceToDevice, st));
+      Bw = rawcopy.as<double>();
+    }
+    struct UpdTimer : TrsmTimer {
+      EventSpans sp;
+      void begin() override { sp.begin(); }
+      void end() override { sp.end(); }
+    } ut;
+    ut.sp.st = st;
+    GpuTimer tt(st);
+    tt.start();
+    // the Cholesky work (at least 65 naux doubles) holds the packed diagonal blocks
+    if (cw.n < sizeof(double) * trsm_work_elems(naux)) throw Error(-1, "eri3: Cholesky work too small for the solve");
+    const TrsmStats ts = trsm_solve(Lp, naux, Bw, B->ncols_p, B->ldr, cw.as<double>(), st, &ut);
+
     DevMem src_d = upload(src, st);
     DFX_HIP(hipMemcpyAsync(B->tmask.p, mask.data(), sizeof(mask[0]) * mask.size(), hipMemcpyHostToDevice, st));
     DFX_HIP(hipMemcpyAsync(B->tpos.p, tpos.data(), sizeof(int) * tpos.size(), hipMemcpyHostToDevice, st));
@@ -674,15 +682,8 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
     tile_split(Bw, naux, B->ldr, src_d.as<int64_t>(), B->hi.as<float>(), B->lo.as<float>(), B->ncols_t, st);
     DFX_HIP(hipGetLastError());
     tt.stop();
-    // a metric that is not positive definite has made B of NaNs by now; it is
-    // reported here and B dropped
-    int info = 0;
-    DFX_HIP(hipMemcpyAsync(&info, info_d.p, sizeof(int), hipMemcpyDeviceToHost, st));
-    DFX_HIP(hipStreamSynchronize(st));
     B->info.eri_seconds = te.seconds();
     B->info.metric_seconds = t_metric0 + tc.seconds();
-    if (info != 0)
-      throw Error(DFX_ENOTPOSDEF, "fitting metric is not positive definite (pivot " + std::to_string(info - 1) + ")");
     {
       std::vector<double> diag(naux);
       DFX_HIP(hipMemcpyAsync(diag.data(), dg.p, sizeof(double) * naux, hipMemcpyDeviceToHost, st));
