@@ -25,13 +25,37 @@ __device__ __forceinline__ void tile_ij(int t, int& I, int& J) {
   J = t - i * (i + 1) / 2;
 }
 
-// weighted density in the tile layout (the kept tiles): off-diagonal tiles count twice
-__global__ void pack_density_kernel(const double* __restrict__ D, int nbf, const int* __restrict__ tiles,
-                                    double* __restrict__ d) {
-  const int t = tiles[blockIdx.x];
+// A tile without a kept pair is skipped where B is streamed, but zero times Inf or NaN is
+// NaN: what such a tile of D or of J owes a non-finite input is z = sum 0 x over the
+// values x that meet its zeros, 0 or NaN.  The kernels below take ALL where every tile is
+// kept and there is none of it.  The sum of all threads' z (256), in all threads.
+__device__ __forceinline__ double wg_zsum(double z) {
+  __shared__ double r[4];
+  for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
+  if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = z;
+  __syncthreads();
+  return r[0] + r[1] + r[2] + r[3];
+}
+
+// weighted density in the tile layout, off-diagonal tiles counted twice; of a tile that is not
+// kept, z of its elements in the place of the first
+template <bool ALL>
+__global__ void __launch_bounds__(256) pack_density_kernel(const double* __restrict__ D, int nbf,
+                                                           const int* __restrict__ tpos, double* __restrict__ d) {
+  const int t = blockIdx.x;
   int I, J;
   tile_ij(t, I, J);
   const double w = (I == J) ? 1.0 : 2.0;
+  if (!ALL && tpos[t] < 0) {
+    double z = 0.0;
+    for (int e = threadIdx.x; e < TILE2; e += 256) {
+      const int r = I * TILE + (e >> 5), c = J * TILE + (e & 31);
+      if (r < nbf && c < nbf) z = fma(0.0, D[(int64_t)r * nbf + c], z);
+    }
+    z = wg_zsum(z);
+    if (threadIdx.x == 0) d[(int64_t)t * TILE2] = z;
+    return;
+  }
   for (int e = threadIdx.x; e < TILE2; e += blockDim.x) {
     const int r = I * TILE + (e >> 5), c = J * TILE + (e & 31);
     d[(int64_t)t * TILE2 + e] = (r < nbf && c < nbf) ? w * D[(int64_t)r * nbf + c] : 0.0;
@@ -43,9 +67,10 @@ __global__ void pack_density_kernel(const double* __restrict__ D, int nbf, const
 // from C (a few hundred KB, in L2).  Replaces a DGEMM for D (4 to 36 tiles of
 // 128 x 128 at nbf = 192 to 730: 21 to 30 us on a mostly idle chip) and the
 // packing pass after it; 4 us at nbf = 192, nocc = 40.
+template <bool ALL>
 __global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict__ C, int nbf, int nocc,
-                                                        const int* __restrict__ tiles, double* __restrict__ d) {
-  const int t = tiles[blockIdx.x];
+                                                        const int* __restrict__ tpos, double* __restrict__ d) {
+  const int t = blockIdx.x;
   int I, J;
   tile_ij(t, I, J);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -62,6 +87,14 @@ __global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict
     const double b = in && c < nbf ? pc[k + lk] : 0.0;
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
   }
+  if (!ALL && tpos[t] < 0) {
+    double z = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) z = fma(0.0, acc[q], z);
+    z = wg_zsum(z);
+    if (threadIdx.x == 0) d[(int64_t)t * TILE2] = z;
+    return;
+  }
   const double wt = (I == J) ? 1.0 : 2.0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) d[(int64_t)t * TILE2 + (r0 + 4 * q + lk) * TILE + c0 + li] = wt * acc[q];
@@ -74,17 +107,23 @@ __global__ void __launch_bounds__(256) pack_cocc_kernel(const double* __restrict
 // sum, which the readers of gamma add in order (j_plan: enough workgroups to
 // fill the chip where naux / JG_Q alone does not).
 constexpr int JG_Q = 4;
+template <bool ALL>
 __global__ void __launch_bounds__(256) j_gamma_kernel(const float* __restrict__ hi,
                                                       const float* __restrict__ lo, int64_t ncols, int naux,
                                                       const double* __restrict__ d,
                                                       const int* __restrict__ tiles, int nt_kept, int tchunk,
-                                                      double* __restrict__ gp) {
+                                                      const int* __restrict__ tpos, double* __restrict__ gp) {
   const int Q0 = blockIdx.x * JG_Q;
   const int nq = min(JG_Q, naux - Q0);
   const int t0 = blockIdx.y * tchunk, t1 = min(t0 + tchunk, nt_kept);
   double s[JG_Q];
 #pragma unroll
   for (int k = 0; k < JG_Q; ++k) s[k] = 0.0;
+  // z of the tiles that are not kept (pack_density_kernel), to one element: through it
+  // every element of J takes it
+  if (!ALL && blockIdx.x == 0 && blockIdx.y == 0)
+    for (int t = threadIdx.x; t < (int)(ncols / TILE2); t += 256)
+      if (tpos[t] < 0) s[0] += d[(int64_t)t * TILE2];
   for (int t = t0; t < t1; ++t) {
     const int64_t c = (int64_t)tiles[t] * TILE2 + 4 * threadIdx.x;
     const double4 dd = *reinterpret_cast<const double4*>(d + c);
@@ -161,11 +200,12 @@ __global__ void __launch_bounds__(256) j_back_kernel(const float* __restrict__ h
 }
 
 // the sb parts of the kept tiles of J, added in order -> dense symmetric matrix
-// (zero where no tile was kept), one workgroup per tile; the mirror image goes out through LDS so that
-// both copies are stored as rows
+// (where no tile was kept, zero times gamma), one workgroup per tile; the mirror image
+// goes out through LDS so that both copies are stored as rows
+template <bool ALL>
 __global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict__ jp, const int* __restrict__ tpos,
-                                                       int nt_kept, int sb, int nbf,
-                                                       double* __restrict__ M) {
+                                                       int nt_kept, int sb, int nbf, const double* __restrict__ gp,
+                                                       int ngp, double* __restrict__ M) {
   __shared__ double tl[TILE][TILE + 1];
   int I, J;
   tile_ij(blockIdx.x, I, J);
@@ -175,6 +215,14 @@ __global__ void __launch_bounds__(256) j_unpack_kernel(const double* __restrict_
   const double* __restrict__ src = jp + (int64_t)(pos < 0 ? 0 : pos) * TILE2 + 4 * threadIdx.x;
   const int parts = pos < 0 ? 0 : sb;
   double s[4] = {0.0, 0.0, 0.0, 0.0};
+  if (!ALL && pos < 0) {
+    double z = 0.0;
+#pragma unroll 16
+    for (int i = threadIdx.x; i < ngp; i += 256) z = fma(0.0, gp[i], z);
+    z = wg_zsum(z);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = z;
+  }
 #pragma unroll 8
   for (int k = 0; k < parts; ++k) {
     const double4 v = *reinterpret_cast<const double4*>(src + (int64_t)k * nt_kept * TILE2);
@@ -250,12 +298,20 @@ size_t j_gamma_work_bytes(int nbf, int naux, int64_t ncols) {
   return sizeof(double) * (size_t)j_gamma_reach(j_plan(naux, ncols, (int)(ncols / TILE2)), naux, ncols);
 }
 
+static bool all_kept(const JKArgs& a) { return (int64_t)a.nt_kept * TILE2 == a.ncols; }
+
+static void pack_density(const JKArgs& a, const double* D, double* d, hipStream_t st) {
+  hipLaunchKernelGGL(all_kept(a) ? pack_density_kernel<true> : pack_density_kernel<false>,
+                     dim3((unsigned)(a.ncols / TILE2)), dim3(256), 0, st, D, a.nbf, a.tpos, d);
+}
+
 // both words of B in every precision: J is bandwidth-bound, and with the hi
 // word alone its error (amplified by the conditioning of the metric) exceeds
 // that of a reduced-precision K
 static void launch_gamma(const JKArgs& a, const JPlan& p, const double* dvec, double* gp, hipStream_t st) {
-  hipLaunchKernelGGL(j_gamma_kernel, dim3((a.naux + JG_Q - 1) / JG_Q, p.sg), dim3(256), 0, st, a.hi, a.lo, a.ncols,
-                     a.naux, dvec, a.tiles, a.nt_kept, p.tchunk, gp);
+  hipLaunchKernelGGL(all_kept(a) ? j_gamma_kernel<true> : j_gamma_kernel<false>,
+                     dim3((a.naux + JG_Q - 1) / JG_Q, p.sg), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, dvec,
+                     a.tiles, a.nt_kept, p.tchunk, a.tpos, gp);
 }
 
 // the launches below write up to the plan's reach and no further
@@ -269,8 +325,7 @@ void j_gamma(const JKArgs& a, const double* D, double* gam, double* work, size_t
   const JPlan p = j_plan(a.naux, a.ncols, a.nt_kept);
   check_reach("j_gamma", j_gamma_reach(p, a.naux, a.ncols), work_bytes);
   double* gp = work + a.ncols;
-  if (a.nt_kept)
-    hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
+  pack_density(a, D, work, st);
   launch_gamma(a, p, work, gp, st);
   hipLaunchKernelGGL(j_gamma_sum_kernel, dim3((a.naux + 255) / 256), dim3(256), 0, st, gp, p.sg, a.naux, gam);
 }
@@ -289,21 +344,21 @@ static void j_build_packed(const JKArgs& a, const JPlan& p, double* J, double* w
   if (a.nt_kept)
     hipLaunchKernelGGL(j_back_kernel, dim3(a.nt_kept, p.sb), dim3(256), 0, st, a.hi, a.lo, a.ncols, a.naux, a.tiles,
                        gp, p.sg, p.qchunk, jp);
-  hipLaunchKernelGGL(j_unpack_kernel, dim3(tiles), dim3(256), 0, st, jp, a.tpos, a.nt_kept, p.sb, a.nbf, J);
+  hipLaunchKernelGGL(all_kept(a) ? j_unpack_kernel<true> : j_unpack_kernel<false>, dim3(tiles), dim3(256), 0, st, jp,
+                     a.tpos, a.nt_kept, p.sb, a.nbf, gp, p.sg * a.naux, J);
 }
 
 void j_build(const JKArgs& a, const double* D, double* J, double* work, size_t work_bytes, hipStream_t st) {
   const JPlan p = j_checked_plan(a, work_bytes);
-  if (a.nt_kept)
-    hipLaunchKernelGGL(pack_density_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, D, a.nbf, a.tiles, work);
+  pack_density(a, D, work, st);
   j_build_packed(a, p, J, work, st);
 }
 
 void j_build_cocc(const JKArgs& a, const double* C, int nocc, double* J, double* work, size_t work_bytes,
                   hipStream_t st) {
   const JPlan p = j_checked_plan(a, work_bytes);
-  if (a.nt_kept)
-    hipLaunchKernelGGL(pack_cocc_kernel, dim3((unsigned)a.nt_kept), dim3(256), 0, st, C, a.nbf, nocc, a.tiles, work);
+  hipLaunchKernelGGL(all_kept(a) ? pack_cocc_kernel<true> : pack_cocc_kernel<false>, dim3((unsigned)(a.ncols / TILE2)),
+                     dim3(256), 0, st, C, a.nbf, nocc, a.tpos, work);
   j_build_packed(a, p, J, work, st);
 }
 

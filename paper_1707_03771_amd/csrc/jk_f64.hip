@@ -178,14 +178,29 @@ __global__ void __launch_bounds__(KX_T) kx64_kernel(const float* __restrict__ hi
 // 16-column blocks swapped in pairs when NB is even, so that fragment reads
 // spread over the banks), B's words come by buffer loads at scalar bases, and
 // what is left is their conversion, in one place per stage.
+// A column of C with an Inf or NaN is NaN throughout in the copy: skipping a tile's zeros
+// must not lose it, as zero times either is NaN.
 constexpr int KS_T = 256;
-__global__ void cpad16_kernel(const double* __restrict__ C, int nbf, int nocc, int nbfp, int np,
-                              double* __restrict__ Cp) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)nbfp * np) return;
-  const int nu = (int)(idx / np), c = (int)(idx % np);
-  const int i = (nu & 1) && np % 32 == 0 ? c ^ 16 : c;
-  Cp[idx] = (nu < nbf && i < nocc) ? C[(int64_t)nu * nocc + i] : 0.0;
+// One workgroup per 64 rows and 16 columns of the copy; every one reads its columns whole
+// (some 1000 rows by 64 at a time: a few loads in flight each, from L2).
+__global__ void __launch_bounds__(1024) cpad16_kernel(const double* __restrict__ C, int nbf, int nocc, int nbfp, int np,
+                                                      double* __restrict__ Cp) {
+  __shared__ double red[16][16];
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15, i = 16 * blockIdx.y + c, nu = 64 * blockIdx.x + r;
+  const double own = nu < nbf && i < nocc ? C[(int64_t)nu * nocc + i] : 0.0;
+  double z = 0.0;  // 0 or NaN
+  if (i < nocc) {
+#pragma unroll 8
+    for (int k = r; k < nbf; k += 64) z = fma(0.0, C[(int64_t)k * nocc + i], z);
+  }
+  z += __shfl_xor(z, 16);  // a wave has 4 of the 64 rows
+  z += __shfl_xor(z, 32);
+  if ((r & 3) == 0) red[r >> 2][c] = z;
+  __syncthreads();
+  z = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) z += red[q][c];
+  if (nu < nbfp) Cp[(int64_t)nu * np + ((nu & 1) && np % 32 == 0 ? i ^ 16 : i)] = own + z;
 }
 
 extern __shared__ __attribute__((aligned(1024))) double kxs_lds[];
@@ -339,6 +354,11 @@ __global__ void __launch_bounds__(KS_T, 2) kx64s_kernel(const float* __restrict_
     load(J, 1, 1);
     stage_sync();
     frag(0, 0, 0);
+  } else {  // no tile at all: zero times C, of which one row tells whether it is finite
+#pragma unroll
+    for (int a = 0; a < RW; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[a][b] = v4d(0.0 * Cp[16 * b + li]);
   }
   while (J < nt) {
     advance();
@@ -590,11 +610,11 @@ static F64Plan f64_plan(const JKArgs& a, int nocc) {
 }
 
 static void pad_cocc(const JKArgs& a, const double* C, int nocc, const F64Plan& p, double* Cp, hipStream_t st) {
-  const dim3 g((unsigned)(((int64_t)p.nbfp * p.np + 255) / 256));
   if (kxs_rows(a.nbf, nocc))
-    hipLaunchKernelGGL(cpad16_kernel, g, dim3(256), 0, st, C, a.nbf, nocc, p.nbfp, p.np, Cp);
+    hipLaunchKernelGGL(cpad16_kernel, dim3((p.nbfp + 63) / 64, p.np / 16), dim3(1024), 0, st, C, a.nbf, nocc, p.nbfp,
+                       p.np, Cp);
   else
-    hipLaunchKernelGGL(cpad_kernel, g, dim3(256), 0, st, C, a.nbf, nocc, p.nbfp, p.np, Cp);
+    hipLaunchKernelGGL(cpad_kernel, dim3((unsigned)(((int64_t)p.nbfp * p.np + 255) / 256)), dim3(256), 0, st, C, a.nbf, nocc, p.nbfp, p.np, Cp);
 }
 
 size_t half_transform_f64_work(const JKArgs& a, int nocc) {
