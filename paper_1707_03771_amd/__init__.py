@@ -189,28 +189,51 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
+_PLAIN = {float, int, bool, np.float64, np.float32}  # numbers that one array takes as they are
+
+
 class _ShellArray:
     """dfx_shell[] over shell dicts (center, l, exps, coefs); keeps the arrays alive.
-    Filled column by column: a thousand shells in well under a millisecond."""
+    center is anything whose first three items are numbers, exps and coefs whatever
+    makes a float64 array, its first axis the primitives.  Lists of numbers are
+    gathered column by column: a thousand shells in about a millisecond."""
 
     def __init__(self, shells):
         n = self.n = len(shells)
         table = np.zeros(max(1, n), dtype=np.dtype(Shell))
+        self.keep = [table]
         if n:
-            flat, ptr = {}, {}
             for key in ("exps", "coefs"):
-                cols = [c if isinstance(c, (list, tuple)) else np.ascontiguousarray(c, dtype=np.float64)
-                        for c in (s[key] for s in shells)]
-                lens = np.array([len(c) for c in cols], dtype=np.int64)
-                flat[key] = np.fromiter(itertools.chain.from_iterable(cols), dtype=np.float64, count=int(lens.sum()))
-                ptr[key] = flat[key].ctypes.data + 8 * (np.cumsum(lens) - lens)
+                cols = [s[key] for s in shells]
+                flat, size, prims = self._numbers(cols) or self._arrays(cols)
+                self.keep.append(flat)
+                table[key][:n] = flat.ctypes.data + 8 * (np.cumsum(size) - size)
                 if key == "exps":
-                    table["nprim"][:n] = lens
-            table["xyz"][:n] = [s["center"][:3] for s in shells]
+                    table["nprim"][:n] = prims
+            ctr = [s["center"] for s in shells]
+            if not all(type(c) is np.ndarray and c.shape == (3,) and c.dtype.kind == "f" for c in ctr):
+                ctr = [[float(c[0]), float(c[1]), float(c[2])] for c in ctr]
+            table["xyz"][:n] = ctr
             table["l"][:n] = [int(s["l"]) for s in shells]
-            table["exps"][:n], table["coefs"][:n] = ptr["exps"], ptr["coefs"]
-            self.keep = [flat, table]
         self.arr = (Shell * max(1, n)).from_buffer(table)
+
+    @staticmethod
+    def _numbers(cols):
+        """All columns in one array, with the elements and the primitives of each; None
+        unless every one is a list or tuple of plain numbers."""
+        if not all(type(c) in (list, tuple) for c in cols):
+            return None
+        size = np.array([len(c) for c in cols], dtype=np.int64)
+        flat = list(itertools.chain.from_iterable(cols))
+        if not all(map(_PLAIN.__contains__, map(type, flat))):
+            return None
+        return np.array(flat, dtype=np.float64), size, size
+
+    @staticmethod
+    def _arrays(cols):
+        arrs = [np.ascontiguousarray(c, dtype=np.float64) for c in cols]
+        return (np.concatenate([a.ravel() for a in arrs]), np.array([a.size for a in arrs], dtype=np.int64),
+                np.array([len(a) for a in arrs], dtype=np.int64))
 
 
 class _GeomC:
