@@ -10,9 +10,10 @@
 namespace dfx {
 
 // ---- products on FP32 matrix cores (v_mfma_f32_16x16x4f32: FP32 products and sums) ----
-// A workgroup owns a T x T tile of the result, T = 16, 32 or 64; its eight waves take
-// blocks of 16 k in turn, operands straight from memory to registers (two to
-// four blocks in flight), and their sums are added in LDS in a fixed order.
+// A workgroup owns a T x T tile of the result, T = 16, 32 or 64; its eight waves (one
+// for long batches of narrow layers, forward_one_wave) take blocks of 16 k in turn,
+// operands straight from memory to registers (two to four blocks in flight), and
+// their sums are added in LDS in a fixed order.
 // MFMA operands: lane (li, lk) = (lane % 16, lane / 16) gives A[row li][k lk] and
 // B[k lk][col li]; the result's element r of that lane is C[row 4 lk + r][col li].
 // Within a block of 16 the lane has k = 4 lk .. 4 lk + 3, one MFMA each.
@@ -24,6 +25,8 @@ namespace dfx {
 // 256^3 x 70, batch 128: 435 us with 64 x 64 tiles through LDS and all of these
 // launches apart, 100 so.
 constexpr int MW = 8, MT = 64 * MW;  // waves and threads of a workgroup
+// results per thread of a workgroup of NW waves on a tile of 16 F
+constexpr int mlp_nout(int F, int NW) { return (256 * F * F + 64 * NW - 1) / (64 * NW); }
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -35,8 +38,8 @@ struct MatOp {
   int n;
 };
 
-// the 16 F rows from x0 of an operand as a wave reads them: blocks of 16 k, MW apart
-template <bool KC, int F>
+// the 16 F rows from x0 of an operand as a wave reads them: blocks of 16 k, NW apart
+template <bool KC, int F, int NW>
 struct TileOp {
   const float* p;  // x0 and the wave's first block (wave-uniform)
   int64_t ld;
@@ -51,7 +54,7 @@ struct TileOp {
     }
   }
   __device__ __forceinline__ void load(int64_t i, float (&v)[F][4]) const {
-    const float* q = p + i * (KC ? 16 * MW : 16 * MW * ld);
+    const float* q = p + i * (KC ? 16 * NW : 16 * NW * ld);
 #pragma unroll
     for (int f = 0; f < F; ++f) {
       if (KC) {
@@ -66,7 +69,7 @@ struct TileOp {
   }
   // the last block, of which k < kr exist
   __device__ __forceinline__ void load_tail(int64_t i, int kr, int lk, float (&v)[F][4]) const {
-    const float* q = p + i * (KC ? 16 * MW : 16 * MW * ld);
+    const float* q = p + i * (KC ? 16 * NW : 16 * NW * ld);
 #pragma unroll
     for (int f = 0; f < F; ++f)
 #pragma unroll
@@ -80,11 +83,12 @@ __device__ __forceinline__ int tile_row(int e) { return (e >> 8) / F * 16 + 4 * 
 template <int F>
 __device__ __forceinline__ int tile_col(int e) { return (e >> 8) % F * 16 + (e & 15); }
 
-// The tile's product over k < K: element e = threadIdx.x + MT h < 256 F^2 in out[h].
+// The tile's product over k < K: element e = threadIdx.x + 64 NW h < 256 F^2 in out[h].
 // rsum (ROWSUM): the sums of A's 16 F rows over k, in threads 0 .. 16 F - 1.
-template <bool KA, bool KB, int F, bool ROWSUM>
+template <bool KA, bool KB, int F, bool ROWSUM, int NW>
 __device__ __forceinline__ void tile_gemm(const MatOp& A, const MatOp& B, int m0, int n0, int K, float* red,
-                                          float (&out)[(F * F + 1) / 2], float& rsum) {
+                                          float (&out)[mlp_nout(F, NW)], float& rsum) {
+  constexpr int MW = NW, MT = 64 * NW;
   constexpr int D = F == 4 ? 2 : 4;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lk = lane >> 4;
@@ -97,8 +101,8 @@ __device__ __forceinline__ void tile_gemm(const MatOp& A, const MatOp& B, int m0
     for (int j = 0; j < F; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
   }
   float a[D][F][4], b[D][F][4];
-  TileOp<KA, F> oa;
-  TileOp<KB, F> ob;
+  TileOp<KA, F, NW> oa;
+  TileOp<KB, F, NW> ob;
   oa.init(A, m0, w, li, lk);
   ob.init(B, n0, w, li, lk);
   auto step = [&](const float (&x)[F][4], const float (&y)[F][4]) {
@@ -180,20 +184,22 @@ __device__ __forceinline__ void tile_gemm(const MatOp& A, const MatOp& B, int m0
 // Layer forward: z = a W^T + b.  hidden: Z = z, out = silu(z).  Otherwise out = z, or
 // with T the loss: out = 2 (z - T) / n over all n = rows x cols outputs, and the
 // workgroup's sum of (z - T)^2 to part.
-template <int F>
-__global__ void __launch_bounds__(MT) layer_forward_kernel(int rows, int cols, int K, const float* __restrict__ a,
-                                                           const float* __restrict__ W, const float* __restrict__ bias,
-                                                           int hidden, float* __restrict__ Z, float* __restrict__ out,
-                                                           const float* __restrict__ T, double* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) float red[MW * 256 * F * (F == 4 ? 1 : F)];
+template <int F, int NW>
+__global__ void __launch_bounds__(64 * NW) layer_forward_kernel(int rows, int cols, int K, const float* __restrict__ a,
+                                                                const float* __restrict__ W,
+                                                                const float* __restrict__ bias, int hidden,
+                                                                float* __restrict__ Z, float* __restrict__ out,
+                                                                const float* __restrict__ T,
+                                                                double* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) float red[NW * 256 * F * (F == 4 ? 1 : F)];
   const int nt = (cols + 16 * F - 1) / (16 * F);
   const int m0 = blockIdx.x / nt * 16 * F, n0 = blockIdx.x % nt * 16 * F;
-  float v[(F * F + 1) / 2], rsum;
-  tile_gemm<true, true, F, false>(MatOp{a, K, rows}, MatOp{W, K, cols}, m0, n0, K, red, v, rsum);
+  float v[mlp_nout(F, NW)], rsum;
+  tile_gemm<true, true, F, false, NW>(MatOp{a, K, rows}, MatOp{W, K, cols}, m0, n0, K, red, v, rsum);
   double s = 0.0;
 #pragma unroll
-  for (int h = 0; h < (F * F + 1) / 2; ++h) {
-    const int e = threadIdx.x + MT * h, r = m0 + tile_row<F>(e), c = n0 + tile_col<F>(e);
+  for (int h = 0; h < mlp_nout(F, NW); ++h) {
+    const int e = threadIdx.x + 64 * NW * h, r = m0 + tile_row<F>(e), c = n0 + tile_col<F>(e);
     if (e >= 256 * F * F || r >= rows || c >= cols) continue;
     const int64_t i = (int64_t)r * cols + c;
     const float z = v[h] + bias[c];
@@ -216,7 +222,7 @@ __global__ void __launch_bounds__(MT) layer_forward_kernel(int rows, int cols, i
   __syncthreads();
   if (threadIdx.x == 0) {
     s = 0.0;
-    for (int x = 0; x < MW; ++x) s += ws[x];
+    for (int x = 0; x < NW; ++x) s += ws[x];
     part[blockIdx.x] = s;
   }
 }
@@ -235,13 +241,13 @@ __global__ void __launch_bounds__(MT) layer_backward_kernel(int rows, int no, in
   const bool da = (int)blockIdx.x < nda;
   const int t = da ? blockIdx.x : blockIdx.x - nda;
   const int m0 = t / nt * 16 * F, n0 = t % nt * 16 * F;
-  float v[(F * F + 1) / 2], rsum;
+  float v[mlp_nout(F, MW)], rsum;
   if (da)
-    tile_gemm<true, false, F, false>(MatOp{G, no, rows}, MatOp{W, ni, ni}, m0, n0, no, red, v, rsum);
+    tile_gemm<true, false, F, false, MW>(MatOp{G, no, rows}, MatOp{W, ni, ni}, m0, n0, no, red, v, rsum);
   else
-    tile_gemm<false, false, F, true>(MatOp{G, no, no}, MatOp{a, ni, ni}, m0, n0, rows, red, v, rsum);
+    tile_gemm<false, false, F, true, MW>(MatOp{G, no, no}, MatOp{a, ni, ni}, m0, n0, rows, red, v, rsum);
 #pragma unroll
-  for (int h = 0; h < (F * F + 1) / 2; ++h) {
+  for (int h = 0; h < mlp_nout(F, MW); ++h) {
     const int e = threadIdx.x + MT * h, r = m0 + tile_row<F>(e), c = n0 + tile_col<F>(e);
     if (e >= 256 * F * F || r >= (da ? rows : no) || c >= ni) continue;
     const int64_t i = (int64_t)r * ni + c;
@@ -264,6 +270,16 @@ static int tiles_of(int64_t m, int64_t n, int F) { return (int)(((m + 16 * F - 1
 // (128 tiles) 100 / 117 / 159; 454 x 512^2 x 70, batch 1024 (2048) 188 / 157 / 208;
 // 1024^3 x 256, batch 1024 (4096) 454 / 320 / 290; batch 4096 1841 / 1236 / 1023.
 static int tile_frags(int64_t tiles16) { return tiles16 >= 4096 ? 4 : tiles16 > 1024 ? 2 : 1; }
+
+// A long batch through a narrow layer has tiles enough for single waves: over a short K
+// (some eight blocks of 16) most of the eight waves of a workgroup have nothing to do
+// but to wait for the sum, and tiles of 64 are mostly padding where there are few
+// columns.  One wave a tile of 16 or 32 then.  Forward pass, batch 100000, us, eight
+// waves and 64 x 64 / one wave (64 x 64 through LDS before either): 4-4-4 100 / 49
+// (68), 16-16-16 96 / 55 (82), 32-32-32 387 / 335 (379), 64-16-64 370 / 328 (360).
+// From K = 256 and 64 columns on neither is ahead (256^3, batch 5000: 108 / 90, 454 x
+// 256 x 70, batch 100000: 940 / 949).
+static bool forward_one_wave(int64_t tiles16, int K, int cols) { return tiles16 >= 4096 && (K <= 128 || cols <= 32); }
 
 __global__ void adam_kernel(float* theta, const float* __restrict__ g, float* m, float* v, int64_t n, float lr,
                             float b1, float b2, float eps, float c1, float c2) {
@@ -319,10 +335,14 @@ static int forward_impl(const std::vector<int>& w, const float* theta, const flo
     wp += 2 * (size_t)batch * no;
     const float* b = p + (size_t)ni * no;
     const float* Tl = hidden ? nullptr : T;
-    const int F = tile_frags(tiles_of(batch, no, 1));
+    const int64_t tiles16 = tiles_of(batch, no, 1);
+    const bool one = forward_one_wave(tiles16, ni, no);
+    const int F = one ? (no <= 16 ? 1 : 2) : tile_frags(tiles16);
     tiles = tiles_of(batch, no, F);
-    hipLaunchKernelGGL(F == 4 ? layer_forward_kernel<4> : F == 2 ? layer_forward_kernel<2> : layer_forward_kernel<1>,
-                       dim3(tiles), dim3(MT), 0, st, batch, no, ni, a, p, b, hidden, Z, A, Tl, part);
+    auto* kern = F == 4   ? layer_forward_kernel<4, MW>
+                 : F == 2 ? (one ? layer_forward_kernel<2, 1> : layer_forward_kernel<2, MW>)
+                          : (one ? layer_forward_kernel<1, 1> : layer_forward_kernel<1, MW>);
+    hipLaunchKernelGGL(kern, dim3(tiles), dim3(one ? 64 : MT), 0, st, batch, no, ni, a, p, b, hidden, Z, A, Tl, part);
     p += (size_t)ni * no + no;
     a = A;
   }
