@@ -772,7 +772,7 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k
     a[i][c] = (i < kb && c <= i) ? Jb[(int64_t)i * n + c] : (i == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  for (int p = 0; p < CB; p += CP) {
+  for (int p = 0; p < kb; p += CP) {  // panels past kb stay the identity
     if (tid < CB) {
       const int t = tid;
       double v[CP];
@@ -818,7 +818,7 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* J, int n, int k
   }
   // inverse, X[i][c] = -(sum_{k=c}^{i-1} L[i][k] X[k][c]) / L[i][i], X[c][c] = 1 / L[c][c]
   const int c = tid & 63, q = tid >> 6;
-  for (int g = 0; g < CB; g += CP) {
+  for (int g = 0; g < kb; g += CP) {
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll 8
     for (int k = 0; k < g; ++k) {
