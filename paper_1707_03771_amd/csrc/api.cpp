@@ -387,7 +387,12 @@ std::unique_ptr<dfx_B> dfx::build_B(HostShells bas, HostShells auxs, double tau_
       a.npairs = (int)sp_f[cls].size();
       a.q = sq[cls].as<double>();
       a.rys = rys;
-      schwarz_dispatch(cls / 4, cls % 4, a, st);
+      int64_t quartets = 0;
+      for (size_t k = 0; k < sp_f[cls].size(); ++k) {
+        const int64_t q = (int64_t)B->bas.nprim[sp_f[cls][k]] * B->bas.nprim[sp_s[cls][k]];
+        quartets = std::max(quartets, q * q);
+      }
+      schwarz_dispatch(cls / 4, cls % 4, a, quartets, st);
     }
     DFX_HIP(hipGetLastError());
     B->Qab.assign((size_t)nsh * nsh, 0.0);

@@ -35,7 +35,7 @@ __constant__ SuppRow g_supp[4][7] = {
 // shell pair (LA >= LB after swapping), lanes over the spherical (mu, nu).
 // Per root, lanes 0..2 build the four-index 2D integrals of one direction in
 // LDS; every lane then sums its sparse spherical combination.
-template <int LA, int LB>
+template <int LA, int LB, bool STAGE>
 __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
   constexpr int NR = (2 * (LA + LB)) / 2 + 1;
   constexpr int E = LA + LB;
@@ -44,14 +44,21 @@ __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
   // one T per primitive quartet and pair: the few coefficients it needs are read
   // from the table in L2 (staging all of it in LDS for each pair was most of the
   // kernel), and powers come from a table in LDS.  (f d) pairs of 40 carbons:
-  // 2.18 -> 0.27 ms; (d d) of 8 waters 0.32 -> 0.09 ms
-  const double* __restrict__ tab = a.rys + rys_dev_off(NR);
+  // 2.18 -> 0.27 ms; (d d) of 8 waters 0.32 -> 0.09 ms.  STAGE (schwarz_dispatch): in
+  // LDS all the same
+  __shared__ double staged[STAGE ? rys_dev_size(NR) : 1];
+  if (STAGE) rys_stage<NR>(staged, a.rys);
+  const double* __restrict__ tab = STAGE ? staged : a.rys + rys_dev_off(NR);
   __shared__ double H4[3][N4];
-  __shared__ signed char pwa[ncart(LA)][4], pwb[ncart(LB)][4];
+  // (ints: a store of a character might change any memory, and the loads of exponents
+  // and coefficients after it are then no scalar loads)
+  __shared__ int pwa[ncart(LA)][3], pwb[ncart(LB)][3];
   const int p = blockIdx.x;
   if (p >= a.npairs) return;
-  for (int e = threadIdx.x; e < 3 * ncart(LA); e += 64) pwa[e / 3][e % 3] = (signed char)cpow(LA, e / 3, e % 3);
-  for (int e = threadIdx.x; e < 3 * ncart(LB); e += 64) pwb[e / 3][e % 3] = (signed char)cpow(LB, e / 3, e % 3);
+  if (LA)
+    for (int e = threadIdx.x; e < 3 * ncart(LA); e += 64) pwa[e / 3][e % 3] = cpow(LA, e / 3, e % 3);
+  if (LB)
+    for (int e = threadIdx.x; e < 3 * ncart(LB); e += 64) pwb[e / 3][e % 3] = cpow(LB, e / 3, e % 3);
   const int s1 = a.pf[p], s2 = a.ps[p];
   const int lane = threadIdx.x;
   constexpr int SA = 2 * LA + 1, SB = 2 * LB + 1;
@@ -65,6 +72,8 @@ __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
   const int n2 = a.sh.nprim[s2], o2 = a.sh.poff[s2];
   const SuppRow ra = g_supp[LA][active ? ma : 0], rb = g_supp[LB][active ? mb : 0];
   double acc = 0.0;
+  // two s functions have one term: its factor once, not from memory in every quartet
+  const double t4 = ra.t[0] * rb.t[0] * ra.t[0] * rb.t[0];
   constexpr double TWO_PI_52 = 34.98683665524972;
   for (int i1 = 0; i1 < n1; ++i1)
     for (int j1 = 0; j1 < n2; ++j1) {
@@ -143,7 +152,14 @@ __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
                 }
             }
             __syncthreads();
-            if (active) {
+            if (LA + LB == 0) {
+              if (active) {
+                double v = t4;
+#pragma unroll
+                for (int x = 0; x < 3; ++x) v *= H4[x][0];
+                acc += v;
+              }
+            } else if (active) {
               for (int i = 0; i < ra.n; ++i)
                 for (int j = 0; j < rb.n; ++j)
                   for (int k = 0; k < ra.n; ++k)
@@ -152,8 +168,9 @@ __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
                       double v = ra.t[i] * rb.t[j] * ra.t[k] * rb.t[l];
 #pragma unroll
                       for (int x = 0; x < 3; ++x) {
-                        const int pa = pwa[ci][x], pb = pwb[cj][x];
-                        const int pc = pwa[ck][x], pd = pwb[cl][x];
+                        // (an s function has no power to look up)
+                        const int pa = LA ? pwa[ci][x] : 0, pb = LB ? pwb[cj][x] : 0;
+                        const int pc = LA ? pwa[ck][x] : 0, pd = LB ? pwb[cl][x] : 0;
                         v *= H4[x][((pa * D2 + pb) * D1 + pc) * D2 + pd];
                       }
                       acc += v;
@@ -169,11 +186,18 @@ __global__ void __launch_bounds__(64) schwarz_kernel(SchwarzArgs a) {
   if (lane == 0) a.q[p] = sqrt(fmax(m, 0.0));
 }
 
-void schwarz_dispatch(int LA, int LB, SchwarzArgs a, hipStream_t st) {
+// quartets: the most primitive quartets of a pair.  From four primitives a shell on, the
+// coefficients of s and p pairs are read often enough to be worth staging.  A fit of 60
+// p shells of 3, 4, 6 and 10 primitives, ms: 1.00, 1.99, 7.2 and 49.2 from L2; 1.04, 1.83,
+// 6.6 and 46.0 staged; 60 s shells of 10: 11.6 with the factor in memory and staged, 12.9
+// from L2, 11.4 so.  With d functions the sums over components outweigh them (1 to
+// 2% either way).
+void schwarz_dispatch(int LA, int LB, SchwarzArgs a, int64_t quartets, hipStream_t st) {
   const dim3 g(a.npairs), b(64);
-#define SC(X, Y)                                                        \
-  case (X)*8 + (Y):                                                     \
-    hipLaunchKernelGGL((schwarz_kernel<X, Y>), g, b, 0, st, a);         \
+  const bool stage = quartets >= 256;
+#define SC(X, Y)                                                                                                 \
+  case (X)*8 + (Y):                                                                                              \
+    hipLaunchKernelGGL((stage ? schwarz_kernel<X, Y, (X < 2)> : schwarz_kernel<X, Y, false>), g, b, 0, st, a); \
     break;
   switch (LA * 8 + LB) {
     SC(0, 0) SC(1, 0) SC(1, 1) SC(2, 0) SC(2, 1) SC(2, 2) SC(3, 0) SC(3, 1) SC(3, 2) SC(3, 3)

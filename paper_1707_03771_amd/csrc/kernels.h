@@ -30,7 +30,7 @@ struct OneEArgs {
 
 void eri3_dispatch(int LA, int LB, int LC, bool unitb, int mode, Eri3Args a, hipStream_t st);
 void metric_dispatch(int LA, int LC, Eri3Args a, hipStream_t st);
-void schwarz_dispatch(int LA, int LB, SchwarzArgs a, hipStream_t st);
+void schwarz_dispatch(int LA, int LB, SchwarzArgs a, int64_t quartets, hipStream_t st);
 void onee_dispatch(int LA, int LB, OneEArgs a, hipStream_t st);
 void aux_schwarz(const double* J, int64_t ld, DevShells aux, double* q, hipStream_t st);
 
