@@ -661,7 +661,7 @@ struct Scf {
   // The purification's steps up to TC2_MAX rows, a launch each (tc2_step_kernel);
   // the host looks at the state every TC2_BATCH steps.  The bounds are in part; the
   // shares of the traces and the state, of two steps, in gw.  P: the projector.
-  static constexpr int TC2_MAX = 1536, TC2_BATCH = 8;
+  static constexpr int TC2_MAX = 1792, TC2_BATCH = 8;
   bool tc2_steps(const double* F, double*& P, double*& P2, int& steps, const char*& why) {
     const int mt = (m + SG_T - 1) / SG_T, ntl = mt * (mt + 1) / 2;
     double* buf[2] = {P, P2};
@@ -685,9 +685,11 @@ struct Scf {
     P2 = buf[(steps & 1) ^ 1];
     return h.done && h.ok;
   }
-  // The same for larger m, where the tiles of 64 and 128 of the symmetric product
-  // take less time (every tile of 32 reads 64 rows of P again, through L2): a step
-  // took 76 us so and 62 in one launch at m = 1450, a tenth less so at 1930.
+  // The same for larger m, with the symmetric product in tiles of 64 and 128 (every tile
+  // of 32 reads 64 rows of P again, through L2).  Helium lines, us a step with the QR
+  // counted in, so and in one launch: m = 1450 378 and 312, 1536 372 and 277, 1664 458 and
+  // 382, 1800 479 and 471, 1864 432 and 433, 1930 442 and 486: the line lies at the last
+  // multiple of the tiles at which one launch was ahead.
   bool tc2_steps_large(const double* F, double*& P, double*& P2, int& steps, const char*& why) {
     double b[2];
     DFX_HIP(hipMemcpyAsync(b, part.p, sizeof b, hipMemcpyDeviceToHost, st));
