@@ -522,9 +522,13 @@ void k_reduce(const double* P, int ns, int nbf, double* K, bool accumulate, hipS
 // more workgroups on the CU; the workgroups are dealt to 32 CUs on each of 8
 // XCDs, so the CU with the most of them sets the time; every slice is written
 // and read again once, and more than one slice takes another launch (5 us).
-// Tiles of 64 read X through L2 twice as often, which begins to tell between 1200
-// functions (11.0 ms, no slower than 128) and 1354 and 1536 (22.9 and 22.6 ms in
-// tiles of 64, 22.2 and 20.7 of 128).
+// Tiles of 64 read X through L2 twice as often.  Over a long k-range (X of several GB)
+// that begins to tell between 1200 functions (11.0 ms, no slower than 128) and 1354
+// and 1536 (22.9 and 22.6 ms in tiles of 64, 22.2 and 20.7 of 128), which is where the
+// line lies.  Over a short one it comes later: at kdim = 51200 K takes 1.76, 2.37,
+// 2.64, 2.87 and 3.42 ms in tiles of 64 and 1.89, 2.56, 3.00, 3.02 and 3.32 of 128 at
+// 1280, 1472, 1600, 1664 and 1792 functions, and the plan, whose efficiencies do not
+// know of kdim, takes 128 at all of these.
 // Before, 128-tiles and about 2048 workgroups at any size: nbf = 192, kdim =
 // 33920 (3 tiles, 688 slices): 72 us + 255 us for the sum.
 struct SyrkPlan {
