@@ -301,7 +301,11 @@ static double any_cycles(int M, int N, int K, int batch) {
 
 static int gemm_tiles(int M, int N) { return ((M + GM - 1) / GM) * ((N + GN - 1) / GN); }
 
-// rows of both operands 16-byte aligned (the lanes' offsets fit 32 bits)
+// rows of both operands 16-byte aligned (the lanes' offsets fit 32 bits).  L has a row
+// per auxiliary function, so with an odd number of them its rows are not, and the fit's
+// updates take dgemm_any_kernel: 730 functions with 3106 auxiliary ones 33.3 ms a fit,
+// with 3105 43.8 (both kernels register-staged: 74.3 and 77.7, Cholesky blocks and set-up
+// among them).
 static bool gemm_aligned(const GemmF64& g) {
   auto ok = [](const double* p, int64_t ld, int64_t s) {
     return !(reinterpret_cast<uintptr_t>(p) & 15) && ld % 2 == 0 && s % 2 == 0 && ld < (1 << 25);
